@@ -15,14 +15,18 @@
 // 16-byte vectors along k straight from global memory (W is stored
 // transposed, Wt[n][k]); the k index of a 16-wide chunk is permuted
 // identically on both operands, which leaves the contraction unchanged.
+#include <type_traits>
+
 #include "dpa1_internal.h"
 #include "ln_res.h"
+#include "split.h"
 
 namespace dpa1 {
 
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+using split::halfx8;
 
 __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -461,98 +465,88 @@ __global__ __launch_bounds__(256, 2) void k_gemm_lds(GemmArgs a, Epi epi) {
   }
 }
 
-// Resident-weight variant for the long-K FP32 adjoint of the QKV projection
-// (K = KCH*16 = 384 rows of W, Nreal <= NT*16 output columns): the whole
-// W^T[Nreal][K] block lives in LDS for the launch (one 8-wavefront workgroup
-// per CU), so the k loop has no barrier and reads no weights from L2.  Each
-// wavefront walks its own 64-row tiles independently and streams X through
-// a ring of three 16-deep chunks, two chunks ahead of the one it multiplies;
-// the ring runs on across tile boundaries, so the next tile's first chunks
-// arrive during the current tile's last ones and its epilogue.  Output
-// columns past Nreal read a clamped W row; the epilogue zeroes them.
-template <int MT, int NT, int KCH, class Epi>
-__global__ __launch_bounds__(512, 1) void k_gemm_wres(GemmArgs a, Epi epi) {
-  static_assert(KCH % 3 == 0, "the chunk ring is unrolled by three");
-  constexpr int K = KCH * 16;
-  constexpr int LDW = K + 4;
-  extern __shared__ float wsm[];  // [Nreal][LDW], then cs
+// Resident-weight product on two-term f16 operands (split.h), for the FP32
+// adjoints of the attention layers' projections: of QKV (384 deep, 100
+// columns) and of the output projection (100 deep, 128 columns).  Bound by
+// HBM once the matrix cores take 1/4 of their FP32 time.  A workgroup packs
+// its W^T block [Nreal][KS] into LDS once; each wavefront then walks over 16-
+// row tiles in wave-major order (the last round's tiles land on different
+// CUs).  A tile's whole K extent sits in registers, so each row's own scale
+// comes from a maximum over its lanes' values without a second pass, and a
+// chunk's registers take the next tile's chunk as soon as it is multiplied:
+// the loads of a whole tile (24 KB of QKV gradients) are in flight per
+// wavefront.  Measured at 1.31 M rows: QKV adjoint 1.15 -> 0.79 ms (3.85 GB,
+// 4.9 TB/s), output projection 0.33 -> 0.28 ms (1.26 GB), against FP32 MFMAs
+// on 64-row (32-row) tiles.  Output columns past Nreal read a clamped W row
+// (the epilogue zeroes or skips them).
+// KT = 1: X and W hold data only in the first four columns of the last 16-wide
+// chunk, KS ends there, and every lane group reads group 0's values of W
+// against X's zeros.
+template <int NT, int KCH, int KT, int WAVES, class Epi>
+__global__ __launch_bounds__(64 * WAVES, 1) void k_gemm_split(GemmArgs a, Epi epi) {
+  constexpr int KS = KT == 1 ? 16 * (KCH - 1) + 4 : 16 * KCH;  // staged depth
+  // row stride of 4 mod 8 dwords: eight rows' 16-byte reads touch 32 banks
+  constexpr int LDW = KS % 8 == 4 ? KS : KS + 4;
+  extern __shared__ float wsm[];  // packed W^T [nst][LDW], then the column vectors
+  split::packx4 *wp = (split::packx4 *)wsm;
   const int M = a.Mptr ? *a.Mptr : a.Mmax;
-  const int nreal = a.Nreal;
-  for (int idx = threadIdx.x; idx < nreal * (K / 4); idx += blockDim.x) {
-    const int n = idx / (K / 4), c4 = idx % (K / 4);
-    *(float4 *)(wsm + n * LDW + 4 * c4) = *(const float4 *)(a.Wt + (size_t)n * a.K + 4 * c4);
+  const int nst = min(NT * 16, a.Nreal);  // staged rows of W^T
+  for (int idx = threadIdx.x; idx < nst * (KS / 4); idx += 64 * WAVES) {
+    const int n = idx / (KS / 4), c4 = idx % (KS / 4);
+    const floatx4 v = *(const floatx4 *)(a.Wt + (size_t)n * a.K + 4 * c4);
+    wp[n * (LDW / 4) + c4] = split::pack(v * a.wup);
   }
-  float *cs = wsm + nreal * LDW;  // [Epi::kCols][NT * 16]
+  float *cs = wsm + nst * LDW;  // [Epi::kCols][NT * 16]
   stage_cols<Epi, NT>(epi, 0, a.Npad, cs);
   __syncthreads();
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int ntt = a.Npad / 16;
-  // wave-major tile order: the tiles left over after the last full round
-  // land on different CUs (1.21 -> 1.16 ms against the block-major order)
-  const int stride = gridDim.x * 8 * 16 * MT;  // rows between a wave's consecutive tiles
-  int row0 = (wave * gridDim.x + blockIdx.x) * 16 * MT;
+  const int stride = gridDim.x * WAVES * 16;  // rows between a wave's consecutive tiles
+  int row0 = (wave * gridDim.x + blockIdx.x) * 16;
   if (row0 >= M) return;  // no barrier follows
   int lane_it = lane;
   asm volatile("" : "+v"(lane_it));
   const int r = lane_it & 15;
   const int g = lane_it >> 4;
-  const float *wl[NT];
+  const split::packx4 *wl[NT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int n = nt * 16 + r < nreal ? nt * 16 + r : nreal - 1;
-    wl[nt] = wsm + n * LDW + 4 * g;
-  }
-  auto rows_of = [&](int base, const float *(&xp)[MT]) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int row = base + mt * 16 + r;
-      xp[mt] = a.X + (size_t)(row < M ? row : 0) * a.ldx + 4 * g;
-    }
-  };
-  const float *xc[MT], *xn[MT];
-  rows_of(row0, xc);
-  rows_of(row0 + stride, xn);
-  floatx4 xb[3][MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    xb[0][mt] = *(const floatx4 *)(xc[mt]);
-    xb[1][mt] = *(const floatx4 *)(xc[mt] + 16);
-  }
+  for (int nt = 0; nt < NT; ++nt)
+    wl[nt] = wp + (nt * 16 + r < nst ? nt * 16 + r : nst - 1) * (LDW / 4);
+  floatx4 x[1][KCH];
+  load_x_tile<1, KCH, 0, 4>(a, row0, M, r, g, x);
   for (; row0 < M; row0 += stride) {
-    floatx4 acc[MT][NT];
+    float m = 0.f;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int c = 0; c < KCH; ++c) m = split::max_abs(m, x[0][c]);
+    const split::Scale sc = split::scale_of(split::row_max(m));
+    split::packx4 xp[KCH];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int c = 0; c < KCH; c += 3) {
+    for (int c = 0; c < KCH; ++c) xp[c] = split::pack(x[0][c] * sc.up);
+    // next tile (rows past the last one read row 0, unused)
+    const int rown = row0 + stride + r;
+    const float *xn = a.X + (size_t)(rown < M ? rown : 0) * a.ldx + 4 * g;
+    floatx4 acc[1][NT];
 #pragma unroll
-      for (int u = 0; u < 3; ++u) {
-        // chunk c + u sits in slot u; chunk c + u + 2 (of this tile, or of
-        // the next one past the last chunk) goes into the slot freed by the
-        // previous step
-        const int cp = c + u + 2;
-        const bool here = cp < KCH;
+    for (int nt = 0; nt < NT; ++nt) acc[0][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          xb[(u + 2) % 3][mt] = *(const floatx4 *)(here ? xc[mt] + 16 * cp : xn[mt] + 16 * (cp - KCH));
-        floatx4 w[NT];
+    for (int c = 0; c < KCH; ++c) {
+      const int q = KT == 1 && c == KCH - 1 ? 4 * c : 4 * c + g;
+      split::packx4 w[NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) w[nt] = *(const floatx4 *)(wl[nt] + 16 * (c + u));
-        __builtin_amdgcn_sched_barrier(0);
+      for (int nt = 0; nt < NT; ++nt) w[nt] = wl[nt][q];
+      __builtin_amdgcn_sched_barrier(0);  // one chunk of weights live at a time
+      const halfx8 lo = split::dup_lo(xp[c]), hi = split::dup_hi(xp[c]);
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+      for (int nt = 0; nt < NT; ++nt) acc[0][nt] = split::mfma(w[nt], lo, acc[0][nt]);
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma4(w[nt][t], xb[u][mt][t], acc[mt][nt]);
-      }
+      for (int nt = 0; nt < NT; ++nt) acc[0][nt] = split::mfma(w[nt], hi, acc[0][nt]);
+      x[0][c] = *(const floatx4 *)(xn + 16 * c);
     }
-    epi.template apply<MT, NT>(acc, row0, 0, ntt, lane, M, cs);
+    const float d = sc.down * a.wdown;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) xc[mt] = xn[mt];
-    rows_of(row0 + 2 * stride, xn);
+    for (int nt = 0; nt < NT; ++nt) acc[0][nt] *= d;
+    epi.template apply<1, NT>(acc, row0, 0, ntt, lane, M, cs);
   }
 }
 
@@ -1157,37 +1151,43 @@ void dispatch_nt(const GemmArgs &a, const Epi &e, int nt, hipStream_t s) {
   }
 }
 
-// LDS bytes of the resident-weight kernel: W^T[Nreal][K + 4] and the staged
-// column vectors.
-template <class Epi, int NT, int KCH>
-size_t wres_lds(int nreal) {
-  return sizeof(float) * ((size_t)nreal * (KCH * 16 + 4) + Epi::kCols * NT * 16);
-}
-
-// One workgroup of eight wavefronts per CU; the grid never exceeds the CU
-// count (a second wave of workgroups would start only after the first).
-template <class Epi, int NT, int KCH>
-bool launch_wres(const GemmArgs &a, const Epi &e, hipStream_t s) {
-  constexpr int MT = 4;
-  static int ready[64];  // 1: dynamic LDS limit raised on that device, -1: refused
+// Dynamic LDS limit of the current device, raised for a kernel at its first
+// launch there; 0 when it is refused.
+template <class K>
+size_t raised_lds(K kernel, int (&ready)[64]) {
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
-  const size_t lds = wres_lds<Epi, NT, KCH>(a.Nreal);
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
   if (ready[dev] == 0) {
     int maxl = 0;
     ready[dev] = hipDeviceGetAttribute(&maxl, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
                              hipSuccess &&
-                         hipFuncSetAttribute((const void *)k_gemm_wres<MT, NT, KCH, Epi>,
+                         hipFuncSetAttribute((const void *)kernel,
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
                                              maxl) == hipSuccess
                      ? maxl
                      : -1;
   }
-  if (ready[dev] < 0 || lds > (size_t)ready[dev]) return false;
-  const long tiles = (a.Mmax + 8L * 16 * MT - 1) / (8L * 16 * MT);
-  const long gx = tiles < cu_count() ? tiles : cu_count();
+  return ready[dev] > 0 ? (size_t)ready[dev] : 0;
+}
+
+// Persistent grid of the split-operand kernel: `per_cu` workgroups on each CU
+// are resident (by LDS and registers) and more would start only when others
+// have finished their whole share.  Returns false when the weight block does
+// not fit the device's LDS.
+template <int NT, int KCH, int KT, int WAVES, class Epi>
+bool launch_split(const GemmArgs &a, const Epi &e, int per_cu, hipStream_t s) {
+  constexpr int KS = KT == 1 ? 16 * (KCH - 1) + 4 : 16 * KCH;
+  constexpr int LDW = KS % 8 == 4 ? KS : KS + 4;
+  static int ready[64];
+  const int nst = a.Nreal < NT * 16 ? a.Nreal : NT * 16;
+  const size_t lds = sizeof(float) * ((size_t)nst * LDW + Epi::kCols * NT * 16);
+  if (lds > raised_lds(k_gemm_split<NT, KCH, KT, WAVES, Epi>, ready)) return false;
+  const long tiles = (a.Mmax + WAVES * 16L - 1) / (WAVES * 16L);
+  const long cap = (long)per_cu * cu_count();
+  const long gx = tiles < cap ? tiles : cap;
   if (gx <= 0) return true;
-  hipLaunchKernelGGL((k_gemm_wres<MT, NT, KCH, Epi>), dim3((unsigned)gx), dim3(512), lds, s, a, e);
+  hipLaunchKernelGGL((k_gemm_split<NT, KCH, KT, WAVES, Epi>), dim3((unsigned)gx), dim3(64 * WAVES),
+                     lds, s, a, e);
   return true;
 }
 
@@ -1196,21 +1196,9 @@ bool launch_wres(const GemmArgs &a, const Epi &e, hipStream_t s) {
 template <class Epi, int NT, int CB, int KCH, int BF>
 bool launch_cols(const GemmArgs &a, const Epi &e, hipStream_t s) {
   constexpr int KS = 16 * (KCH - 1) + 4, NC = CB * NT * 16;
-  static int ready[64];  // dynamic LDS limit: 0 unknown, -1 refused, else bytes
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+  static int ready[64];
   const size_t lds = sizeof(float) * ((size_t)NC * (KS + 4) + NC);
-  if (ready[dev] == 0) {
-    int maxl = 0;
-    ready[dev] = hipDeviceGetAttribute(&maxl, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
-                             hipSuccess &&
-                         hipFuncSetAttribute((const void *)k_gemm_cols<NT, CB, KCH, Epi, BF>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             maxl) == hipSuccess
-                     ? maxl
-                     : -1;
-  }
-  if (ready[dev] < 0 || lds > (size_t)ready[dev]) return false;
+  if (lds > raised_lds(k_gemm_cols<NT, CB, KCH, Epi, BF>, ready)) return false;
   const long tiles = (a.Mmax + 8L * 32 - 1) / (8L * 32);
   const long gx = tiles < cu_count() ? tiles : cu_count();
   if (gx <= 0) return true;
@@ -1283,6 +1271,23 @@ void run(const GemmArgs &a, const Epi &e, bool full_rows, hipStream_t s) {
   // column blocks of at most four tiles: more wavefronts per SIMD to cover
   // the load latency of each k step (measured best against 1, 2 and 8)
   if (!full_rows && a.Mmax < 65536 && nt > 4) nt = 4;
+  // FP32 adjoints of the attention layers' projections over the 97- to
+  // 112-wide embedding (their weights come with a scale): two-term f16
+  // operands, whatever the number of rows, so that a row's bits do not depend
+  // on how many others there are (16 k rows 29 -> 24 us, 41 k rows 58 -> 39 us,
+  // 1.31 M rows 1.15 -> 0.79 ms for QKV).  Widths above 105 do not fit LDS
+  // with 384 deep rows and stay on FP32 operands.
+  if constexpr (std::is_same_v<Epi, EpiLinear>) {
+    if (!a.bf16 && a.wup > 0.f && a.K == 112 && ntt == 8 &&
+        (a.kreal > 96 && a.kreal <= 100 ? launch_split<8, 7, 1, 8>(a, e, 2, s)
+                                        : launch_split<8, 7, 4, 8>(a, e, 2, s)))
+      return;
+  }
+  if constexpr (std::is_same_v<Epi, EpiQKVBwd>) {
+    if (!a.bf16 && a.wup > 0.f && a.K == 384 && ntt == 7 &&
+        launch_split<7, 24, 4, 8>(a, e, 1, s))
+      return;
+  }
   // the FP32 QKV projection (384 output columns over a 100-wide embedding):
   // the whole weight block resident, X read once
   if constexpr (Epi::kLds == 1 && Epi::kCols == 1) {
@@ -1298,13 +1303,6 @@ void run(const GemmArgs &a, const Epi &e, bool full_rows, hipStream_t s) {
       if (nt == 8 && a.K == 112) return launch_lds<Epi, 8, 7>(a, e, s);
       return launch_lds<Epi, 8, 8>(a, e, s);
     }
-  }
-  // the FP32 adjoint of the QKV projection (K = 384, seven column tiles):
-  // the whole weight block resident in LDS when it fits
-  if constexpr (Epi::kLds == 0) {
-    if (a.Mmax >= 65536 && full_rows && !a.bf16 && a.K == 384 && nt == 7 && ntt == 7 &&
-        launch_wres<Epi, 7, 24>(a, e, s))
-      return;
   }
   // the long-K adjoint of the QKV projection otherwise: 64-row tiles halve
   // the weight reads per row (two waves per SIMD, 238 registers, no spills)
