@@ -25,6 +25,7 @@
 
 #include "dpa1_internal.h"
 #include "ln_res.h"
+#include "split.h"
 
 namespace dpa1 {
 
@@ -82,6 +83,24 @@ __device__ __forceinline__ float sum_rows(float v) {  // over the 16 lanes of a 
   v += __shfl_xor(v, 2);
   v += __shfl_xor(v, 4);
   v += __shfl_xor(v, 8);
+  return v;
+}
+
+// The value of a partner lane within the 16 lanes of a group, on the vector
+// ALU (data-parallel primitives): i ^ 8 (rotation by 8), i ^ 7 (mirror of 8
+// lanes), i ^ 3 (mirror of 4), i ^ 1.  In this order the four exchanges reach
+// all 16 lanes, and each keeps the lane bits above its own.
+constexpr int kDppXor8 = 0x128, kDppXor7 = 0x141, kDppXor3 = 0x1B, kDppXor1 = 0xB1;
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float sum16(float v) {  // over the 16 lanes of a group
+  v += dpp<kDppXor8>(v);
+  v += dpp<kDppXor7>(v);
+  v += dpp<kDppXor3>(v);
+  v += dpp<kDppXor1>(v);
   return v;
 }
 
@@ -218,14 +237,14 @@ __device__ __forceinline__ float4 gate_load(const float *__restrict__ geom, int 
   lo = b.w;
   return make_float4(a.y, a.z, a.w, b.x);
 }
-// kw[NPAD]: the switch value of each neighbour in FP64 (zero past n).
+// kw[NPAD]: the switch value of each neighbour in FP64 (zero past n), or null.
 template <int NPAD>
 __device__ __forceinline__ void gate_store(float4 *kg, double *kw, int tid, int n,
                                            const float4 &v, float lo) {
   const bool ok = tid < n;
   if (tid < NPAD) {
     kg[tid] = make_float4(ok ? v.x : 0.f, ok ? v.y : 0.f, ok ? v.z : 0.f, ok ? v.w : 0.f);
-    kw[tid] = ok ? (double)v.w + (double)lo : 0.0;
+    if (kw) kw[tid] = ok ? (double)v.w + (double)lo : 0.0;
   }
 }
 
@@ -285,22 +304,6 @@ __device__ __forceinline__ void accum_lds2(const float *XT, int tile, int r, int
 
 // The same contraction with the rows in row-major LDS (X[row][kLDR]): the A
 // operand is read with scalar LDS loads, four rows per lane group.
-__device__ __forceinline__ void accum_rows(const float *X, int tile, int r, int g,
-                                           const floatx4 &bt, floatx4 (&acc)[8]) {
-  const float *xb = X + (tile * 16 + 4 * g) * kLDR + r;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    floatx4 x[4];
-#pragma unroll
-    for (int f = 0; f < 4; ++f)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) x[f][t] = xb[t * kLDR + (4 * h + f) * 16];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int f = 0; f < 4; ++f) acc[4 * h + f] = mfma4(x[f][t], bt[t], acc[4 * h + f]);
-  }
-}
 // BF16: row tiles 'tile' and 'tile' + 1 in one 16x16x32 step.
 __device__ __forceinline__ void accum_rows2(const float *X, int tile, int r, int g,
                                             const floatx4 &bt0, const floatx4 &bt1,
@@ -414,7 +417,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD
     float *__restrict__ out, float *__restrict__ lam, float2 *__restrict__ fstat,
     AttnOut op) {
   constexpr int NT = NPAD / 16;
-  constexpr bool STORE_O = !OP || NPAD > 96;
+  constexpr bool STORE_O = !OP || (BF && NPAD > 96);
   extern __shared__ float4 smem[];
   float4 *kg = smem;
   double *kw = (double *)(smem + NPAD);  // [NPAD] switch values in FP64
@@ -624,7 +627,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD
 // (Q^T staged) and the key-side sums; it adds both sides into dE/dsw and
 // dE/drhat.
 
-template <int NPAD, bool BF>
+template <int NPAD>
 __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd_q(
     const float *__restrict__ qkv, const float *__restrict__ o, const float *__restrict__ dO,
     const float *__restrict__ geom, const int *__restrict__ pair_off,
@@ -635,8 +638,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
   constexpr int NT = NPAD / 16;
   extern __shared__ float4 smem[];
   float4 *kg = smem;                     // [NPAD] rhat, sw
-  double *kw = (double *)(kg + NPAD);    // [NPAD] switch values in FP64
-  float *buf = (float *)(kw + NPAD);     // V rows, then K^T
+  float *buf = (float *)(kg + NPAD);     // V rows, then K^T
   const int ld = kQKV * 128;
   const float inv_sqrt_d = 0.08838834764831845f;
   const int cnt = *ccount;
@@ -652,14 +654,14 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
     const int q = wave * 16 + r;
     const bool qok = q < n;
     float4 sv[8];
-    stage_rows_load<NPAD, BF>(qkv, 256, ld, base, n, tid, sv);  // V
+    stage_rows_load<NPAD, true>(qkv, 256, ld, base, n, tid, sv);  // V
     float gl;
     const float4 gv = gate_load(geom, base, n, tid, gl);
     floatx4 dov[8], ov[8];
-    load_rows<BF>(dO, 0, 128, base, n, q, g, dov);
-    load_rows<BF>(o, 0, 128, base, n, q, g, ov);
+    load_rows<true>(dO, 0, 128, base, n, q, g, dov);
+    load_rows<true>(o, 0, 128, base, n, q, g, ov);
     stage_rows_store<NPAD>(buf, tid, n, sv);
-    gate_store<NPAD>(kg, kw, tid, n, gv, gl);
+    gate_store<NPAD>(kg, nullptr, tid, n, gv, gl);
     __syncthreads();
     float dq = 0.f;
     if (wave < ntile) {
@@ -670,11 +672,11 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
       dq = sum_groups(dq);
     }
     float4 kpre[8];  // K, read while dA^T is formed
-    stage_t_load<NPAD, BF>(qkv, 128, ld, base, n, tid, kpre);
+    stage_t_load<NPAD, true>(qkv, 128, ld, base, n, tid, kpre);
 
     floatx4 da[NT];
     if (wave < ntile) {
-      qk_lds<NT, BF>(buf, r, g, dov, da);  // dA^T tiles: lane (query r, keys 4g + v)
+      qk_lds<NT, true>(buf, r, g, dov, da);  // dA^T tiles: lane (query r, keys 4g + v)
       if (qok) {  // dA row of this query, for the key-tile kernel
         float *dp = dA + (size_t)(base + q) * kLamLd + 4 * g;
 #pragma unroll
@@ -689,14 +691,13 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
       const int qr = qok ? q : 0;
       const float4 gq = kg[q];
       const float wq = qok ? gq.w : 0.f;
-      const double wqd = qok ? kw[q] : 0.0;
       const float2 fs = fstat[base + qr];
       const float m = fs.x, invz = fs.y;
       if (g == 0 && qok) astat[base + q] = make_float4(m, invz, dq, 0.f);
       // lam of this query row, read one key tile ahead of its use
       const float *lp = lam + (size_t)(base + qr) * kLamLd + 4 * g;
       floatx4 dqacc[8];
-      floatx4 dsp;  // BF16: dS of the even tile of a pair
+      floatx4 dsp;  // dS of the even tile of a pair
 #pragma unroll
       for (int ft = 0; ft < 8; ++ft) dqacc[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
       float dwq = 0.f, drqx = 0.f, drqy = 0.f, drqz = 0.f;
@@ -713,7 +714,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
           const float c = gq.x * gk.x + gq.y * gk.y + gq.z * gk.z;
           const float ww = wq * gk.w;
           const float lm = ok ? lcur[v] : 0.f;
-          const float l = BF ? (lm + shift) * ww - shift : logit64(lm, wqd, kw[k], shift);
+          const float l = (lm + shift) * ww - shift;
           const float p = ok ? exp_hw(l - m) * invz : 0.f;
           const float h = ww * c;
           const float dH = da[kt][v] * p;
@@ -726,12 +727,9 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
           drqy += Y * gk.y;
           drqz += Y * gk.z;
         }
-        if constexpr (BF) {  // tiles taken in pairs
-          if (kt % 2 == 0) dsp = ds;
-          else accum_lds2<NPAD>(buf, kt - 1, r, g, dsp, ds, dqacc);
-        } else {
-          accum_lds<NPAD>(buf, kt, r, g, ds, dqacc);
-        }
+        // tiles taken in pairs
+        if (kt % 2 == 0) dsp = ds;
+        else accum_lds2<NPAD>(buf, kt - 1, r, g, dsp, ds, dqacc);
         lcur = lnxt;
       }
       dwq = sum_groups(dwq);
@@ -740,17 +738,17 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
       drqz = sum_groups(drqz);
       if (g == 0 && qok) qside[base + q] = make_float4(dwq, drqx, drqy, drqz);
       if (qok) {
-        float *dp = pt_at<BF>(dqkv, (size_t)(base + q) * ld + 4 * g);
+        float *dp = pt_at<true>(dqkv, (size_t)(base + q) * ld + 4 * g);
 #pragma unroll
-        for (int ft = 0; ft < 8; ++ft) stp4<BF>(dp, 16 * ft, dqacc[ft]);
+        for (int ft = 0; ft < 8; ++ft) stp4<true>(dp, 16 * ft, dqacc[ft]);
       }
     }
     __syncthreads();  // LDS is restaged for the next centre
   }
 }
 
-template <int NPAD, bool BF>
-__global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void k_attn_bwd_k(
+template <int NPAD>
+__global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd_k(
     const float *__restrict__ qkv, const float *__restrict__ dO,
     const float *__restrict__ geom, const int *__restrict__ pair_off,
     const int *__restrict__ nnei, const int *__restrict__ clist, const int *__restrict__ ccount,
@@ -762,14 +760,10 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
   extern __shared__ float4 smem[];
   float4 *kg = smem;                     // [NPAD] rhat, sw
   float4 *stats = kg + NPAD;             // [NPAD] m, 1/Z, D_q of each query
-  double *kw = (double *)(stats + NPAD); // [NPAD] switch values in FP64
-  float *buf = (float *)(kw + NPAD);     // dO rows, then Q^T
+  float *buf = (float *)(stats + NPAD);  // dO rows, then Q^T
   const int ld = kQKV * 128;
   const float inv_sqrt_d = 0.08838834764831845f;
   const int cnt = *ccount;
-  // FP32: the Q rows of phase 2 are loaded during phase 1 (BF16 loads them
-  // after phase 1, holding fewer registers)
-  constexpr bool PREF = !BF;
   for (int it = blockIdx.x; it < cnt; it += gridDim.x) {
     const int tid = fresh_tid();
     const int wave = tid >> 6;
@@ -779,7 +773,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
     const int n = nnei[i];
     const int base = pair_off[i];
     float4 sv[8];
-    stage_rows_load<NPAD, BF>(dO, 0, 128, base, n, tid, sv);  // dO
+    stage_rows_load<NPAD, true>(dO, 0, 128, base, n, tid, sv);  // dO
     float gl;
     const float4 gv = gate_load(geom, base, n, tid, gl);
     const float4 av = astat[base + (tid < n ? tid : 0)];
@@ -787,11 +781,9 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
     const int kk = wave * 16 + r;
     const bool kok = kk < n;
     stage_rows_store<NPAD>(buf, tid, n, sv);
-    gate_store<NPAD>(kg, kw, tid, n, gv, gl);
+    gate_store<NPAD>(kg, nullptr, tid, n, gv, gl);
     if (tid < NPAD) stats[tid] = tid < n ? av : make_float4(0.f, 1.f, 0.f, 0.f);
     __syncthreads();
-    float4 qpre[8];
-    if constexpr (PREF) stage_t_load<NPAD, BF>(qkv, 0, ld, base, n, tid, qpre);  // Q rows of phase 2
 
     // ---------------- phase 1: dV, dS and the key-side sums
     floatx4 ds[NT];
@@ -799,7 +791,6 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
     if (wave < ntile) {
       const float4 gk = kg[kk];
       const float wk = kok ? gk.w : 0.f;
-      const double wkd = kok ? kw[kk] : 0.0;
       // lam and dA of this key against the queries of one tile (lane: key r,
       // queries 4g + v), read one query tile ahead
       const size_t col = (size_t)base * kLamLd + (kok ? kk : 0);
@@ -816,17 +807,16 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
       float lcur[4], lnxt[4], dcur[4], dnxt[4];
       lam_tile(0, lcur, dcur);
       floatx4 dvacc[8];
-      floatx4 atp;  // BF16: A^T of the even tile of a pair
+      floatx4 atp;  // A^T of the even tile of a pair
 #pragma unroll
       for (int ft = 0; ft < 8; ++ft) dvacc[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int qt = 0; qt < NT; ++qt) {
         ds[qt] = floatx4{0.f, 0.f, 0.f, 0.f};
         if (qt >= ntile) {
-          // BF16: an unpaired last tile meets a zero partner
-          if constexpr (BF)
-            if (qt % 2 == 1 && qt - 1 < ntile)
-              accum_rows2(buf, qt - 1, r, g, atp, floatx4{0.f, 0.f, 0.f, 0.f}, dvacc);
+          // an unpaired last tile meets a zero partner
+          if (qt % 2 == 1 && qt - 1 < ntile)
+            accum_rows2(buf, qt - 1, r, g, atp, floatx4{0.f, 0.f, 0.f, 0.f}, dvacc);
           continue;
         }
         if (qt + 1 < NT) lam_tile(qt + 1, lnxt, dnxt);
@@ -840,7 +830,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
           const float c = gq.x * gk.x + gq.y * gk.y + gq.z * gk.z;
           const float ww = gq.w * wk;
           const float lm = ok ? lcur[v] : 0.f;
-          const float l = BF ? (lm + shift) * ww - shift : logit64(lm, kw[qq], wkd, shift);
+          const float l = (lm + shift) * ww - shift;
           const float p = ok ? exp_hw(l - sq.x) * sq.y : 0.f;
           const float h = ww * c;
           const float dav = ok ? dcur[v] : 0.f;
@@ -855,12 +845,9 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
           drky += Y * gq.y;
           drkz += Y * gq.z;
         }
-        if constexpr (BF) {  // dV = A^T dO, tiles taken in pairs
-          if (qt % 2 == 0) atp = at;
-          else accum_rows2(buf, qt - 1, r, g, atp, at, dvacc);
-        } else {
-          accum_rows(buf, qt, r, g, at, dvacc);  // dV = A^T dO
-        }
+        // dV = A^T dO, tiles taken in pairs
+        if (qt % 2 == 0) atp = at;
+        else accum_rows2(buf, qt - 1, r, g, atp, at, dvacc);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           lcur[v] = lnxt[v];
@@ -869,9 +856,9 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
         __builtin_amdgcn_sched_barrier(0);
       }
       if (kok) {
-        float *dp = pt_at<BF>(dqkv, (size_t)(base + kk) * ld + 256 + 4 * g);
+        float *dp = pt_at<true>(dqkv, (size_t)(base + kk) * ld + 256 + 4 * g);
 #pragma unroll
-        for (int ft = 0; ft < 8; ++ft) stp4<BF>(dp, 16 * ft, dvacc[ft]);
+        for (int ft = 0; ft < 8; ++ft) stp4<true>(dp, 16 * ft, dvacc[ft]);
       }
       dwk = sum_groups(dwk);
       drkx = sum_groups(drkx);
@@ -879,7 +866,9 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
       drkz = sum_groups(drkz);
     }
     __syncthreads();
-    if constexpr (!PREF) stage_t_load<NPAD, BF>(qkv, 0, ld, base, n, tid, qpre);
+    // Q rows of phase 2 (loaded only now: fewer registers in phase 1)
+    float4 qpre[8];
+    stage_t_load<NPAD, true>(qkv, 0, ld, base, n, tid, qpre);
     stage_t_store<NPAD>(buf, tid, n, qpre);  // Q^T
     __syncthreads();
 
@@ -888,20 +877,14 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF ? (NPAD <= 96 ? 3 : 2) : 2) void
       floatx4 dkacc[8];
 #pragma unroll
       for (int ft = 0; ft < 8; ++ft) dkacc[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (BF) {
-        // tiles in pairs; ds of tiles at or past ntile is zero
+      // tiles in pairs; ds of tiles at or past ntile is zero
 #pragma unroll
-        for (int qt = 0; qt < NT; qt += 2)
-          if (qt < ntile) accum_lds2<NPAD>(buf, qt, r, g, ds[qt], ds[qt + 1], dkacc);
-      } else {
-#pragma unroll
-        for (int qt = 0; qt < NT; ++qt)
-          if (qt < ntile) accum_lds<NPAD>(buf, qt, r, g, ds[qt], dkacc);
-      }
+      for (int qt = 0; qt < NT; qt += 2)
+        if (qt < ntile) accum_lds2<NPAD>(buf, qt, r, g, ds[qt], ds[qt + 1], dkacc);
       if (kok) {
-        float *dp = pt_at<BF>(dqkv, (size_t)(base + kk) * ld + 128 + 4 * g);
+        float *dp = pt_at<true>(dqkv, (size_t)(base + kk) * ld + 128 + 4 * g);
 #pragma unroll
-        for (int ft = 0; ft < 8; ++ft) stp4<BF>(dp, 16 * ft, dkacc[ft]);
+        for (int ft = 0; ft < 8; ++ft) stp4<true>(dp, 16 * ft, dkacc[ft]);
         if (g == 0) {
           const float4 qs = qsbuf[base + kk];
           const size_t p = (size_t)(base + kk);
@@ -944,7 +927,6 @@ template <int NPAD>
 size_t bwdf_lds() {
   constexpr int W = NPAD / 16;
   return sizeof(float4) * NPAD * (2 + W)  // kg, qside, key-side sums per query tile
-         + sizeof(double) * NPAD          // kw
          + sizeof(float) * stage_floats<NPAD>() + sizeof(float) * 2 * NPAD * fused_ld<NPAD>();
 }
 
@@ -971,7 +953,7 @@ __device__ __forceinline__ float reduce16_transposed(float (&v)[16], int r) {
 // BF: BF16 matrix-core operands (tiles taken in pairs, every class has an
 // even number) and BF16 storage of QKV, dO and dQKV, as in the two-kernel
 // form; LDS and the elementwise work stay FP32.
-template <int NPAD, bool BF>
+template <int NPAD>
 __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd_f(
     const float *__restrict__ qkv, const float *__restrict__ dO,
     const float *__restrict__ geom, const int *__restrict__ pair_off,
@@ -984,8 +966,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
   float4 *kg = smem;                       // [NPAD] rhat, sw
   float4 *qside = kg + NPAD;               // [NPAD] query-side sums of each neighbour
   float4 *ksum = qside + NPAD;             // [NT][NPAD] key-side sums, per query tile
-  double *kw = (double *)(ksum + NT * NPAD);  // [NPAD] switch values in FP64
-  float *buf = (float *)(kw + NPAD);       // V rows, K^T, dO rows, Q^T in turn
+  float *buf = (float *)(ksum + NT * NPAD);  // V rows, K^T, dO rows, Q^T in turn
   float *As = buf + stage_floats<NPAD>();  // [NPAD][LDF] A = P H
   float *Ds = As + NPAD * LDF;             // [NPAD][LDF] dS
   const int ld = kQKV * 128;
@@ -1002,7 +983,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
     const int i0 = clist[blockIdx.x];
     n_nx = nnei[i0];
     base_nx = pair_off[i0];
-    stage_rows_load<NPAD, BF>(qkv, 256, ld, base_nx, n_nx, tid, sv);  // V
+    stage_rows_load<NPAD, true>(qkv, 256, ld, base_nx, n_nx, tid, sv);  // V
     gv = gate_load(geom, base_nx, n_nx, tid, gl);
   }
   for (int it = blockIdx.x; it < cnt; it += gridDim.x) {
@@ -1016,16 +997,16 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
     const int q = wave * 16 + r;
     const bool qok = q < n;
     floatx4 dov[8];
-    load_rows<BF>(dO, 0, 128, base, n, q, g, dov);
+    load_rows<true>(dO, 0, 128, base, n, q, g, dov);
     stage_rows_store<NPAD>(buf, tid, n, sv);
-    gate_store<NPAD>(kg, kw, tid, n, gv, gl);
+    gate_store<NPAD>(kg, nullptr, tid, n, gv, gl);
     __syncthreads();
 
     // ---------------- phase Q: dA^T, dS, dQ, A and dS to LDS, both sides' sums
     float4 kpre[8];  // K, read while dA^T is formed
-    stage_t_load<NPAD, BF>(qkv, 128, ld, base, n, tid, kpre);
+    stage_t_load<NPAD, true>(qkv, 128, ld, base, n, tid, kpre);
     floatx4 da[NT];
-    if (wave < ntile) qk_lds<NT, BF>(buf, r, g, dov, da);  // lane: query r, keys 4g + v
+    if (wave < ntile) qk_lds<NT, true>(buf, r, g, dov, da);  // lane: query r, keys 4g + v
     __syncthreads();
     stage_t_store<NPAD>(buf, tid, n, kpre);  // K^T
     __syncthreads();
@@ -1033,7 +1014,6 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
       const int qr = qok ? q : 0;
       const float4 gq = kg[q];
       const float wq = qok ? gq.w : 0.f;
-      const double wqd = qok ? kw[q] : 0.0;
       const float2 fs = fstat[base + qr];
       const float m = fs.x, invz = fs.y;
       const float *lp = lam + (size_t)(base + qr) * kLamLd + 4 * g;
@@ -1054,7 +1034,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
             const float4 gk = kg[k];
             const float c = gq.x * gk.x + gq.y * gk.y + gq.z * gk.z;
             const float lm = ok ? lcur[v] : 0.f;
-            const float l = BF ? (lm + shift) * (wq * gk.w) - shift : logit64(lm, wqd, kw[k], shift);
+            const float l = (lm + shift) * (wq * gk.w) - shift;
             const float p = ok ? exp_hw(l - m) * invz : 0.f;
             dq += p * (wq * gk.w * c) * da[kt][v];
             pk[kt][v] = p;
@@ -1069,7 +1049,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
 #pragma unroll
       for (int ft = 0; ft < 8; ++ft) dqacc[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
       float dwq = 0.f, drqx = 0.f, drqy = 0.f, drqz = 0.f;
-      floatx4 dsp;  // BF16: dS of the even tile of a pair
+      floatx4 dsp;  // dS of the even tile of a pair
       // pass 2: the softmax adjoint; A = P H and dS replace P and lam
 #pragma unroll
       for (int kt = 0; kt < NT; ++kt) {
@@ -1107,12 +1087,9 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
         // 4g + r % 4 of this tile
         const float kt_sum = reduce16_transposed(ks, r);
         ((float *)ksum)[(wave * NPAD + kt * 16 + 4 * g + (r & 3)) * 4 + (r >> 2)] = kt_sum;
-        if constexpr (BF) {  // dQ = dS K, tiles taken in pairs
-          if (kt % 2 == 0) dsp = ds;
-          else accum_lds2<NPAD>(buf, kt - 1, r, g, dsp, ds, dqacc);
-        } else {
-          accum_lds<NPAD>(buf, kt, r, g, ds, dqacc);  // dQ = dS K
-        }
+        // dQ = dS K, tiles taken in pairs
+        if (kt % 2 == 0) dsp = ds;
+        else accum_lds2<NPAD>(buf, kt - 1, r, g, dsp, ds, dqacc);
       }
       dwq = sum_groups(dwq);
       drqx = sum_groups(drqx);
@@ -1120,9 +1097,9 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
       drqz = sum_groups(drqz);
       if (g == 0 && qok) qside[q] = make_float4(dwq, drqx, drqy, drqz);
       if (qok) {
-        float *dp = pt_at<BF>(dqkv, (size_t)(base + q) * ld + 4 * g);
+        float *dp = pt_at<true>(dqkv, (size_t)(base + q) * ld + 4 * g);
 #pragma unroll
-        for (int ft = 0; ft < 8; ++ft) stp4<BF>(dp, 16 * ft, dqacc[ft]);
+        for (int ft = 0; ft < 8; ++ft) stp4<true>(dp, 16 * ft, dqacc[ft]);
       }
     }
     __syncthreads();
@@ -1138,37 +1115,32 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
 
     // ---------------- phase K: dV = A^T dO, dK = dS^T Q, key-side sums
     float4 qpre[8];  // Q, read while dV is formed
-    stage_t_load<NPAD, BF>(qkv, 0, ld, base, n, tid, qpre);
+    stage_t_load<NPAD, true>(qkv, 0, ld, base, n, tid, qpre);
     const int kk = wave * 16 + r;
     const bool kok = kk < n;
     if (wave < ntile) {
       floatx4 dvacc[8];
 #pragma unroll
       for (int ft = 0; ft < 8; ++ft) dvacc[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
-      floatx4 atp;  // BF16: A^T of the even tile of a pair
+      floatx4 atp;  // A^T of the even tile of a pair
 #pragma unroll
       for (int qt = 0; qt < NT; ++qt) {
         if (qt >= ntile) {
-          // BF16: an unpaired last tile meets a zero partner
-          if constexpr (BF)
-            if (qt % 2 == 1 && qt - 1 < ntile)
-              accum_rows2(buf, qt - 1, r, g, atp, floatx4{0.f, 0.f, 0.f, 0.f}, dvacc);
+          // an unpaired last tile meets a zero partner
+          if (qt % 2 == 1 && qt - 1 < ntile)
+            accum_rows2(buf, qt - 1, r, g, atp, floatx4{0.f, 0.f, 0.f, 0.f}, dvacc);
           continue;
         }
         floatx4 at;  // lane: key r, queries 4g + v
 #pragma unroll
         for (int v = 0; v < 4; ++v) at[v] = As[(qt * 16 + 4 * g + v) * LDF + kk];
-        if constexpr (BF) {
-          if (qt % 2 == 0) atp = at;
-          else accum_rows2(buf, qt - 1, r, g, atp, at, dvacc);
-        } else {
-          accum_rows(buf, qt, r, g, at, dvacc);
-        }
+        if (qt % 2 == 0) atp = at;
+        else accum_rows2(buf, qt - 1, r, g, atp, at, dvacc);
       }
       if (kok) {
-        float *dp = pt_at<BF>(dqkv, (size_t)(base + kk) * ld + 256 + 4 * g);
+        float *dp = pt_at<true>(dqkv, (size_t)(base + kk) * ld + 256 + 4 * g);
 #pragma unroll
-        for (int ft = 0; ft < 8; ++ft) stp4<BF>(dp, 16 * ft, dvacc[ft]);
+        for (int ft = 0; ft < 8; ++ft) stp4<true>(dp, 16 * ft, dvacc[ft]);
       }
     }
     __syncthreads();
@@ -1180,7 +1152,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
         const int inx = clist[itn];
         n_nx = nnei[inx];
         base_nx = pair_off[inx];
-        stage_rows_load<NPAD, BF>(qkv, 256, ld, base_nx, n_nx, tid, sv);  // next V
+        stage_rows_load<NPAD, true>(qkv, 256, ld, base_nx, n_nx, tid, sv);  // next V
         gv = gate_load(geom, base_nx, n_nx, tid, gl);
       }
     }
@@ -1188,36 +1160,25 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
       floatx4 dkacc[8];
 #pragma unroll
       for (int ft = 0; ft < 8; ++ft) dkacc[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (BF) {
-        // tiles in pairs; dS of query tiles at or past ntile (not written for
-        // this centre) is zero
+      // tiles in pairs; dS of query tiles at or past ntile (not written for
+      // this centre) is zero
 #pragma unroll
-        for (int qt = 0; qt < NT; qt += 2) {
-          if (qt >= ntile) continue;
-          floatx4 d0, d1;
-          const bool ok1 = qt + 1 < ntile;
+      for (int qt = 0; qt < NT; qt += 2) {
+        if (qt >= ntile) continue;
+        floatx4 d0, d1;
+        const bool ok1 = qt + 1 < ntile;
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            d0[v] = Ds[(qt * 16 + 4 * g + v) * LDF + kk];
-            const float x1 = Ds[((qt + 1) * 16 + 4 * g + v) * LDF + kk];
-            d1[v] = ok1 ? x1 : 0.f;
-          }
-          accum_lds2<NPAD>(buf, qt, r, g, d0, d1, dkacc);
+        for (int v = 0; v < 4; ++v) {
+          d0[v] = Ds[(qt * 16 + 4 * g + v) * LDF + kk];
+          const float x1 = Ds[((qt + 1) * 16 + 4 * g + v) * LDF + kk];
+          d1[v] = ok1 ? x1 : 0.f;
         }
-      } else {
-#pragma unroll
-        for (int qt = 0; qt < NT; ++qt) {
-          if (qt >= ntile) continue;
-          floatx4 dsv;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) dsv[v] = Ds[(qt * 16 + 4 * g + v) * LDF + kk];
-          accum_lds<NPAD>(buf, qt, r, g, dsv, dkacc);
-        }
+        accum_lds2<NPAD>(buf, qt, r, g, d0, d1, dkacc);
       }
       if (kok) {
-        float *dp = pt_at<BF>(dqkv, (size_t)(base + kk) * ld + 128 + 4 * g);
+        float *dp = pt_at<true>(dqkv, (size_t)(base + kk) * ld + 128 + 4 * g);
 #pragma unroll
-        for (int ft = 0; ft < 8; ++ft) stp4<BF>(dp, 16 * ft, dkacc[ft]);
+        for (int ft = 0; ft < 8; ++ft) stp4<true>(dp, 16 * ft, dkacc[ft]);
         if (g == 0) {
           float4 t = qside[kk];
           for (int w = 0; w < ntile; ++w) {
@@ -1244,6 +1205,487 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
       }
     }
     __syncthreads();  // LDS is restaged for the next centre
+  }
+}
+
+// ---------------------------------------------------- adjoint, split operands
+//
+// The FP32 adjoint of one centre, one workgroup per centre, on two-term f16
+// operands (split.h).  Wavefront = tile of 16 keys: with its own V rows as the
+// MFMA's column operand and dO in LDS, dA comes out as lane (key r, queries
+// 4g + v), which is the column operand of dV = A^T dO and dK = dS^T Q as it
+// stands; only dS goes through LDS, for dQ = dS K (wavefront = tile of 16
+// queries).  dO is staged once for both dA and dV, V not at all, and A never
+// leaves registers.  The sums over keys (D_q = sum_k A dA, and the query-side
+// switch and direction gradients) are reduced over a wavefront's 16 keys by
+// lane exchanges and over wavefronts through LDS in a fixed order.
+//
+// Rows staged in LDS carry their own power-of-two scale; where rows are
+// contracted over, the scale is folded into the other operand, whose row then
+// takes a scale of its own.
+//
+// LDS holds, one after the other, dO rows, Q rows, and dS beside the K rows in
+// two halves of 64 features: 80 KB for the 96 class, so that a CU holds two
+// centres.  They share one workgroup of 12 wavefronts, three on every SIMD: two
+// workgroups of six would each put two wavefronts on the first SIMDs, four
+// there in all, which their registers do not allow (measured: the second
+// waits).  The two centres have barriers of their own (with the workgroup's
+// barrier they wait for each other's phases: 1.62 ms against 1.41).
+//
+// Per layer at 15,668 centres of 84 neighbours: FP32 MFMAs with A and dS in LDS
+// (141 KB, one centre per CU) 2.30 ms, this 1.43 ms for 5.3 GB, three quarters
+// of what a plain copy reaches; at 3,800 centres of 107 neighbours (the
+// 128 class, one centre of eight wavefronts per CU) 0.84 ms in two FP32
+// kernels, 0.56 ms here.
+template <int NPAD>
+constexpr int split_ds_ld() { return NPAD + 4; }
+constexpr int kLDH = 68;  // row stride of half the features: 64 + 4
+
+template <int NPAD>
+constexpr int split_main_floats() {
+  constexpr int rows = NPAD * kLDR, halves = NPAD * (split_ds_ld<NPAD>() + kLDH);
+  return rows > halves ? rows : halves;
+}
+// Centres of a workgroup: two of the 96 class (12 wavefronts, three per SIMD).
+template <int NPAD>
+constexpr int bwds_centres() { return NPAD == 96 ? 2 : 1; }
+template <int NPAD>
+constexpr int bwds_threads() { return bwds_centres<NPAD>() * NPAD / 16 * 64; }
+template <int NPAD>
+constexpr size_t bwds_lds() {
+  constexpr int W = NPAD / 16;
+  return bwds_centres<NPAD>() *
+         (sizeof(float4) * NPAD * (1 + W)               // kg, query-side sums per key tile
+          + (sizeof(double) + sizeof(float2)) * NPAD    // kw, softmax statistics
+          // row scales, D_q per key tile (then the key-side sums) and whole
+          + sizeof(float) * NPAD * (2 + (W > 4 ? W : 4))
+          + sizeof(float) * split_main_floats<NPAD>());
+}
+
+// One 16-row tile as load_rows gives it, from a wave-uniform base with 32-bit
+// offsets.
+__device__ __forceinline__ void load_own(const float *rows, int ld, int row, int n, int g,
+                                         floatx4 (&v)[8]) {
+  const unsigned off = (unsigned)((row < n ? row : 0) * ld + 4 * g);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) v[c] = *(const floatx4 *)(rows + off + 16 * c);
+}
+
+// Own rows, scaled and packed; rows that do not exist become zeros.
+__device__ __forceinline__ float pack_rows(const floatx4 (&v)[8], bool ok, split::packx4 (&p)[8]) {
+  float m = 0.f;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) m = split::max_abs(m, v[c]);
+  const split::Scale sc = split::scale_of(split::row_max(m));
+  const split::packx4 z = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const split::packx4 x = split::pack(v[c] * sc.up);
+    p[c] = ok ? x : z;
+  }
+  return sc.down;
+}
+
+// The column operand of a contraction over neighbours: b[kt][v] times the row
+// scales of the other operand, with one scale for the whole column; returns
+// its inverse.
+template <int NT>
+__device__ __forceinline__ float pack_column(const floatx4 (&b)[NT], const float *scl, int g,
+                                             split::packx4 (&p)[NT]) {
+  floatx4 x[NT];
+  float m = 0.f;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    x[t] = b[t] * *(const floatx4 *)(scl + 16 * t + 4 * g);
+    m = split::max_abs(m, x[t]);
+  }
+  const split::Scale sc = split::scale_of(split::row_max(m));
+#pragma unroll
+  for (int t = 0; t < NT; ++t) p[t] = split::pack(x[t] * sc.up);
+  return sc.down;
+}
+
+// acc[f] = sum over the rows of X of X^T b for NF feature tiles f
+// (X packed, row-major, row stride LD, first feature at X): lane own row r,
+// features 16 f + 4 g + v.  Operands are read for four tiles at a time.
+template <int NT, int NF, int LD>
+__device__ __forceinline__ void contract_rows(const float *X, int r, int g,
+                                              const split::packx4 (&b)[NT],
+                                              floatx4 (&acc)[NF]) {
+#pragma unroll
+  for (int f = 0; f < NF; ++f) acc[f] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const uint32_t *xb = (const uint32_t *)X + 4 * g * LD + r;
+#pragma unroll
+  for (int qt = 0; qt < NT; ++qt) {
+    const split::halfx8 lo = split::dup_lo(b[qt]), hi = split::dup_hi(b[qt]);
+#pragma unroll
+    for (int h = 0; h < NF; h += 4) {
+      split::packx4 x[4];
+#pragma unroll
+      for (int f = 0; f < 4; ++f)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) x[f][t] = xb[(16 * qt + t) * LD + 16 * (h + f)];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) acc[h + f] = split::mfma(x[f], lo, acc[h + f]);
+#pragma unroll
+      for (int f = 0; f < 4; ++f) acc[h + f] = split::mfma(x[f], hi, acc[h + f]);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // one tile's operands live at a time
+  }
+}
+template <int NF>
+__device__ __forceinline__ void store_rows(float *out, bool ok, const floatx4 (&acc)[NF],
+                                           float down) {
+  if (ok) {
+#pragma unroll
+    for (int f = 0; f < NF; ++f) *(floatx4 *)(out + 16 * f) = acc[f] * down;
+  }
+}
+
+// Sum of 16 per-lane values over the 16 lanes of a lane group: after four
+// halving steps lane r holds the total of value r.
+__device__ __forceinline__ float reduce16_dpp(float (&v)[16], int r) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float lo = v[j] + dpp<kDppXor8>(v[j]), hi = v[j + 8] + dpp<kDppXor8>(v[j + 8]);
+    v[j] = (r & 8) ? hi : lo;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float lo = v[j] + dpp<kDppXor7>(v[j]), hi = v[j + 4] + dpp<kDppXor7>(v[j + 4]);
+    v[j] = (r & 4) ? hi : lo;
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const float lo = v[j] + dpp<kDppXor3>(v[j]), hi = v[j + 2] + dpp<kDppXor3>(v[j + 2]);
+    v[j] = (r & 2) ? hi : lo;
+  }
+  const float lo = v[0] + dpp<kDppXor1>(v[0]), hi = v[1] + dpp<kDppXor1>(v[1]);
+  return (r & 1) ? hi : lo;
+}
+
+// Lane indices that the optimiser cannot connect with those of an earlier
+// phase, so that no address is kept in registers from one to the next.
+#define FRESH_LANES                                    \
+  int lane_ = lane;                                    \
+  asm volatile("" : "+v"(lane_));                      \
+  const int r = lane_ & 15, g = lane_ >> 4;            \
+  const int kk = wave * 16 + r;                        \
+  const bool kok = kk < n;                             \
+  (void)kok;
+
+template <int NPAD>
+__global__ __launch_bounds__(bwds_threads<NPAD>(), NPAD <= 96 ? 3 : 2) void k_attn_bwd_s(
+    const float *__restrict__ qkv, const float *__restrict__ dO,
+    const float *__restrict__ geom, const int *__restrict__ pair_off,
+    const int *__restrict__ nnei, const int *__restrict__ clist, const int *__restrict__ ccount,
+    float shift, const float *__restrict__ lam, const float2 *__restrict__ fstat,
+    float *__restrict__ dqkv, float *__restrict__ gw, float *__restrict__ gr, int accumulate) {
+  constexpr int NT = NPAD / 16;
+  constexpr int LDD = split_ds_ld<NPAD>();
+  constexpr int C = bwds_centres<NPAD>();
+  extern __shared__ float4 smem[];
+  __shared__ unsigned bar[C];  // arrivals at the barriers of each centre
+  const int part = C == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / (NT * 64));
+  float4 *kg = smem + part * (bwds_lds<NPAD>() / C / sizeof(float4));  // [NPAD] rhat, sw
+  float4 *qsum = kg + NPAD;                         // [NT][NPAD] query-side sums per key tile
+  double *kw = (double *)(qsum + NT * NPAD);        // [NPAD] switch values in FP64
+  float2 *stats = (float2 *)(kw + NPAD);            // [NPAD] m, 1/Z
+  float *scl = (float *)(stats + NPAD);             // [NPAD] inverse scales of the staged rows
+  float *dqs = scl + NPAD;                          // [NT][NPAD] D_q per key tile
+  float4 *kside = (float4 *)dqs;                    // [NPAD] key-side sums, in its place
+  float *dqt = dqs + (NT > 4 ? NT : 4) * NPAD;      // [NPAD] D_q
+  float *buf = dqt + NPAD;                          // dO rows, Q rows
+  float *Ds = buf;                                  // [NPAD][LDD] dS, beside
+  float *kh = buf + NPAD * LDD;                     // [NPAD][kLDH] half the features of K
+  const int ld = kQKV * 128;
+  const float inv_sqrt_d = 0.08838834764831845f;
+  const int cnt = *ccount;
+  // dO and V rows and the gate record of a centre are loaded during the last
+  // product of the previous one
+  floatx4 rows[8], vrows[8];
+  float4 gv;
+  float2 fs;
+  float gl = 0.f;
+  int n_nx = 0, base_nx = 0;
+  auto fetch = [&](int at, int tid) {  // (past the last centre: that one again)
+    const int i = clist[min(at, cnt - 1)];
+    n_nx = __builtin_amdgcn_readfirstlane(nnei[i]);
+    base_nx = __builtin_amdgcn_readfirstlane(pair_off[i]);
+    const int row = (tid >> 6) * 16 + (tid & 15), g = (tid & 63) >> 4;
+    load_own(dO + (size_t)base_nx * 128, 128, row, n_nx, g, rows);
+    load_own(qkv + (size_t)base_nx * ld + 256, ld, row, n_nx, g, vrows);
+    gv = gate_load(geom, base_nx, n_nx, tid, gl);
+    fs = fstat[base_nx + (tid < n_nx ? tid : 0)];
+  };
+  // part 1 takes the centres one grid further on: with fewer centres than
+  // workgroups every centre has a CU to itself
+  const int step = (int)gridDim.x * C;
+  const int first = (int)blockIdx.x + part * (int)gridDim.x;
+  // Barrier of the wavefronts of one centre: a workgroup barrier when there is
+  // one centre, else an arrival count in LDS.  All of a workgroup's wavefronts
+  // are resident and pass the same barriers, so the count is reached; the other
+  // centre's phases, of other lengths, are not waited for.
+  unsigned arrived = 0;
+  if constexpr (C > 1) {
+    if (threadIdx.x < C) bar[threadIdx.x] = 0;
+    __syncthreads();
+  }
+  auto barrier = [&]() {
+    if constexpr (C == 1) {
+      __syncthreads();
+    } else {
+      arrived += NT;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      if ((threadIdx.x & 63) == 0)
+        __hip_atomic_fetch_add(&bar[part], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                 &bar[part], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < arrived)
+        __builtin_amdgcn_s_sleep(1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+  };
+  if (first >= cnt) return;  // one centre's wavefronts, no shared barrier follows
+  fetch(first, fresh_tid() - part * NT * 64);
+  for (int it = first; it < cnt; it += step) {
+    const int tid = fresh_tid() - part * NT * 64;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int r = lane & 15, g = lane >> 4;
+    const int n = n_nx;
+    const int base = base_nx;
+    const float *qb = qkv + (size_t)base * ld;
+    const int kk = wave * 16 + r;  // own row: key, and query of the last product
+    const bool kok = kk < n;
+    float *db = dqkv + (size_t)base * ld;
+    split::packx4 own[8];
+    {
+      const float down = pack_rows(rows, kok, own);
+      if (g == 0) scl[kk] = down;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) *(split::packx4 *)(buf + kk * kLDR + 16 * c + 4 * g) = own[c];
+    }
+    gate_store<NPAD>(kg, kw, tid, n, gv, gl);
+    if (tid < NPAD) stats[tid] = fs;
+    // logits of this key against the queries of every tile
+    const float *lc = lam + (size_t)base * kLamLd;
+    auto lam_tile = [&](int qt, int kk, int g) {
+      floatx4 l;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int q = qt * 16 + 4 * g + v;
+        l[v] = lc[(unsigned)((q < n ? q : 0) * kLamLd + (kk < n ? kk : 0))];
+      }
+      return l;
+    };
+    floatx4 lm[NT];
+#pragma unroll
+    for (int qt = 0; qt < NT; ++qt) lm[qt] = lam_tile(qt, kk, g);
+    const float iv = pack_rows(vrows, true, own);
+    barrier();
+
+    // ---------------- dA, P, D_q
+    floatx4 da[NT], pk[NT];
+    {
+#pragma unroll
+      for (int qt = 0; qt < NT; ++qt) da[qt] = floatx4{0.f, 0.f, 0.f, 0.f};
+      const float *xb = buf + r * kLDR + 4 * g;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        split::packx4 x[NT];
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt)
+          x[qt] = *(const split::packx4 *)(xb + qt * 16 * kLDR + 16 * c);
+        __builtin_amdgcn_sched_barrier(0);
+        const split::halfx8 lo = split::dup_lo(own[c]), hi = split::dup_hi(own[c]);
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt) da[qt] = split::mfma(x[qt], lo, da[qt]);
+#pragma unroll
+        for (int qt = 0; qt < NT; ++qt) da[qt] = split::mfma(x[qt], hi, da[qt]);
+      }
+      const float4 gk = kg[kk];
+      const double wkd = kok ? kw[kk] : 0.0;
+#pragma unroll
+      for (int qt = 0; qt < NT; ++qt) {
+        const floatx4 sq = *(const floatx4 *)(scl + qt * 16 + 4 * g);
+        floatx4 part;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int q = qt * 16 + 4 * g + v;
+          const bool ok = kok && q < n;
+          const float4 gq = kg[q];
+          const float2 sm = stats[q];
+          const float c = gq.x * gk.x + gq.y * gk.y + gq.z * gk.z;
+          const float l = logit64(ok ? lm[qt][v] : 0.f, kw[q], wkd, shift);
+          const float p = ok ? exp_hw(l - sm.x) * sm.y : 0.f;
+          const float d = ok ? da[qt][v] * iv * sq[v] : 0.f;
+          da[qt][v] = d;
+          pk[qt][v] = p;
+          part[v] = sum16(p * (gq.w * gk.w * c) * d);
+        }
+        if (r == 0) *(floatx4 *)(dqs + wave * NPAD + qt * 16 + 4 * g) = part;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    barrier();
+    if (tid < NPAD) {
+      float t = 0.f;
+#pragma unroll
+      for (int w = 0; w < NT; ++w) t += dqs[w * NPAD + tid];
+      dqt[tid] = t;
+    }
+    barrier();
+
+    // ---------------- softmax adjoint: A^T in pk, dS^T in da; both sides' sums.
+    // The logits come from L2 a second time, one tile ahead: kept since the
+    // first pass they would push the 96 class past its 168 registers, and a
+    // spilled register's reload waits for every load and store before it.
+    {
+      FRESH_LANES
+      float dwk = 0.f, drx = 0.f, dry = 0.f, drz = 0.f;  // key-side sums
+      const float4 gk = kg[kk];
+      const float wk = kok ? gk.w : 0.f;
+      floatx4 lcur = lam_tile(0, kk, g);
+#pragma unroll
+      for (int qt = 0; qt < NT; ++qt) {
+        const floatx4 lnxt = lam_tile(qt + 1 < NT ? qt + 1 : qt, kk, g);
+        const floatx4 dq = *(const floatx4 *)(dqt + qt * 16 + 4 * g);
+        float qs[16];  // query-side terms X w_k, Y rhat_k of the four queries
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int q = qt * 16 + 4 * g + v;
+          const bool ok = kok && q < n;
+          const float4 gq = kg[q];
+          const float c = gq.x * gk.x + gq.y * gk.y + gq.z * gk.z;
+          const float ww = gq.w * wk;
+          const float p = pk[qt][v];
+          const float h = ww * c;
+          const float dH = da[qt][v] * p;
+          const float dL = ok ? p * (da[qt][v] * h - dq[v]) : 0.f;
+          const float X = dL * ((ok ? lcur[v] : 0.f) + shift) + dH * c;
+          const float Y = dH * ww;
+          pk[qt][v] = p * h;
+          da[qt][v] = dL * ww * inv_sqrt_d;
+          dwk += X * gq.w;
+          drx += Y * gq.x;
+          dry += Y * gq.y;
+          drz += Y * gq.z;
+          qs[v] = X * wk;
+          qs[4 + v] = Y * gk.x;
+          qs[8 + v] = Y * gk.y;
+          qs[12 + v] = Y * gk.z;
+        }
+        // lane r now holds the tile's total of term r / 4 for query 4g + r % 4
+        const float t = reduce16_dpp(qs, r);
+        ((float *)qsum)[(wave * NPAD + qt * 16 + 4 * g + (r & 3)) * 4 + (r >> 2)] = t;
+        lcur = lnxt;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      dwk = sum_groups(dwk);
+      drx = sum_groups(drx);
+      dry = sum_groups(dry);
+      drz = sum_groups(drz);
+      // (every wavefront is past the D_q sums)
+      if (g == 0) kside[kk] = make_float4(dwk, drx, dry, drz);
+      // dV = A^T dO
+      split::packx4 bp[NT];
+      const float down = pack_column<NT>(pk, scl, g, bp);
+      floatx4 acc[8];
+      contract_rows<NT, 8, kLDR>(buf, r, g, bp, acc);
+      // Q on its way to LDS, ahead of the stores (a wait for loads waits for
+      // every store issued before them)
+      load_own(qb, ld, kk, n, g, rows);
+      store_rows(db + (unsigned)(kk * ld + 4 * g) + 256, kok, acc, down);
+    }
+    barrier();
+
+    // ---------------- dK = dS^T Q
+    {
+      FRESH_LANES
+      const float down = pack_rows(rows, kok, own);
+      if (g == 0) scl[kk] = down;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) *(split::packx4 *)(buf + kk * kLDR + 16 * c + 4 * g) = own[c];
+    }
+    {
+      FRESH_LANES
+      load_own(qb + 128, ld, kk, n, g, rows);  // K
+    }
+    barrier();
+    {
+      FRESH_LANES
+      split::packx4 bp[NT];
+      const float down = pack_column<NT>(da, scl, g, bp);
+      floatx4 acc[8];
+      contract_rows<NT, 8, kLDR>(buf, r, g, bp, acc);
+      store_rows(db + (unsigned)(kk * ld + 4 * g) + 128, kok, acc, down);
+    }
+    barrier();
+
+    // ---------------- dQ = dS K, 64 features at a time
+    {
+      FRESH_LANES
+      const float down = pack_rows(rows, kok, own);
+      if (g == 0) scl[kk] = down;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) *(split::packx4 *)(kh + kk * kLDH + 16 * c + 4 * g) = own[c];
+    }
+    {
+#pragma unroll
+      for (int qt = 0; qt < NT; ++qt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Ds[(qt * 16 + 4 * g + v) * LDD + kk] = da[qt][v];
+    }
+    barrier();
+    split::packx4 bp[NT];
+    float down = 0.f;
+    float gw0 = 0.f;  // the other layers' share of dE/dsw, dE/drhat
+    float4 gr0 = make_float4(0.f, 0.f, 0.f, 0.f);
+    {
+      FRESH_LANES
+      if (accumulate) {
+        gw0 = gw[base + (kok ? kk : 0)];
+        gr0 = *(const float4 *)(gr + 4 * (size_t)(base + (kok ? kk : 0)));
+      }
+      floatx4 x[NT];
+#pragma unroll
+      for (int kt = 0; kt < NT; ++kt)
+        x[kt] = *(const floatx4 *)(Ds + kk * LDD + kt * 16 + 4 * g);
+      down = pack_column<NT>(x, scl, g, bp);
+      floatx4 acc[4];
+      contract_rows<NT, 4, kLDH>(kh, r, g, bp, acc);
+      store_rows(db + (unsigned)(kk * ld + 4 * g), kok, acc, down);
+    }
+    barrier();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) *(split::packx4 *)(kh + kk * kLDH + 16 * c + 4 * g) = own[4 + c];
+    // unconditional, also after the last centre: under a branch the old rows
+    // would stay live to the end of the loop
+    fetch(it + step, tid);
+    barrier();
+    {
+      FRESH_LANES
+      // (the operand's duplicates are formed again rather than kept)
+#pragma unroll
+      for (int kt = 0; kt < NT; ++kt) asm volatile("" : "+v"(bp[kt]));
+      floatx4 acc[4];
+      contract_rows<NT, 4, kLDH>(kh, r, g, bp, acc);
+      store_rows(db + (unsigned)(kk * ld + 4 * g) + 64, kok, acc, down);
+      if (kok && g == 0) {
+        float4 t = kside[kk];
+#pragma unroll
+        for (int w = 0; w < NT; ++w) {
+          const float4 q = qsum[w * NPAD + kk];
+          t.x += q.x;
+          t.y += q.y;
+          t.z += q.z;
+          t.w += q.w;
+        }
+        gw[base + kk] = gw0 + t.x;
+        *(float4 *)(gr + 4 * (size_t)(base + kk)) = make_float4(gr0.x + t.y, gr0.y + t.z, gr0.z + t.w, 0.f);
+      }
+    }
+    barrier();  // LDS is restaged for the next centre
   }
 }
 
@@ -1753,18 +2195,19 @@ size_t fwd_lds() {
 }
 template <int NPAD>
 size_t bwdq_lds() {
-  return (sizeof(float4) + sizeof(double)) * NPAD + sizeof(float) * stage_floats<NPAD>();
+  return sizeof(float4) * NPAD + sizeof(float) * stage_floats<NPAD>();
 }
 template <int NPAD>
 size_t bwdk_lds() {
-  return (sizeof(float4) * 2 + sizeof(double)) * NPAD + sizeof(float) * stage_floats<NPAD>();
+  return sizeof(float4) * 2 * NPAD + sizeof(float) * stage_floats<NPAD>();
 }
 
 // Persistent grid sizes: resident blocks per CU times CUs, per device.
 constexpr int kMaxDevices = 64;
-int g_grid[kMaxDevices][10][4];  // fwd, bwd_q, bwd_k in FP32, then in BF16; fused FP32
-                                 // adjoint; FP32 forward with the output projection; fused
-                                 // BF16 adjoint; BF16 forward with the output projection
+int g_grid[kMaxDevices][10][4];  // FP32 forward and adjoint, -; BF16 forward, query-tile and
+                                 // key-tile adjoint; -; FP32 forward with the output
+                                 // projection; fused BF16 adjoint; BF16 forward with the
+                                 // output projection
 
 int g_desc_grid[kMaxDevices][2];  // fused descriptor / projection adjoint: FP32, BF16
 
@@ -1791,40 +2234,36 @@ hipError_t occupancy_grid(K kernel, int threads, size_t lds, int cus, int *out) 
 template <int NPAD, bool BF>
 hipError_t prepare_class(int dev, int cus, int cls) {
   const int th = NPAD / 16 * 64;
-  const int k0 = BF ? 3 : 0;  // grid table rows: fp32 fwd, bwd_q, bwd_k, then bf16
-  hipError_t e = hipSuccess;
-  if (NPAD > 64) {
-    e = hipFuncSetAttribute((const void *)k_attn_fwd<NPAD, BF, false>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_lds<NPAD>());
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void *)k_attn_bwd_q<NPAD, BF>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bwdq_lds<NPAD>());
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void *)k_attn_bwd_k<NPAD, BF>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bwdk_lds<NPAD>());
-  }
+  const auto lds_limit = [](const void *kernel, size_t lds) {
+    return lds > 65536 ? hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)lds)
+                       : hipSuccess;
+  };
+  hipError_t e = lds_limit((const void *)k_attn_fwd<NPAD, BF, false>, fwd_lds<NPAD>());
   if (e == hipSuccess)
     e = occupancy_grid(k_attn_fwd<NPAD, BF, false>, th, fwd_lds<NPAD>(), cus,
-                       &g_grid[dev][k0][cls]);
+                       &g_grid[dev][BF ? 3 : 0][cls]);
   if (e == hipSuccess)
-    e = occupancy_grid(k_attn_bwd_q<NPAD, BF>, th, bwdq_lds<NPAD>(), cus,
-                       &g_grid[dev][k0 + 1][cls]);
-  if (e == hipSuccess)
-    e = occupancy_grid(k_attn_bwd_k<NPAD, BF>, th, bwdk_lds<NPAD>(), cus,
-                       &g_grid[dev][k0 + 2][cls]);
-  if (e == hipSuccess && fwd_lds<NPAD, true>() > 65536)
-    e = hipFuncSetAttribute((const void *)k_attn_fwd<NPAD, BF, true>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)fwd_lds<NPAD, true>());
+    e = lds_limit((const void *)k_attn_fwd<NPAD, BF, true>, fwd_lds<NPAD, true>());
   if (e == hipSuccess)
     e = occupancy_grid(k_attn_fwd<NPAD, BF, true>, th, fwd_lds<NPAD, true>(), cus,
                        &g_grid[dev][BF ? 9 : 7][cls]);
-  if constexpr (NPAD <= 96) {
-    if (e == hipSuccess && bwdf_lds<NPAD>() > 65536)
-      e = hipFuncSetAttribute((const void *)k_attn_bwd_f<NPAD, BF>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bwdf_lds<NPAD>());
+  if constexpr (!BF) {
+    if (e == hipSuccess) e = lds_limit((const void *)k_attn_bwd_s<NPAD>, bwds_lds<NPAD>());
     if (e == hipSuccess)
-      e = occupancy_grid(k_attn_bwd_f<NPAD, BF>, th, bwdf_lds<NPAD>(), cus,
-                         &g_grid[dev][BF ? 8 : 6][cls]);
+      e = occupancy_grid(k_attn_bwd_s<NPAD>, bwds_threads<NPAD>(), bwds_lds<NPAD>(), cus,
+                         &g_grid[dev][1][cls]);
+  } else if constexpr (NPAD <= 96) {
+    if (e == hipSuccess) e = lds_limit((const void *)k_attn_bwd_f<NPAD>, bwdf_lds<NPAD>());
+    if (e == hipSuccess)
+      e = occupancy_grid(k_attn_bwd_f<NPAD>, th, bwdf_lds<NPAD>(), cus, &g_grid[dev][8][cls]);
+  } else {
+    if (e == hipSuccess) e = lds_limit((const void *)k_attn_bwd_q<NPAD>, bwdq_lds<NPAD>());
+    if (e == hipSuccess)
+      e = occupancy_grid(k_attn_bwd_q<NPAD>, th, bwdq_lds<NPAD>(), cus, &g_grid[dev][4][cls]);
+    if (e == hipSuccess) e = lds_limit((const void *)k_attn_bwd_k<NPAD>, bwdk_lds<NPAD>());
+    if (e == hipSuccess)
+      e = occupancy_grid(k_attn_bwd_k<NPAD>, th, bwdk_lds<NPAD>(), cus, &g_grid[dev][5][cls]);
   }
   return e;
 }
@@ -1906,55 +2345,44 @@ void launch_attn_fwd_class(int cls, const AttnArgs &a, const float *qkv, float *
                                             AttnOut{}));
 }
 
-void launch_attn_bwd_q_class(int cls, const AttnArgs &a, const float *qkv, const float *o,
-                             const float *dO, const float *lam, const float *fstat, float *dqkv,
-                             float *astat, float *qside, float *dA, hipStream_t s) {
-  if (a.nloc <= 0) return;
-  const int *cl = a.clist + (size_t)cls * a.nloc, *cc = a.ccount + cls;
-  const dim3 grid(grid_for(a.bf16 ? 4 : 1, cls, a.small));
-  ATTN_CLASS_SWITCH(cls, hipLaunchKernelGGL((k_attn_bwd_q<NP, BFV>), grid, dim3(NP / 16 * 64),
-                                            bwdq_lds<NP>(), s, qkv, o, dO, a.geom, a.pair_off,
-                                            a.nnei, cl, cc, a.sel, a.shift, lam,
-                                            (const float2 *)fstat, dqkv, (float4 *)astat,
-                                            (float4 *)qside, dA));
-}
-
-bool attn_bwd_fused(const AttnArgs &, int cls) { return cls <= 2; }
+bool attn_bwd_fused(const AttnArgs &a, int cls) { return !a.bf16 || cls <= 2; }
 
 void launch_attn_bwd_fused_class(int cls, const AttnArgs &a, const float *qkv, const float *dO,
                                  const float *lam, const float *fstat, float *dqkv, float *gw,
                                  float *gr, int accumulate, hipStream_t s) {
   if (a.nloc <= 0 || !attn_bwd_fused(a, cls)) return;
   const int *cl = a.clist + (size_t)cls * a.nloc, *cc = a.ccount + cls;
-  const dim3 grid(grid_for(a.bf16 ? 8 : 6, cls, a.small));
-#define ATTN_BWD_F(NP, BFV)                                                                    \
-  hipLaunchKernelGGL((k_attn_bwd_f<NP, BFV>), grid, dim3(NP / 16 * 64), bwdf_lds<NP>(), s, qkv, \
-                     dO, a.geom, a.pair_off, a.nnei, cl, cc, a.sel, a.shift, lam,              \
-                     (const float2 *)fstat, dqkv, gw, gr, accumulate)
-  if (a.bf16) {
-    if (cls == 0) ATTN_BWD_F(32, true);
-    else if (cls == 1) ATTN_BWD_F(64, true);
-    else ATTN_BWD_F(96, true);
-  } else {
-    if (cls == 0) ATTN_BWD_F(32, false);
-    else if (cls == 1) ATTN_BWD_F(64, false);
-    else ATTN_BWD_F(96, false);
-  }
-#undef ATTN_BWD_F
+  const dim3 grid(grid_for(a.bf16 ? 8 : 1, cls, a.small));
+  ATTN_CLASS_SWITCH(cls, {
+    if constexpr (!BFV)
+      hipLaunchKernelGGL(k_attn_bwd_s<NP>, grid, dim3(bwds_threads<NP>()), bwds_lds<NP>(), s, qkv, dO,
+                         a.geom, a.pair_off, a.nnei, cl, cc, a.shift, lam, (const float2 *)fstat,
+                         dqkv, gw, gr, accumulate);
+    else if constexpr (NP <= 96)
+      hipLaunchKernelGGL(k_attn_bwd_f<NP>, grid, dim3(NP / 16 * 64), bwdf_lds<NP>(), s, qkv, dO,
+                         a.geom, a.pair_off, a.nnei, cl, cc, a.sel, a.shift, lam,
+                         (const float2 *)fstat, dqkv, gw, gr, accumulate);
+  });
 }
 
-void launch_attn_bwd_k_class(int cls, const AttnArgs &a, const float *qkv, const float *dO,
-                             const float *lam, const float *dA, float *dqkv, const float *astat,
-                             const float *qside, float *gw, float *gr, int accumulate,
-                             hipStream_t s) {
+void launch_attn_bwd_q(const AttnArgs &a, const float *qkv, const float *o, const float *dO,
+                       const float *lam, const float *fstat, float *dqkv, float *astat,
+                       float *qside, float *dA, hipStream_t s) {
   if (a.nloc <= 0) return;
-  const int *cl = a.clist + (size_t)cls * a.nloc, *cc = a.ccount + cls;
-  const dim3 grid(grid_for(a.bf16 ? 5 : 2, cls, a.small));
-  ATTN_CLASS_SWITCH(cls, hipLaunchKernelGGL((k_attn_bwd_k<NP, BFV>), grid, dim3(NP / 16 * 64),
-                                            bwdk_lds<NP>(), s, qkv, dO, a.geom, a.pair_off,
-                                            a.nnei, cl, cc, a.shift, lam, dA, dqkv,
-                                            (const float4 *)astat, (const float4 *)qside, gw, gr,
-                                            accumulate));
+  hipLaunchKernelGGL(k_attn_bwd_q<128>, dim3(grid_for(4, 3, a.small)), dim3(512), bwdq_lds<128>(),
+                     s, qkv, o, dO, a.geom, a.pair_off, a.nnei, a.clist + 3 * (size_t)a.nloc,
+                     a.ccount + 3, a.sel, a.shift, lam, (const float2 *)fstat, dqkv,
+                     (float4 *)astat, (float4 *)qside, dA);
+}
+
+void launch_attn_bwd_k(const AttnArgs &a, const float *qkv, const float *dO, const float *lam,
+                       const float *dA, float *dqkv, const float *astat, const float *qside,
+                       float *gw, float *gr, int accumulate, hipStream_t s) {
+  if (a.nloc <= 0) return;
+  hipLaunchKernelGGL(k_attn_bwd_k<128>, dim3(grid_for(5, 3, a.small)), dim3(512), bwdk_lds<128>(),
+                     s, qkv, dO, a.geom, a.pair_off, a.nnei, a.clist + 3 * (size_t)a.nloc,
+                     a.ccount + 3, a.shift, lam, dA, dqkv, (const float4 *)astat,
+                     (const float4 *)qside, gw, gr, accumulate);
 }
 
 void launch_desc_fwd(const float *geom, const float *G, int ldg, const int *pair_off,

@@ -627,12 +627,8 @@ const char *const kAttnFwdName[4] = {"attn_fwd_n32", "attn_fwd_n64", "attn_fwd_n
                                      "attn_fwd_n128"};
 const char *const kAttnFwdLnName[4] = {"attn_fwd_ln_n32", "attn_fwd_ln_n64", "attn_fwd_ln_n96",
                                        "attn_fwd_ln_n128"};
-const char *const kAttnBwdQName[4] = {"attn_bwd_q_n32", "attn_bwd_q_n64", "attn_bwd_q_n96",
-                                      "attn_bwd_q_n128"};
 const char *const kAttnBwdName[4] = {"attn_bwd_n32", "attn_bwd_n64", "attn_bwd_n96",
                                      "attn_bwd_n128"};
-const char *const kAttnBwdKName[4] = {"attn_bwd_k_n32", "attn_bwd_k_n64", "attn_bwd_k_n96",
-                                      "attn_bwd_k_n128"};
 
 // The attention forward applies the output projection and layer norm itself
 // when the embedding width pads to kAttnOpCols columns and the attention
@@ -698,8 +694,8 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
     active = 1 << (ncls - 1);
     for (int c = 0; c < ncls - 1; ++c)
       if (m->ccount_host[4 + c] > 0) active |= 1 << c;
-    // the largest class with the fused FP32 adjoint stays launched, so that a
-    // centre is always computed by the same kind of adjoint (fused or not)
+    // in BF16 the largest class with the fused adjoint stays launched, so that
+    // a centre is always computed by the same kind of adjoint (fused or not)
     // and results do not depend on which classes were empty before
     const AttnArgs probe{nullptr, nullptr, nullptr, nullptr, nullptr, nloc, sel, 0.f, m->bf16};
     for (int c = ncls - 2; c >= 0; --c)
@@ -903,17 +899,12 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
         RUN(kAttnBwdName[cls],
           launch_attn_bwd_fused_class(cls, aa, w.qkv[a], w.dO, w.lam[a], w.fstat[a], w.dqkv,
                                       w.gw, w.gr, a != na - 1, s));
-    for (int cls = 0; cls < attn_class_count(sel); ++cls)
-      if (((m->cls_active >> cls) & 1) && !attn_bwd_fused(aa, cls))
-        RUN(kAttnBwdQName[cls],
-          launch_attn_bwd_q_class(cls, aa, w.qkv[a], w.o[a], w.dO, w.lam[a], w.fstat[a], w.dqkv,
-                                  w.astat, w.qside, w.dA, s));
-    for (int cls = 0; cls < attn_class_count(sel); ++cls)
-      if (((m->cls_active >> cls) & 1) && !attn_bwd_fused(aa, cls))
-        RUN(kAttnBwdKName[cls],
-          launch_attn_bwd_k_class(cls, aa, w.qkv[a], w.dO, w.lam[a], w.dA, w.dqkv, w.astat,
-                                  w.qside,
-                                  w.gw, w.gr, a != na - 1, s));
+    if (attn_class_count(sel) == 4 && !attn_bwd_fused(aa, 3)) {
+      RUN("attn_bwd_q_n128", launch_attn_bwd_q(aa, w.qkv[a], w.o[a], w.dO, w.lam[a], w.fstat[a],
+                                               w.dqkv, w.astat, w.qside, w.dA, s));
+      RUN("attn_bwd_k_n128", launch_attn_bwd_k(aa, w.qkv[a], w.dO, w.lam[a], w.dA, w.dqkv,
+                                               w.astat, w.qside, w.gw, w.gr, a != na - 1, s));
+    }
     GemmArgs g2{w.dqkv, 3 * D, A.Wb_qkv, 3 * D, ldM, m->M,    Pptr,
                 Pmax,   m->bf16, m->bf16, 0,  0,   sqkv.up, sqkv.down};
     const int mode = a > 0 ? 0 : (emb_fused ? 2 : 1);

@@ -196,32 +196,31 @@ struct AttnOut {
 // Forward: O = (P o H) V per centre; stores lam = QK^T/sqrt(d) per pair row
 // ([P][kAttnLamLd]) and (m, 1/Z) per pair (fstat, float2).  With op it
 // also applies the output projection and layer norm (gout, xhat,
-// rstd as the projection GEMM writes them) and stores O only for the
+// rstd as the projection GEMM writes them) and stores O only for the BF16
 // 128-neighbour class, whose two-kernel adjoint reads it; with op == nullptr
 // it stores O for every class.
 void launch_attn_fwd_class(int cls, const AttnArgs &a, const float *qkv, float *out, float *lam,
                            float *fstat, const AttnOut *op, hipStream_t s);
-// Backward, query tiles: dQ, (m, 1/Z, D_q) and the query-side gate/switch
-// gradients (astat, qside: per-pair float4 buffers read by the key-tile pass).
-// dA [P][kAttnLamLd]: dL/dA of every (query, key) pair of a centre, in the
-// layout of lam, written here and read by the key-tile pass.
-void launch_attn_bwd_q_class(int cls, const AttnArgs &a, const float *qkv, const float *o,
-                             const float *dO, const float *lam, const float *fstat, float *dqkv,
-                             float *astat, float *qside, float *dA, hipStream_t s);
-// Backward, key tiles: dK, dV and the total dE/dsw, dE/drhat per pair
-// (accumulated onto gw/gr when accumulate != 0).
-void launch_attn_bwd_k_class(int cls, const AttnArgs &a, const float *qkv, const float *dO,
-                             const float *lam, const float *dA, float *dqkv, const float *astat,
-                             const float *qside, float *gw, float *gr, int accumulate,
-                             hipStream_t s);
-// Both halves of the backward in one kernel (FP32, classes of up to 96
-// neighbours; attn_bwd_fused tells whether a class has it): the outputs of
-// the query-tile and key-tile passes without dA, astat and qside, and
-// without reading O (D_q = sum_k A dA instead of dO . o).
+// Backward of one class in one kernel: dqkv and dE/dsw, dE/drhat per pair
+// (accumulated onto gw/gr when accumulate != 0), without reading O (D_q =
+// sum_k A dA instead of dO . o).  attn_bwd_fused tells whether a class has it:
+// every class in FP32 (two-term f16 operands), up to 96 neighbours in BF16.
 bool attn_bwd_fused(const AttnArgs &a, int cls);
 void launch_attn_bwd_fused_class(int cls, const AttnArgs &a, const float *qkv, const float *dO,
                                  const float *lam, const float *fstat, float *dqkv, float *gw,
                                  float *gr, int accumulate, hipStream_t s);
+// The BF16 128-neighbour class, query tiles: dQ, (m, 1/Z, D_q) and the
+// query-side gate/switch gradients (astat, qside: per-pair float4 buffers read
+// by the key-tile pass).
+// dA [P][kAttnLamLd]: dL/dA of every (query, key) pair of a centre, in the
+// layout of lam, written here and read by the key-tile pass.
+void launch_attn_bwd_q(const AttnArgs &a, const float *qkv, const float *o, const float *dO,
+                       const float *lam, const float *fstat, float *dqkv, float *astat,
+                       float *qside, float *dA, hipStream_t s);
+// Its key tiles: dK, dV and the total dE/dsw, dE/drhat per pair.
+void launch_attn_bwd_k(const AttnArgs &a, const float *qkv, const float *dO, const float *lam,
+                       const float *dA, float *dqkv, const float *astat, const float *qside,
+                       float *gw, float *gr, int accumulate, hipStream_t s);
 // Descriptor: T = R~^T G / sel (4 x M), D = T^T T[:, :axis] -> dmat [nloc x M*axis].
 void launch_desc_fwd(const float *geom, const float *G, int ldg, const int *pair_off,
                      const int *nnei, int nloc, int sel, int M, int axis, float *T, float *dmat,
