@@ -379,6 +379,38 @@ __device__ __forceinline__ int fresh_tid() {
   return t;
 }
 
+// Barrier of the wavefronts that work on one centre: the workgroup's barrier
+// when it has one centre (C = 1), else an arrival count in LDS, one per centre,
+// so that the centres of a workgroup do not wait for each other's phases.  All
+// of a workgroup's wavefronts are resident and those of a centre pass the same
+// barriers, so a count is always reached.  The constructor is for every
+// thread of the workgroup.
+template <int C, int WAVES>
+struct CentreBarrier {
+  unsigned *count;
+  unsigned arrived = 0;
+  __device__ __forceinline__ CentreBarrier(unsigned *counts, int part) : count(counts + part) {
+    if constexpr (C > 1) {
+      if (threadIdx.x < C) counts[threadIdx.x] = 0;
+      __syncthreads();
+    }
+  }
+  __device__ __forceinline__ void operator()() {
+    if constexpr (C == 1) {
+      __syncthreads();
+    } else {
+      arrived += WAVES;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      if ((threadIdx.x & 63) == 0)
+        __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                 count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < arrived)
+        __builtin_amdgcn_s_sleep(1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+  }
+};
+
 // Floats of the staging buffer: NPAD rows x kLDR or 128 features x (NPAD + 4).
 template <int NPAD>
 constexpr int stage_floats() {
@@ -396,10 +428,8 @@ constexpr int stage_floats() {
 // (row stride kLamLd, all NPAD key columns of every query row) and the
 // softmax statistics (m, 1/Z) of every query are stored for the adjoint,
 // which then does not recompute Q K^T.  The FP32 forward issues the next
-// centre's staging loads during its last phase, into registers the current
-// centre no longer needs, so that the HBM latency of a centre's operands
-// overlaps the previous centre's products (two workgroups per compute unit
-// leave the registers for it).
+// centre's staging loads while it finishes the current one, so that the HBM
+// latency of a centre's operands overlaps the previous centre's products.
 
 constexpr int kLamLd = kAttnLamLd;
 constexpr int kOpCols = kAttnOpCols;   // output columns of the fused projection
@@ -409,8 +439,27 @@ constexpr int kOpTiles = kOpCols / 16;
 // (W_O^T, 7 column tiles, staged in LDS once per workgroup; the epilogue is
 // the one the projection GEMM uses), so the attention output o goes to
 // memory only where the two-kernel adjoint of the 128 class reads it.
-template <int NPAD, bool BF, bool OP>
-__global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD <= 96 ? 3 : 2)) : 2) void k_attn_fwd(
+// LDS of one centre: kg, kw, buf.
+template <int NPAD>
+constexpr size_t fwd_centre_lds() {
+  return (sizeof(float4) + sizeof(double)) * NPAD + sizeof(float) * stage_floats<NPAD>();
+}
+
+// With the projection a workgroup holds several centres (fwd_centres), each
+// with its own buffer and barriers, around the one W_O^T: two of the 96 class
+// put three wavefronts on every SIMD, where a workgroup of six leaves two SIMDs
+// with half the others' MFMAs and a second one does not fit (160 KB of LDS, and
+// six wavefronts of more than 128 registers cannot share a CU with another
+// six: each workgroup starts on the first SIMD).  Per layer at 15,668 centres
+// of 84 neighbours: FP32 1.69 -> 1.36 ms, BF16 0.78 -> 0.70 ms.
+// Above 105 features W_O^T and two centres of the 96 class no longer fit, and
+// a workgroup takes one centre (C = 1) in every class.
+template <int NPAD>
+constexpr int fwd_centres() { return NPAD > 96 ? 1 : (NPAD == 32 ? 4 : 2); }
+constexpr int kFwdMaxCols = 105;
+
+template <int NPAD, bool BF, bool OP, int C>
+__global__ __launch_bounds__(C * NPAD / 16 * 64, OP ? (C == 2 && NPAD == 96 ? 3 : 2) : BF ? (NPAD <= 64 ? 4 : (NPAD <= 96 ? 3 : 2)) : 2) void k_attn_fwd(
     const float *__restrict__ qkv, const float *__restrict__ geom,
     const int *__restrict__ pair_off, const int *__restrict__ nnei,
     const int *__restrict__ clist, const int *__restrict__ ccount, int sel, float shift,
@@ -419,16 +468,19 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD
   constexpr int NT = NPAD / 16;
   constexpr bool STORE_O = !OP || (BF && NPAD > 96);
   extern __shared__ float4 smem[];
-  float4 *kg = smem;
-  double *kw = (double *)(smem + NPAD);  // [NPAD] switch values in FP64
+  __shared__ unsigned bar[C];
+  const int part = C == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / (NT * 64));
+  float4 *kg = smem + part * (int)(fwd_centre_lds<NPAD>() / sizeof(float4));
+  double *kw = (double *)(kg + NPAD);    // [NPAD] switch values in FP64
   float *buf = (float *)(kw + NPAD);     // K rows, then V^T
-  float *wo = buf + stage_floats<NPAD>();  // OP: W_O^T [kOpCols][kLDR]
-  float *cso = wo + kOpCols * kLDR;        // OP: bias, gamma, beta [3][kOpCols]
+  // OP: W_O^T [op.Nreal][kLDR], then bias, gamma, beta [3][kOpCols]
+  float *wo = (float *)(smem + C * (int)(fwd_centre_lds<NPAD>() / sizeof(float4)));
+  float *cso = wo + op.Nreal * kLDR;
   const int ld = kQKV * 128;
   const float inv_sqrt_d = 0.08838834764831845f;  // 1/sqrt(128)
   const int cnt = *ccount;
   if constexpr (OP) {
-    for (int idx = threadIdx.x; idx < kOpCols * 32; idx += blockDim.x) {
+    for (int idx = threadIdx.x; idx < op.Nreal * 32; idx += blockDim.x) {
       const int row = idx >> 5, c4 = idx & 31;
       *(float4 *)(wo + row * kLDR + 4 * c4) = *(const float4 *)(op.Wt_o + row * 128 + 4 * c4);
     }
@@ -436,45 +488,50 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD
       const int k = idx / kOpCols, n = idx % kOpCols;
       cso[idx] = (k == 0 ? op.bias : (k == 1 ? op.gamma : op.beta))[n];
     }
+    __syncthreads();
   }
-  // FP32: the staging loads of a centre are issued during the A V phase of the
-  // previous one (BF16 holds more registers per tile and loads per centre)
-  constexpr bool PREF = !BF;
+  CentreBarrier<C, NT> barrier(bar, part);
+  // the centres of part p are those of the list's positions first, first +
+  // step, ...: with fewer centres than workgroups each has a CU to itself
+  const int step = (int)gridDim.x * C;
+  const int first = (int)blockIdx.x + part * (int)gridDim.x;
+  if (first >= cnt) return;
+  // FP32: the staging loads of a centre (and, with one centre to a workgroup,
+  // its own query rows) are issued during the A V phase of the previous one
+  // (BF16 holds more registers per tile and loads per centre); after the last
+  // centre they are its own again, since under a branch the old values would
+  // stay live through the whole loop
+  constexpr bool PREF = !BF, PREFQ = PREF && C == 1;
   float4 sv[8];
   floatx4 qv[8];
   float4 gv;
   float gl = 0.f;
   int n_nx = 0, base_nx = 0;
-  if (PREF && (int)blockIdx.x < cnt) {
-    const int tid = fresh_tid();
-    const int i0 = clist[blockIdx.x];
-    n_nx = nnei[i0];
-    base_nx = pair_off[i0];
+  auto fetch = [&](int at, int tid) {
+    const int i = clist[min(at, cnt - 1)];
+    n_nx = nnei[i];
+    base_nx = pair_off[i];
     stage_rows_load<NPAD, BF>(qkv, 128, ld, base_nx, n_nx, tid, sv);  // K
     gv = gate_load(geom, base_nx, n_nx, tid, gl);
-    load_rows<BF>(qkv, 0, ld, base_nx, n_nx, (tid >> 6) * 16 + (tid & 15), (tid & 63) >> 4, qv);
-  }
-  for (int it = blockIdx.x; it < cnt; it += gridDim.x) {
-    const int tid = fresh_tid();
-    const int wave = tid >> 6;
+    if constexpr (PREFQ || !PREF)
+      load_rows<BF>(qkv, 0, ld, base_nx, n_nx, (tid >> 6) * 16 + (tid & 15), (tid & 63) >> 4, qv);
+  };
+  if (PREF) fetch(first, fresh_tid() - part * NT * 64);
+  for (int it = first; it < cnt; it += step) {
+    const int tid = fresh_tid() - part * NT * 64;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
     const int r = lane & 15, g = lane >> 4;
-    if constexpr (!PREF) {
-      const int i = clist[it];
-      n_nx = nnei[i];
-      base_nx = pair_off[i];
-      stage_rows_load<NPAD, BF>(qkv, 128, ld, base_nx, n_nx, tid, sv);  // K
-      gv = gate_load(geom, base_nx, n_nx, tid, gl);
-      load_rows<BF>(qkv, 0, ld, base_nx, n_nx, wave * 16 + r, g, qv);
-    }
+    if constexpr (!PREF) fetch(it, tid);
     const int n = n_nx;
     const int base = base_nx;
     const int ntile = (n + 15) >> 4;
     const int q = wave * 16 + r;
     const bool qok = q < n;
+    if constexpr (PREF && !PREFQ) load_rows<BF>(qkv, 0, ld, base, n, q, g, qv);
     stage_rows_store<NPAD>(buf, tid, n, sv);
     gate_store<NPAD>(kg, kw, tid, n, gv, gl);
-    __syncthreads();
+    barrier();
     float4 vpre[8];  // V, read while Q K^T and the softmax run
     stage_t_load<NPAD, BF>(qkv, 256, ld, base, n, tid, vpre);
 
@@ -519,20 +576,10 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD
       invz = 1.0f / z;
       if (g == 0 && qok) fstat[base + q] = make_float2(m, invz);
     }
-    __syncthreads();
+    barrier();
     stage_t_store<NPAD>(buf, tid, n, vpre);  // V^T
-    __syncthreads();
-    if constexpr (PREF) {
-      const int itn = it + (int)gridDim.x;
-      if (itn < cnt) {
-        const int inx = clist[itn];
-        n_nx = nnei[inx];
-        base_nx = pair_off[inx];
-        stage_rows_load<NPAD, BF>(qkv, 128, ld, base_nx, n_nx, tid, sv);
-        gv = gate_load(geom, base_nx, n_nx, tid, gl);
-        load_rows<BF>(qkv, 0, ld, base_nx, n_nx, q, g, qv);
-      }
-    }
+    barrier();
+    if constexpr (PREFQ) fetch(it + step, tid);
 
     if (wave < ntile) {
       const float4 gq = kg[q];
@@ -572,7 +619,13 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD
         floatx4 y[kOpTiles];
 #pragma unroll
         for (int nt = 0; nt < kOpTiles; ++nt) y[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+        // columns past Nreal (96 < Nreal, so of the last tile) read its last
+        // row; the epilogue zeroes them
         const float *wl = wo + r * kLDR + 4 * g;
+        const float *wlast = wo + min((kOpTiles - 1) * 16 + r, op.Nreal - 1) * kLDR + 4 * g;
+        const auto w_at = [&](int nt, int k) {
+          return *(const floatx4 *)((nt < kOpTiles - 1 ? wl + nt * 16 * kLDR : wlast) + k);
+        };
         if constexpr (BF) {
           // feature chunks 2h and 2h + 1 in one 16x16x32 step
 #pragma unroll
@@ -581,8 +634,8 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD
             bf16x8 w[kOpTiles];
 #pragma unroll
             for (int nt = 0; nt < kOpTiles; ++nt)
-              w[nt] = to_bf16x8(*(const floatx4 *)(wl + nt * 16 * kLDR + 32 * h),
-                                *(const floatx4 *)(wl + nt * 16 * kLDR + 32 * h + 16));
+              w[nt] = to_bf16x8(w_at(nt, 32 * h),
+                                w_at(nt, 32 * h + 16));
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int nt = 0; nt < kOpTiles; ++nt) y[nt] = mfma_bf16x2(w[nt], ob, y[nt]);
@@ -593,7 +646,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD
             floatx4 w[kOpTiles];
 #pragma unroll
             for (int nt = 0; nt < kOpTiles; ++nt)
-              w[nt] = *(const floatx4 *)(wl + nt * 16 * kLDR + 16 * c);
+              w[nt] = w_at(nt, 16 * c);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -601,11 +654,15 @@ __global__ __launch_bounds__(NPAD / 16 * 64, BF && !OP ? (NPAD <= 64 ? 4 : (NPAD
               for (int nt = 0; nt < kOpTiles; ++nt) y[nt] = mfma4(w[nt][t], oacc[c][t], y[nt]);
           }
         }
+        // three wavefronts to a SIMD leave registers for the loads only now
+        if constexpr (PREF && !PREFQ) fetch(it + step, tid);
         lnres::apply_tile<kOpTiles>(y, gi, g, kOpTiles, op.Nreal, op.eps, cso, kOpCols, qok,
                                     base + q, rb, op.gout, op.xhat, op.rstd);
       }
+    } else if constexpr (PREF && !PREFQ) {
+      fetch(it + step, tid);
     }
-    __syncthreads();  // LDS is restaged for the next centre
+    barrier();  // LDS is restaged for the next centre
   }
 }
 
@@ -1422,29 +1479,7 @@ __global__ __launch_bounds__(bwds_threads<NPAD>(), NPAD <= 96 ? 3 : 2) void k_at
   // workgroups every centre has a CU to itself
   const int step = (int)gridDim.x * C;
   const int first = (int)blockIdx.x + part * (int)gridDim.x;
-  // Barrier of the wavefronts of one centre: a workgroup barrier when there is
-  // one centre, else an arrival count in LDS.  All of a workgroup's wavefronts
-  // are resident and pass the same barriers, so the count is reached; the other
-  // centre's phases, of other lengths, are not waited for.
-  unsigned arrived = 0;
-  if constexpr (C > 1) {
-    if (threadIdx.x < C) bar[threadIdx.x] = 0;
-    __syncthreads();
-  }
-  auto barrier = [&]() {
-    if constexpr (C == 1) {
-      __syncthreads();
-    } else {
-      arrived += NT;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      if ((threadIdx.x & 63) == 0)
-        __hip_atomic_fetch_add(&bar[part], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(
-                 &bar[part], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < arrived)
-        __builtin_amdgcn_s_sleep(1);
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    }
-  };
+  CentreBarrier<C, NT> barrier(bar, part);
   if (first >= cnt) return;  // one centre's wavefronts, no shared barrier follows
   fetch(first, fresh_tid() - part * NT * 64);
   for (int it = first; it < cnt; it += step) {
@@ -2188,10 +2223,11 @@ __global__ __launch_bounds__(256, 2) void k_desc_oproj_bwd(DescOprojArgs a) {
 // slots; each class runs a kernel sized for it, over its own centre list, so
 // the common case does not pay for the largest LDS size and an empty class
 // costs one wave of exiting blocks.
-template <int NPAD, bool OP = false>
-size_t fwd_lds() {
-  return (sizeof(float4) + sizeof(double)) * NPAD + sizeof(float) * stage_floats<NPAD>() +
-         (OP ? sizeof(float) * (kOpCols * kLDR + 3 * kOpCols) : 0);
+// LDS of C centres, and of the projection to `cols` features (0: none).
+template <int NPAD>
+size_t fwd_lds(int C, int cols) {
+  return C * fwd_centre_lds<NPAD>() +
+         (cols ? sizeof(float) * (cols * kLDR + 3 * kOpCols) : 0);
 }
 template <int NPAD>
 size_t bwdq_lds() {
@@ -2204,10 +2240,11 @@ size_t bwdk_lds() {
 
 // Persistent grid sizes: resident blocks per CU times CUs, per device.
 constexpr int kMaxDevices = 64;
-int g_grid[kMaxDevices][10][4];  // FP32 forward and adjoint, -; BF16 forward, query-tile and
-                                 // key-tile adjoint; -; FP32 forward with the output
-                                 // projection; fused BF16 adjoint; BF16 forward with the
-                                 // output projection
+// kinds: FP32 forward, adjoint, forward with the projection on one centre; BF16
+// forward, query-tile and key-tile adjoint, forward with the projection on one
+// centre; FP32 forward with the projection; BF16 fused adjoint, forward with the
+// projection
+int g_grid[kMaxDevices][10][4];
 
 int g_desc_grid[kMaxDevices][2];  // fused descriptor / projection adjoint: FP32, BF16
 
@@ -2239,31 +2276,24 @@ hipError_t prepare_class(int dev, int cus, int cls) {
                                              (int)lds)
                        : hipSuccess;
   };
-  hipError_t e = lds_limit((const void *)k_attn_fwd<NPAD, BF, false>, fwd_lds<NPAD>());
+  const auto prepare = [&](auto kernel, int threads, size_t lds, int kind) {
+    const hipError_t r = lds_limit((const void *)kernel, lds);
+    return r == hipSuccess ? occupancy_grid(kernel, threads, lds, cus, &g_grid[dev][kind][cls]) : r;
+  };
+  constexpr int C = fwd_centres<NPAD>();
+  hipError_t e = prepare(k_attn_fwd<NPAD, BF, false, 1>, th, fwd_lds<NPAD>(1, 0), BF ? 3 : 0);
   if (e == hipSuccess)
-    e = occupancy_grid(k_attn_fwd<NPAD, BF, false>, th, fwd_lds<NPAD>(), cus,
-                       &g_grid[dev][BF ? 3 : 0][cls]);
+    e = prepare(k_attn_fwd<NPAD, BF, true, C>, C * th, fwd_lds<NPAD>(C, kFwdMaxCols), BF ? 9 : 7);
   if (e == hipSuccess)
-    e = lds_limit((const void *)k_attn_fwd<NPAD, BF, true>, fwd_lds<NPAD, true>());
-  if (e == hipSuccess)
-    e = occupancy_grid(k_attn_fwd<NPAD, BF, true>, th, fwd_lds<NPAD, true>(), cus,
-                       &g_grid[dev][BF ? 9 : 7][cls]);
+    e = prepare(k_attn_fwd<NPAD, BF, true, 1>, th, fwd_lds<NPAD>(1, kOpCols), BF ? 6 : 2);
   if constexpr (!BF) {
-    if (e == hipSuccess) e = lds_limit((const void *)k_attn_bwd_s<NPAD>, bwds_lds<NPAD>());
     if (e == hipSuccess)
-      e = occupancy_grid(k_attn_bwd_s<NPAD>, bwds_threads<NPAD>(), bwds_lds<NPAD>(), cus,
-                         &g_grid[dev][1][cls]);
+      e = prepare(k_attn_bwd_s<NPAD>, bwds_threads<NPAD>(), bwds_lds<NPAD>(), 1);
   } else if constexpr (NPAD <= 96) {
-    if (e == hipSuccess) e = lds_limit((const void *)k_attn_bwd_f<NPAD>, bwdf_lds<NPAD>());
-    if (e == hipSuccess)
-      e = occupancy_grid(k_attn_bwd_f<NPAD>, th, bwdf_lds<NPAD>(), cus, &g_grid[dev][8][cls]);
+    if (e == hipSuccess) e = prepare(k_attn_bwd_f<NPAD>, th, bwdf_lds<NPAD>(), 8);
   } else {
-    if (e == hipSuccess) e = lds_limit((const void *)k_attn_bwd_q<NPAD>, bwdq_lds<NPAD>());
-    if (e == hipSuccess)
-      e = occupancy_grid(k_attn_bwd_q<NPAD>, th, bwdq_lds<NPAD>(), cus, &g_grid[dev][4][cls]);
-    if (e == hipSuccess) e = lds_limit((const void *)k_attn_bwd_k<NPAD>, bwdk_lds<NPAD>());
-    if (e == hipSuccess)
-      e = occupancy_grid(k_attn_bwd_k<NPAD>, th, bwdk_lds<NPAD>(), cus, &g_grid[dev][5][cls]);
+    if (e == hipSuccess) e = prepare(k_attn_bwd_q<NPAD>, th, bwdq_lds<NPAD>(), 4);
+    if (e == hipSuccess) e = prepare(k_attn_bwd_k<NPAD>, th, bwdk_lds<NPAD>(), 5);
   }
   return e;
 }
@@ -2330,19 +2360,27 @@ void launch_attn_fwd_class(int cls, const AttnArgs &a, const float *qkv, float *
                            float *fstat, const AttnOut *op, hipStream_t s) {
   if (a.nloc <= 0) return;
   const int *cl = a.clist + (size_t)cls * a.nloc, *cc = a.ccount + cls;
-  if (op) {
+  if (op && op->Nreal <= kFwdMaxCols) {
     const dim3 grid(grid_for(a.bf16 ? 9 : 7, cls, a.small));
-    ATTN_CLASS_SWITCH(cls, hipLaunchKernelGGL((k_attn_fwd<NP, BFV, true>), grid,
-                                              dim3(NP / 16 * 64), (fwd_lds<NP, true>()), s, qkv,
+    ATTN_CLASS_SWITCH(cls, {
+      constexpr int C = fwd_centres<NP>();
+      hipLaunchKernelGGL((k_attn_fwd<NP, BFV, true, C>), grid, dim3(C * NP / 16 * 64),
+                         fwd_lds<NP>(C, op->Nreal), s, qkv, a.geom, a.pair_off, a.nnei, cl, cc,
+                         a.sel, a.shift, out, lam, (float2 *)fstat, *op);
+    });
+  } else if (op) {
+    const dim3 grid(grid_for(a.bf16 ? 6 : 2, cls, a.small));
+    ATTN_CLASS_SWITCH(cls, hipLaunchKernelGGL((k_attn_fwd<NP, BFV, true, 1>), grid,
+                                              dim3(NP / 16 * 64), fwd_lds<NP>(1, op->Nreal), s,
+                                              qkv, a.geom, a.pair_off, a.nnei, cl, cc, a.sel,
+                                              a.shift, out, lam, (float2 *)fstat, *op));
+  } else {
+    const dim3 grid(grid_for(a.bf16 ? 3 : 0, cls, a.small));
+    ATTN_CLASS_SWITCH(cls, hipLaunchKernelGGL((k_attn_fwd<NP, BFV, false, 1>), grid,
+                                              dim3(NP / 16 * 64), fwd_lds<NP>(1, 0), s, qkv,
                                               a.geom, a.pair_off, a.nnei, cl, cc, a.sel, a.shift,
-                                              out, lam, (float2 *)fstat, *op));
-    return;
+                                              out, lam, (float2 *)fstat, AttnOut{}));
   }
-  const dim3 grid(grid_for(a.bf16 ? 3 : 0, cls, a.small));
-  ATTN_CLASS_SWITCH(cls, hipLaunchKernelGGL((k_attn_fwd<NP, BFV, false>), grid, dim3(NP / 16 * 64),
-                                            fwd_lds<NP>(), s, qkv, a.geom, a.pair_off, a.nnei,
-                                            cl, cc, a.sel, a.shift, out, lam, (float2 *)fstat,
-                                            AttnOut{}));
 }
 
 bool attn_bwd_fused(const AttnArgs &a, int cls) { return !a.bf16 || cls <= 2; }
