@@ -47,14 +47,13 @@ struct dp_trainer {
   // capacity-sized buffers
   void *arena = nullptr;
   int cap_n = 0, cap_frames = 0;
-  size_t Pcap = 0, ldr = 0;
   double *Fst = nullptr, *Est = nullptr, *vir = nullptr, *sq_part = nullptr, *le = nullptr;
   float *a_dev = nullptr;
   float4 *delta = nullptr;
   float *Td = nullptr, *Xd = nullptr, *Zd1 = nullptr, *Yd1 = nullptr, *Zd2 = nullptr,
         *WoR = nullptr, *Zb2 = nullptr, *Yb1 = nullptr, *Zb1 = nullptr, *Db = nullptr;
   float *X3 = nullptr, *Z3 = nullptr, *X2 = nullptr, *Z2 = nullptr, *Z1 = nullptr,
-        *WS1 = nullptr, *HB2 = nullptr;
+        *WS1 = nullptr;
   int *grp = nullptr;
   float *part = nullptr;
   size_t part_cap = 0;
@@ -120,8 +119,8 @@ int ensure_buffers(dp_trainer *t, int n, int nframes) {
   const int cn = std::max(n, t->cap_n), cf = std::max(nframes, t->cap_frames);
   dp_model *m = t->m;
   const size_t P = ((size_t)cn * m->sel + 15) / 16 * 16;
-  // feature-major pair operands: primal rows [0, P), tangent rows [P, 2 P), and one
-  // 16-row step of slack read (masked) past the last row
+  // pair operands: primal rows [0, P), tangent rows [P, 2 P), and one 16-row step of
+  // slack read (masked) past the last row
   const size_t ldr = 2 * P + 16;
   const int ldD = m->ldD, ldf0 = m->ldf[0], ldf1 = m->ldf[1];
   const int nsq = tr_seed_blocks(cn);
@@ -146,7 +145,7 @@ int ensure_buffers(dp_trainer *t, int n, int nframes) {
                oX3 = take(sizeof(float) * ldr * kTrN2), oZ3 = take(sizeof(float) * ldr * kTrN3),
                oX2 = take(sizeof(float) * ldr * kTrN1), oZ2 = take(sizeof(float) * ldr * kTrN2),
                oZ1 = take(sizeof(float) * ldr * kTrN1), oWS1 = take(sizeof(float) * ldr * kTrN1),
-               oHB2 = take(sizeof(float) * ldr * kTrN2), oGrp = take(sizeof(int) * (P + 16));
+               oGrp = take(sizeof(int) * (P + 16));
   if (ldr * kTrN3 >= ((size_t)1 << 32))
     return fail(DP_ERR_ARG, "natoms * sel = %zu pair rows exceed the trainer's limit", P);
   const size_t part_cap = (size_t)1 << 22;
@@ -182,12 +181,9 @@ int ensure_buffers(dp_trainer *t, int n, int nframes) {
   t->Z2 = (float *)(b + oZ2);
   t->Z1 = (float *)(b + oZ1);
   t->WS1 = (float *)(b + oWS1);
-  t->HB2 = (float *)(b + oHB2);
   t->grp = (int *)(b + oGrp);
   t->part = (float *)(b + oPart);
   t->part_cap = part_cap;
-  t->Pcap = P;
-  t->ldr = ldr;
   t->cap_n = cn;
   t->cap_frames = cf;
   return DP_OK;
@@ -207,7 +203,7 @@ int batch_gradient(dp_trainer *t, const double *d_frames, const int32_t *d_types
   const float cf = (float)(2.0 * pf / (3.0 * N * B));
   const double ca = 2.0 * pe / ((double)N * N * B), cl = pe / ((double)N * N * B);
   const int nsq = tr_seed_blocks(N);
-  // pair-row stride of the feature-major operands: the tangent rows start at Pst
+  // the pair operands' tangent rows start at Pst
   const size_t Pst = ((size_t)N * m->sel + 15) / 16 * 16;
   launch_fill_f64(t->acc, t->acc_n, s);
   for (int f = 0; f < B; ++f) {
@@ -245,7 +241,7 @@ int batch_gradient(dp_trainer *t, const double *d_frames, const int32_t *d_types
     pa.ntypes = T;
     pa.T = w.T;
     pa.axis = m->axis;
-    launch_tr_tangent(pa, t->delta, t->Td, t->Xd, ldD, s);
+    HIP_TRY(launch_tr_tangent(pa, t->delta, t->Td, t->Xd, ldD, s));
     // fitting net: tangents forward, then values and tangents backward
     const Linear &L0 = m->fitl[0], &L1 = m->fitl[1];
     const int bf = m->bf16;
@@ -261,22 +257,21 @@ int batch_gradient(dp_trainer *t, const double *d_frames, const int32_t *d_types
     gemm_linear(GemmArgs{t->Zb1, ldf0, L0.Wb, ldf0, ldD, m->M * m->axis, nullptr, 2 * N, bf},
                 nullptr, t->Db, ldD, s);
     // descriptor and embedding net
-    const size_t ldr = t->ldr;
-    launch_tr_pair_rev(pa, t->delta, t->Td, t->Db, ldD, Pst, ldr, t->X3, t->Z3, t->X2, t->Z2,
-                       t->Z1, t->WS1, t->HB2, t->grp, s);
+    HIP_TRY(launch_tr_pair_rev(pa, t->delta, t->Td, t->Db, ldD, Pst, t->X3, t->Z3, t->X2,
+                               t->Z2, t->Z1, t->WS1, t->grp, s));
     const int *Pdev = w.pair_off + N;
     const int Pmax = (int)Pst;
-    tr_wgrad_fm(t->X3, t->Z3, ldr, Pst, kTrN2, kTrN3, Pdev, Pmax, bf, t->part, t->part_cap,
+    tr_wgrad_fm(t->X3, t->Z3, Pst, kTrN2, kTrN3, Pdev, Pmax, bf, t->part, t->part_cap,
                 t->acc + t->o_W3, s);
-    tr_wgrad_fm(t->X2, t->Z2, ldr, Pst, kTrN1, kTrN2, Pdev, Pmax, bf, t->part, t->part_cap,
+    tr_wgrad_fm(t->X2, t->Z2, Pst, kTrN1, kTrN2, Pdev, Pmax, bf, t->part, t->part_cap,
                 t->acc + t->o_W2, s);
-    tr_colsum_fm(t->Z3, ldr, kTrN3, Pdev, Pmax, nullptr, 1, t->part, t->part_cap,
+    tr_colsum_fm(t->Z3, kTrN3, Pdev, Pmax, nullptr, 1, t->part, t->part_cap,
                  t->acc + t->o_b3, s);
-    tr_colsum_fm(t->Z2, ldr, kTrN2, Pdev, Pmax, nullptr, 1, t->part, t->part_cap,
+    tr_colsum_fm(t->Z2, kTrN2, Pdev, Pmax, nullptr, 1, t->part, t->part_cap,
                  t->acc + t->o_b2, s);
-    tr_colsum_fm(t->Z1, ldr, kTrN1, Pdev, Pmax, t->grp, T * T, t->part, t->part_cap,
+    tr_colsum_fm(t->Z1, kTrN1, Pdev, Pmax, t->grp, T * T, t->part, t->part_cap,
                  t->acc + t->o_tab, s);
-    tr_colsum_fm(t->WS1, ldr, kTrN1, Pdev, Pmax, nullptr, 1, t->part, t->part_cap,
+    tr_colsum_fm(t->WS1, kTrN1, Pdev, Pmax, nullptr, 1, t->part, t->part_cap,
                  t->acc + t->o_ws, s);
     tr_wgrad(w.z[0], t->Yd1, ldf0, t->Zb2, t->Zb2 + (size_t)N * ldf1, ldf1, H0, H1, nullptr, N,
              bf, t->part, t->part_cap, t->acc + t->o_W1f, s);

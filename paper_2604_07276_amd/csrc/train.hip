@@ -23,17 +23,10 @@ typedef float floatx8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kWaves = 4;          // centres per 256-thread block
-constexpr int kGS = kTrN3 + 1;     // LDS row stride of per-pair G rows
-
-// Weights are read through the constant address space: the loads are then
-// scalar (uniform, never written by the kernel) and the weights live in SGPRs.
-typedef const float __attribute__((address_space(4))) *cfp;
-__device__ __forceinline__ float wc(const float *p, int i) { return ((cfp)p)[i]; }
-
-__device__ __forceinline__ void lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  __syncthreads();
+// Order of one wavefront's LDS accesses (the hardware keeps them in order).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // ---------------------------------------------------------------- seeds
@@ -84,11 +77,13 @@ __device__ __forceinline__ PairTangent pair_tangent(const float4 g0, const float
   PairTangent t;
   const float s = g0.x, rx = g0.y, ry = g0.z, rz = g0.w, r = g1.y, dsw = g1.z;
   const float ddx = dj.x - di.x, ddy = dj.y - di.y, ddz = dj.z - di.z;
-  const float rdot = rx * ddx + ry * ddy + rz * ddz;
+  // (written as the fused operations they are, so that every kernel gets the
+  // same bits)
+  const float rdot = fmaf(rz, ddz, fmaf(ry, ddy, rx * ddx));
   const float inv_r = 1.0f / r;
   const float sdot = (dsw - s) * inv_r * rdot;
-  const float ux = (ddx - rx * rdot) * inv_r, uy = (ddy - ry * rdot) * inv_r,
-              uz = (ddz - rz * rdot) * inv_r;
+  const float ux = fmaf(-rx, rdot, ddx) * inv_r, uy = fmaf(-ry, rdot, ddy) * inv_r,
+              uz = fmaf(-rz, rdot, ddz) * inv_r;
   t.s = s;
   t.sdot = sdot;
   t.Rt[0] = s;
@@ -96,147 +91,226 @@ __device__ __forceinline__ PairTangent pair_tangent(const float4 g0, const float
   t.Rt[2] = s * ry;
   t.Rt[3] = s * rz;
   t.Rd[0] = sdot;
-  t.Rd[1] = sdot * rx + s * ux;
-  t.Rd[2] = sdot * ry + s * uy;
-  t.Rd[3] = sdot * rz + s * uz;
+  t.Rd[1] = fmaf(rx, sdot, s * ux);
+  t.Rd[2] = fmaf(ry, sdot, s * uy);
+  t.Rd[3] = fmaf(rz, sdot, s * uz);
   return t;
 }
 
-// First layer h1 = tanh(table[t_j][t_i] + ws s) and h1' = (1 - h1^2) ws.
-__device__ __forceinline__ void emb_l1(const TrainPairArgs &a, int tj, int ti, float s,
-                                       float h1[kTrN1], float h1d[kTrN1]) {
-  const float4 *tab = (const float4 *)(a.table + (size_t)(tj * a.ntypes + ti) * kTrN1);
-#pragma unroll
-  for (int q = 0; q < kTrN1 / 4; ++q) {
-    const float4 tv = tab[q];
-    const float zz[4] = {tv.x, tv.y, tv.z, tv.w};
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int o = 4 * q + u;
-      const float t = tanh_fast(fmaf(wc(a.ws, o), s, zz[u]));
-      h1[o] = t;
-      h1d[o] = (1.0f - t * t) * wc(a.ws, o);
-    }
+// ------------------------------------------------ embedding net on 16 pairs
+//
+// The per-pair embedding passes run on the FP32 matrix cores, a wavefront
+// taking tiles of 16 pairs of its centre.  v_mfma_f32_16x16x4_f32 is, bit for
+// bit, a chain of fused multiply-adds over its four depths in order (checked on
+// the hardware over 1.5 M results), so a product over ascending depth started
+// from the bias gives the bits of the scalar loop z = fma(w[k], h[k], z), at
+// twice the vector unit's rate and without a scalar weight load per use.  With
+// weights as the row operand a lane receives, for pair r = lane % 16, outputs
+// 16 t + 4 g + {0..3} (g = lane / 16) of tile t; as the column operand of the
+// next product it has to hold depth 4 c + g in step c, which a turn through
+// wave-private LDS arranges (rows of 68 or 36 floats: no bank conflicts).
+// Weights sit in LDS in the order of the steps: 64 lanes' values side by side.
+//
+// One lane per pair with scalar weights left a third of the lanes idle (84
+// neighbours in two chunks of 64) and, at 256 registers and more, one wavefront
+// per SIMD.  Per frame at 15,668 atoms: tangents 753 -> 251 us, adjoints
+// 1304 + 325 (a second kernel for the first two layers) -> 1058 us; at 192 atoms
+// 58 -> 26 and 85 + 18 -> 43 us.
+
+constexpr int kTrWaves = 12;             // wavefronts of a workgroup, three per SIMD
+constexpr int kTrRow = 68;               // LDS row of 64 values
+constexpr int kTrRow2 = 36;              // LDS row of 32 values
+constexpr int kTrTile = 16 * kTrRow;     // floats of a 16 x 64 tile
+// operand order in LDS: W2 [2 tiles][4 steps], W3 [4][8], and for the reverse
+// W3^T [2][16] and W2^T with the residual's unit rows [16]
+constexpr int kTrW2 = 2 * 4 * 64, kTrW3 = 4 * 8 * 64, kTrW3r = 2 * 16 * 64, kTrW2r = 16 * 64;
+
+__device__ __forceinline__ floatx4 mfma4(float a, float b, const floatx4 &c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ void stage_forward_weights(const TrainPairArgs &a, float *w2, float *w3) {
+  for (int e = threadIdx.x; e < kTrW2; e += 64 * kTrWaves) {
+    const int l = e & 63, c = (e >> 6) & 3, t = e >> 8;
+    w2[e] = a.W2t[(16 * t + (l & 15)) * kTrN1 + 4 * c + (l >> 4)];
+  }
+  for (int e = threadIdx.x; e < kTrW3; e += 64 * kTrWaves) {
+    const int l = e & 63, c = (e >> 6) & 7, t = e >> 9;
+    w3[e] = a.W3t[(16 * t + (l & 15)) * kTrN2 + 4 * c + (l >> 4)];
   }
 }
 
-// Second layer (doubling residual): h2 = tanh(W2^T h1 + b2) + [h1, h1] and its
-// derivative h2' = (1 - t^2) W2^T h1' + [h1', h1'].
-__device__ __forceinline__ void emb_l2(const TrainPairArgs &a, const float h1[kTrN1],
-                                       const float h1d[kTrN1], float h2[kTrN2],
-                                       float h2d[kTrN2]) {
+// One tile's first two layers.  h1, h1d: outputs 4 g + v; h2, h2d, t2, zd2
+// (second layer's tanh and derivative sum): outputs 16 t + 4 g + v.
+struct TileL12 {
+  floatx4 h1, h1d;
+  floatx4 h2[2], h2d[2], t2[2], zd2[2];
+};
+
+// First layer h1 = tanh(table[t_j][t_i] + ws s), h1' = (1 - h1^2) ws; second
+// (doubling residual) h2 = tanh(W2^T h1 + b2) + [h1, h1] and
+// h2' = (1 - t^2) W2^T h1' + [h1', h1'].
+__device__ __forceinline__ void tile_l12(const TrainPairArgs &a, const float *w2, const float *tab,
+                                         float s, int lane, int g, TileL12 &o) {
+  const floatx4 tv = *(const floatx4 *)(tab + 4 * g), wv = *(const floatx4 *)(a.ws + 4 * g);
+  float tb[4], wb[4];
 #pragma unroll
-  for (int o = 0; o < kTrN2; ++o) {
-    float z = wc(a.b2, o), zd = 0.f;
-#pragma unroll
-    for (int k = 0; k < kTrN1; ++k) {
-      z = fmaf(wc(a.W2t, o * kTrN1 + k), h1[k], z);
-      zd = fmaf(wc(a.W2t, o * kTrN1 + k), h1d[k], zd);
-    }
-    const float t = tanh_fast(z);
-    h2[o] = t + h1[o % kTrN1];
-    h2d[o] = (1.0f - t * t) * zd + h1d[o % kTrN1];
+  for (int c = 0; c < 4; ++c) {
+    tb[c] = tab[4 * c + g];
+    wb[c] = a.ws[4 * c + g];
   }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const float t = tanh_fast(fmaf(wv[v], s, tv[v]));
+    o.h1[v] = t;
+    o.h1d[v] = (1.0f - t * t) * wv[v];
+  }
+  floatx4 z[2], zd[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    z[t] = *(const floatx4 *)(a.b2 + 16 * t + 4 * g);
+    zd[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float t = tanh_fast(fmaf(wb[c], s, tb[c]));
+    const float td = (1.0f - t * t) * wb[c];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float w = w2[(q * 4 + c) * 64 + lane];
+      z[q] = mfma4(w, t, z[q]);
+      zd[q] = mfma4(w, td, zd[q]);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float t = tanh_fast(z[q][v]);
+      o.t2[q][v] = t;
+      o.zd2[q][v] = zd[q][v];
+      o.h2[q][v] = t + o.h1[v];
+      o.h2d[q][v] = (1.0f - t * t) * zd[q][v] + o.h1d[v];
+    }
 }
 
-// Number of 64-pair chunks the block must run: the largest of its centres.
-__device__ __forceinline__ int block_chunks(const int *nnei, int nloc) {
-  int mx = 0;
+// Third layer's sums z3 = W3^T h2 + b3 and W3^T h2' of one tile; buf: 2 x 16
+// rows of kTrRow2.
+__device__ __forceinline__ void tile_l3(const TrainPairArgs &a, const float *w3, float *buf,
+                                        int lane, int r, int g, const TileL12 &x, floatx4 (&z)[4],
+                                        floatx4 (&zd)[4]) {
+  float *b2 = buf + 16 * kTrRow2;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    const int i = blockIdx.x * kWaves + w;
-    mx = max(mx, i < nloc ? nnei[i] : 0);
+  for (int q = 0; q < 2; ++q) {
+    *(floatx4 *)(buf + r * kTrRow2 + 16 * q + 4 * g) = x.h2[q];
+    *(floatx4 *)(b2 + r * kTrRow2 + 16 * q + 4 * g) = x.h2d[q];
   }
-  return (mx + 63) / 64;
+  wave_fence();
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    z[t] = *(const floatx4 *)(a.b3 + 16 * t + 4 * g);
+    zd[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const float h = buf[r * kTrRow2 + 4 * c + g], hd = b2[r * kTrRow2 + 4 * c + g];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float w = w3[(t * 8 + c) * 64 + lane];
+      z[t] = mfma4(w, h, z[t]);
+      zd[t] = mfma4(w, hd, zd[t]);
+    }
+  }
+  wave_fence();
 }
 
 // ------------------------------------------------------------ tangent pass
 
-// One wave per centre.  Lanes over pairs compute G, G' (embedding forward
-// and its s-derivative) and the coefficients of
+// One wavefront per centre.  Per tile of 16 pairs: G, G' (embedding forward and
+// its s-derivative, lanes over pairs and features) and the coefficients of
 // T-dot[c][m] = (1/sel) sum_p (R~-dot_p[c] G_p[m] + R~_p[c] s-dot_p G'_p[m]);
-// lanes over m then accumulate T-dot and form
+// lanes over m then accumulate T-dot pair by pair and at the end form
 // D-dot[m][a] = sum_c (T-dot[c][m] T[c][a] + T[c][m] T-dot[c][a]).
-__global__ __launch_bounds__(256) void k_tr_tangent(TrainPairArgs a,
-                                                    const float4 *__restrict__ delta,
-                                                    float *__restrict__ Td,
-                                                    float *__restrict__ Xd, int ldD) {
-  __shared__ float sG[kWaves][64 * kGS];
-  __shared__ float sGp[kWaves][64 * kGS];
-  __shared__ float sC[kWaves][64 * 8];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = blockIdx.x * kWaves + w;
-  const bool live = i < a.nloc;
-  const int ic = live ? i : 0;
-  const int n = live ? a.nnei[ic] : 0;
-  const int off = a.pair_off[ic];
-  const int ti = a.types[ic];
-  const float4 di = delta[ic];
-  const int nch = block_chunks(a.nnei, a.nloc);
-  float tacc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int ch = 0; ch < nch; ++ch) {
-    const int p = ch * 64 + lane;
-    const bool valid = p < n;
-    const int pc = valid ? p : 0;
-    const int q = off + pc;
-    const float4 *gp = (const float4 *)(a.geom + (size_t)q * kGeom);
-    const float4 g0 = gp[0], g1 = gp[1];
-    const int j = a.nlist[(size_t)ic * a.sel + pc];
-    const int tj = a.types[j];
-    const float4 dj = delta[j];
-    if (valid) {
+constexpr int kTrTanWave = 2 * kTrTile + 16 * 8;  // G rows, G' rows, coefficients
+constexpr size_t kTrTanLds = sizeof(float) * (kTrW2 + kTrW3 + kTrWaves * kTrTanWave);
+
+__global__ __launch_bounds__(64 * kTrWaves, 3) void k_tr_tangent(TrainPairArgs a,
+                                                                 const float4 *__restrict__ delta,
+                                                                 float *__restrict__ Td,
+                                                                 float *__restrict__ Xd, int ldD) {
+  extern __shared__ float4 smem[];
+  float *w2 = (float *)smem, *w3 = w2 + kTrW2;
+  stage_forward_weights(a, w2, w3);
+  __syncthreads();
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4;
+  float *sG = w3 + kTrW3 + w * kTrTanWave, *sGp = sG + kTrTile, *sC = sGp + kTrTile;
+  for (int i = w * (int)gridDim.x + blockIdx.x; i < a.nloc; i += kTrWaves * gridDim.x) {
+    const int n = a.nnei[i];
+    const int off = a.pair_off[i];
+    const int ti = a.types[i];
+    const float4 di = delta[i];
+    float tacc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < n; p0 += 16) {
+      const int pc = p0 + r < n ? p0 + r : 0;  // (rows past n: the first pair's, unused)
+      const float4 *gp = (const float4 *)(a.geom + (size_t)(off + pc) * kGeom);
+      const float4 g0 = gp[0], g1 = gp[1];
+      const int j = a.nlist[(size_t)i * a.sel + pc];
+      const int tj = a.types[j];
+      const float4 dj = delta[j];
       const PairTangent pt = pair_tangent(g0, g1, di, dj);
-      float h1[kTrN1], h1d[kTrN1], h2[kTrN2], h2d[kTrN2];
-      emb_l1(a, tj, ti, pt.s, h1, h1d);
-      emb_l2(a, h1, h1d, h2, h2d);
-#pragma unroll 4
-      for (int o = 0; o < kTrN3; ++o) {
-        float z = wc(a.b3, o), zd = 0.f;
+      TileL12 x;
+      tile_l12(a, w2, a.table + (size_t)(tj * a.ntypes + ti) * kTrN1, pt.s, lane, g, x);
+      floatx4 z[4], zd[4];
+      tile_l3(a, w3, sG, lane, r, g, x, z, zd);
 #pragma unroll
-        for (int k = 0; k < kTrN2; ++k) {
-          z = fmaf(wc(a.W3t, o * kTrN2 + k), h2[k], z);
-          zd = fmaf(wc(a.W3t, o * kTrN2 + k), h2d[k], zd);
+      for (int t = 0; t < 4; ++t) {
+        floatx4 gv, gd;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float th = tanh_fast(z[t][v]);
+          gv[v] = th + x.h2[t & 1][v];
+          gd[v] = (1.0f - th * th) * zd[t][v] + x.h2d[t & 1][v];
         }
-        const float t = tanh_fast(z);
-        sG[w][lane * kGS + o] = t + h2[o % kTrN2];
-        sGp[w][lane * kGS + o] = (1.0f - t * t) * zd + h2d[o % kTrN2];
+        *(floatx4 *)(sG + r * kTrRow + 16 * t + 4 * g) = gv;
+        *(floatx4 *)(sGp + r * kTrRow + 16 * t + 4 * g) = gd;
       }
+      if (g == 0) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        sC[w][lane * 8 + c] = pt.Rd[c] * a.inv_sel;
-        sC[w][lane * 8 + 4 + c] = pt.Rt[c] * pt.sdot * a.inv_sel;
+        for (int c = 0; c < 4; ++c) {
+          sC[r * 8 + c] = pt.Rd[c] * a.inv_sel;
+          sC[r * 8 + 4 + c] = pt.Rt[c] * pt.sdot * a.inv_sel;
+        }
       }
+      wave_fence();
+      const int cnt = min(16, n - p0);
+      for (int pp = 0; pp < cnt; ++pp) {
+        const float gv = sG[pp * kTrRow + lane], gd = sGp[pp * kTrRow + lane];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          tacc[c] = fmaf(sC[pp * 8 + c], gv, fmaf(sC[pp * 8 + 4 + c], gd, tacc[c]));
+      }
+      wave_fence();
     }
-    lds_fence();
-    const int cnt = max(0, min(64, n - ch * 64));
-    for (int pp = 0; pp < cnt; ++pp) {
-      const float g = sG[w][pp * kGS + lane], gd = sGp[w][pp * kGS + lane];
+    // D-dot from T-dot and T (lane = m)
+    float tv[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        tacc[c] = fmaf(sC[w][pp * 8 + c], g, fmaf(sC[w][pp * 8 + 4 + c], gd, tacc[c]));
+    for (int c = 0; c < 4; ++c) {
+      tv[c] = a.T[((size_t)i * 4 + c) * kTrN3 + lane];
+      sG[c * 64 + lane] = tv[c];
+      sG[256 + c * 64 + lane] = tacc[c];
+      Td[((size_t)i * 4 + c) * kTrN3 + lane] = tacc[c];
     }
-    lds_fence();
-  }
-  // D-dot from T-dot and T (lane = m)
-  float tv[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    tv[c] = a.T[((size_t)ic * 4 + c) * kTrN3 + lane];
-    sC[w][c * 64 + lane] = tv[c];
-    sC[w][256 + c * 64 + lane] = tacc[c];
-  }
-  lds_fence();
-  if (live) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) Td[((size_t)i * 4 + c) * kTrN3 + lane] = tacc[c];
+    wave_fence();
     float *xp = Xd + (size_t)i * ldD + (size_t)lane * a.axis;
     for (int ax = 0; ax < a.axis; ++ax) {
       float v = 0.f;
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        v = fmaf(tacc[c], sC[w][c * 64 + ax], fmaf(tv[c], sC[w][256 + c * 64 + ax], v));
+        v = fmaf(tacc[c], sG[c * 64 + ax], fmaf(tv[c], sG[256 + c * 64 + ax], v));
       xp[ax] = v;
     }
+    wave_fence();
   }
 }
 
@@ -292,253 +366,252 @@ __global__ void k_tr_fit_l0(const float *__restrict__ t1, const float *__restric
 
 // ------------------------------------------------------------- pair reverse
 
-// One wave per centre.  Lanes over m form T-bar and T-dot-bar from D-bar and
-// D-dot-bar (reverse of D = T^T T<, D-dot = T-dot^T T< + T^T T-dot<); lanes
-// over pairs then form G-bar = (1/sel)(R~ T-bar + R~-dot T-dot-bar) and
-// G'-bar = (1/sel) s-dot R~ T-dot-bar and run the reverse of the embedding net
-// and of its s-derivative, writing the rows of the weight gradients.
-__global__ __launch_bounds__(256) void k_tr_pair_rev(
-    TrainPairArgs a, const float4 *__restrict__ delta, const float *__restrict__ Td,
-    const float *__restrict__ Db, int ldD, size_t Pcap, size_t ldr, float *__restrict__ X3,
-    float *__restrict__ Z3, float *__restrict__ HB2, int *__restrict__ grp) {
-  __shared__ float sT[kWaves][4 * 64], sTd[kWaves][4 * 64];
-  __shared__ float sDb[kWaves][64 * 16], sDdb[kWaves][64 * 16];
-  __shared__ float sTb[kWaves][4 * 64], sTdb[kWaves][4 * 64];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = blockIdx.x * kWaves + w;
-  const bool live = i < a.nloc;
-  const int ic = live ? i : 0;
-  const int n = live ? a.nnei[ic] : 0;
-  const int off = a.pair_off[ic];
-  const int ti = a.types[ic];
-  const int ax = a.axis;
-  const int nloc = a.nloc;
-  // --- T-bar, T-dot-bar (lane = m)
-  float tv[4], tdv[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    tv[c] = a.T[((size_t)ic * 4 + c) * kTrN3 + lane];
-    tdv[c] = Td[((size_t)ic * 4 + c) * kTrN3 + lane];
-    sT[w][c * 64 + lane] = tv[c];
-    sTd[w][c * 64 + lane] = tdv[c];
-  }
-  for (int b = 0; b < ax; ++b) {
-    sDb[w][lane * 16 + b] = Db[(size_t)ic * ldD + (size_t)lane * ax + b];
-    sDdb[w][lane * 16 + b] = Db[(size_t)(nloc + ic) * ldD + (size_t)lane * ax + b];
-  }
-  lds_fence();
-  float tb[4] = {0.f, 0.f, 0.f, 0.f}, tdb[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int b = 0; b < ax; ++b) {
-    const float db = sDb[w][lane * 16 + b], ddb = sDdb[w][lane * 16 + b];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      tb[c] = fmaf(db, sT[w][c * 64 + b], fmaf(ddb, sTd[w][c * 64 + b], tb[c]));
-      tdb[c] = fmaf(ddb, sT[w][c * 64 + b], tdb[c]);
-    }
-  }
-  if (lane < ax) {
-    for (int mp = 0; mp < kTrN3; ++mp) {
-      const float db = sDb[w][mp * 16 + lane], ddb = sDdb[w][mp * 16 + lane];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        tb[c] = fmaf(db, sT[w][c * 64 + mp], fmaf(ddb, sTd[w][c * 64 + mp], tb[c]));
-        tdb[c] = fmaf(ddb, sT[w][c * 64 + mp], tdb[c]);
-      }
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    sTb[w][c * 64 + lane] = tb[c] * a.inv_sel;
-    sTdb[w][c * 64 + lane] = tdb[c] * a.inv_sel;
-  }
-  lds_fence();
-  // --- pairs
-  const float4 di = delta[ic];
-  const unsigned ld32 = (unsigned)ldr, pc32 = (unsigned)Pcap;
-  const int nch = block_chunks(a.nnei, a.nloc);
-  for (int ch = 0; ch < nch; ++ch) {
-    const int p = ch * 64 + lane;
-    const bool valid = p < n;
-    const int pc = valid ? p : 0;
-    const size_t q = (size_t)off + pc;
-    const float4 *gp = (const float4 *)(a.geom + q * kGeom);
-    const float4 g0 = gp[0], g1 = gp[1];
-    const int j = a.nlist[(size_t)ic * a.sel + pc];
-    const int tj = a.types[j];
-    const float4 dj = delta[j];
-    if (!valid) continue;
-    const PairTangent pt = pair_tangent(g0, g1, di, dj);
-    float h1[kTrN1], h1d[kTrN1], h2[kTrN2], h2d[kTrN2];
-    emb_l1(a, tj, ti, pt.s, h1, h1d);
-    emb_l2(a, h1, h1d, h2, h2d);
-    // feature-major stores: 32-bit offsets advanced one feature row at a time
-    // (the host keeps 64 * ldr below 2^32)
-    {
-      unsigned off = (unsigned)q;
-#pragma unroll
-      for (int k = 0; k < kTrN2; ++k) {
-        X3[off] = h2[k];
-        X3[off + pc32] = h2d[k];
-        off += ld32;
-      }
-    }
-    // third layer (doubling residual) in reverse
-    float hb2[kTrN2], hb2d[kTrN2];
-#pragma unroll
-    for (int k = 0; k < kTrN2; ++k) hb2[k] = hb2d[k] = 0.f;
-    unsigned zoff = (unsigned)q;
-#pragma unroll 1
-    for (int o = 0; o < kTrN3; ++o) {
-      float Gb = 0.f, Gdb = 0.f;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const float b1v = sTb[w][c * 64 + o], b2v = sTdb[w][c * 64 + o];
-        Gb = fmaf(pt.Rt[c], b1v, fmaf(pt.Rd[c], b2v, Gb));
-        Gdb = fmaf(pt.Rt[c], b2v, Gdb);
-      }
-      Gdb *= pt.sdot;
-      float z = wc(a.b3, o), zd = 0.f;
-#pragma unroll
-      for (int k = 0; k < kTrN2; ++k) {
-        z = fmaf(wc(a.W3t, o * kTrN2 + k), h2[k], z);
-        zd = fmaf(wc(a.W3t, o * kTrN2 + k), h2d[k], zd);
-      }
-      const float t = tanh_fast(z), g = 1.0f - t * t;
-      const float zbd = g * Gdb;
-      const float zb = g * (Gb - 2.0f * t * zd * Gdb);
-#pragma unroll
-      for (int k = 0; k < kTrN2; ++k) {
-        hb2[k] = fmaf(wc(a.W3t, o * kTrN2 + k), zb, hb2[k]);
-        hb2d[k] = fmaf(wc(a.W3t, o * kTrN2 + k), zbd, hb2d[k]);
-      }
-      Z3[zoff] = zb;
-      Z3[zoff + pc32] = zbd;
-      zoff += ld32;
-    }
-    // the [h2, h2] residual: G-bar[k] and G-bar[k + 32] both feed h2[k]
-#pragma unroll
-    for (int k = 0; k < kTrN2; ++k) {
-      float gb = 0.f, gdb = 0.f;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const int o = k + hh * kTrN2;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const float b1v = sTb[w][c * 64 + o], b2v = sTdb[w][c * 64 + o];
-          gb = fmaf(pt.Rt[c], b1v, fmaf(pt.Rd[c], b2v, gb));
-          gdb = fmaf(pt.Rt[c], b2v, gdb);
-        }
-      }
-      hb2[k] += gb;
-      hb2d[k] = fmaf(gdb, pt.sdot, hb2d[k]);
-    }
-    {
-      unsigned off = (unsigned)q;
-#pragma unroll
-      for (int k = 0; k < kTrN2; ++k) {
-        HB2[off] = hb2[k];
-        HB2[off + pc32] = hb2d[k];
-        off += ld32;
-      }
-    }
-    grp[q] = tj * a.ntypes + ti;
-  }
+// Element of feature 0 of pair row q in a weight-gradient operand of nf
+// features: blocks of 16 rows, feature by feature inside a block.  A tile's
+// stores then fall into one or two blocks of contiguous memory; one row per
+// feature over all pairs (320 streams a tile, 64 bytes at a time) bound the
+// writer: 1372 us a frame at 15,668 atoms, this order 1058 us.
+__device__ __forceinline__ unsigned tr_row(unsigned q, int nf) {
+  return (q >> 4) * (unsigned)(16 * nf) + (q & 15u);
 }
 
+// One wavefront per centre.  Lanes over m form T-bar and T-dot-bar from D-bar
+// and D-dot-bar (reverse of D = T^T T<, D-dot = T-dot^T T< + T^T T-dot<); per
+// tile of 16 pairs follow G-bar = (1/sel)(R~ T-bar + R~-dot T-dot-bar) and
+// G'-bar = (1/sel) s-dot R~ T-dot-bar, and the reverse of the embedding net and
+// of its s-derivative down to the first layer, writing the rows of the weight
+// gradients.  Every sum is a matrix-core chain in the order of its scalar form:
+// the terms of G-bar alternate R~-dot T-dot-bar and R~ T-bar over c, the [h2, h2]
+// and [h1, h1] residuals enter where the loop over outputs adds them (the
+// latter as unit-weight depths between the outputs' own).
+constexpr int kTrRevWave = 2 * 64 * 16 + 2 * 4 * 64;  // D-bar, D-dot-bar, T, T-dot; tiles
+static_assert(kTrRevWave >= 2 * kTrTile, "two 16 x 64 tiles share the space");
+constexpr size_t kTrRevLds =
+    sizeof(float) * (kTrW2 + kTrW3 + kTrW3r + kTrW2r + kTrWaves * kTrRevWave);
 
-// Second and first embedding layers in reverse, one lane per pair (flat over
-// the pair rows): from h2-bar, h2'-bar of the per-centre sweep, recomputing
-// h1, h1' from s and the pair's types.
-__global__ __launch_bounds__(256) void k_tr_pair_rev2(TrainPairArgs a, const int *__restrict__ Pdev,
-                                                      size_t Pcap, size_t ldr,
-                                                      const float *__restrict__ HB2,
-                                                      const int *__restrict__ grp,
-                                                      float *__restrict__ X2, float *__restrict__ Z2,
-                                                      float *__restrict__ Z1,
-                                                      float *__restrict__ WS1) {
-  const int P = Pdev[0];
-  const unsigned ld32 = (unsigned)ldr, pc32 = (unsigned)Pcap;
-  for (int qi = blockIdx.x * 256 + threadIdx.x; qi < P; qi += gridDim.x * 256) {
-    const unsigned q = (unsigned)qi;
-    const float s = a.geom[(size_t)q * kGeom + G_S];
-    const int g = grp[q];
-    const int tj = g / a.ntypes, ti = g - tj * a.ntypes;
-    float hb2[kTrN2], hb2d[kTrN2];
-    {
-      unsigned off = q;
+__global__ __launch_bounds__(64 * kTrWaves, 3) void k_tr_pair_rev(
+    TrainPairArgs a, const float4 *__restrict__ delta, const float *__restrict__ Td,
+    const float *__restrict__ Db, int ldD, size_t Pcap, float *__restrict__ X3,
+    float *__restrict__ Z3, float *__restrict__ X2, float *__restrict__ Z2,
+    float *__restrict__ Z1, float *__restrict__ WS1, int *__restrict__ grp) {
+  extern __shared__ float4 smem[];
+  float *w2 = (float *)smem, *w3 = w2 + kTrW2, *w3r = w3 + kTrW3, *w2r = w3r + kTrW3r;
+  stage_forward_weights(a, w2, w3);
+  for (int e = threadIdx.x; e < kTrW3r; e += 64 * kTrWaves) {
+    const int l = e & 63, c = (e >> 6) & 15, t = e >> 10;
+    w3r[e] = a.W3t[(4 * c + (l >> 4)) * kTrN2 + 16 * t + (l & 15)];
+  }
+  for (int e = threadIdx.x; e < kTrW2r; e += 64 * kTrWaves) {
+    // depth 4 c + g: output o = 2 c + g / 2, its weight (g even) or the residual
+    const int l = e & 63, c = e >> 6, q = l >> 4, o = 2 * c + (q >> 1), k = l & 15;
+    w2r[e] = (q & 1) ? (k == o % kTrN1 ? 1.f : 0.f) : a.W2t[o * kTrN1 + k];
+  }
+  __syncthreads();
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4;
+  float *sDb = w2r + kTrW2r + w * kTrRevWave, *sDdb = sDb + 64 * 16;
+  float *sT = sDdb + 64 * 16, *sTd = sT + 4 * 64;
+  float *ta = sDb, *tb_ = ta + kTrTile;  // the tiles' turns through LDS
+  const int ax = a.axis;
+  const unsigned pc32 = (unsigned)Pcap;
+  const floatx4 wsv = *(const floatx4 *)(a.ws + 4 * g);
+  for (int i = w * (int)gridDim.x + blockIdx.x; i < a.nloc; i += kTrWaves * gridDim.x) {
+    const int n = a.nnei[i];
+    const int off = a.pair_off[i];
+    const int ti = a.types[i];
+    const float4 di = delta[i];
+    // --- T-bar, T-dot-bar (lane = m)
 #pragma unroll
-      for (int k = 0; k < kTrN2; ++k) {
-        hb2[k] = HB2[off];
-        hb2d[k] = HB2[off + pc32];
-        off += ld32;
+    for (int c = 0; c < 4; ++c) {
+      sT[c * 64 + lane] = a.T[((size_t)i * 4 + c) * kTrN3 + lane];
+      sTd[c * 64 + lane] = Td[((size_t)i * 4 + c) * kTrN3 + lane];
+    }
+    for (int b = 0; b < ax; ++b) {
+      sDb[lane * 16 + b] = Db[(size_t)i * ldD + (size_t)lane * ax + b];
+      sDdb[lane * 16 + b] = Db[(size_t)(a.nloc + i) * ldD + (size_t)lane * ax + b];
+    }
+    wave_fence();
+    float tb[4] = {0.f, 0.f, 0.f, 0.f}, tdb[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < ax; ++b) {
+      const float db = sDb[lane * 16 + b], ddb = sDdb[lane * 16 + b];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        tb[c] = fmaf(db, sT[c * 64 + b], fmaf(ddb, sTd[c * 64 + b], tb[c]));
+        tdb[c] = fmaf(ddb, sT[c * 64 + b], tdb[c]);
       }
     }
-    float h1[kTrN1], h1d[kTrN1];
-    emb_l1(a, tj, ti, s, h1, h1d);
-    {
-      unsigned off = q;
+    if (lane < ax) {
+#pragma unroll 4
+      for (int mp = 0; mp < kTrN3; ++mp) {
+        const float db = sDb[mp * 16 + lane], ddb = sDdb[mp * 16 + lane];
 #pragma unroll
-      for (int k = 0; k < kTrN1; ++k) {
-        X2[off] = h1[k];
-        X2[off + pc32] = h1d[k];
-        off += ld32;
-      }
-    }
-    const PairTangent pt{s};
-    // second layer (doubling residual) in reverse
-    float hb1[kTrN1], hb1d[kTrN1];
-#pragma unroll
-    for (int k = 0; k < kTrN1; ++k) hb1[k] = hb1d[k] = 0.f;
-#pragma unroll
-    for (int o4 = 0; o4 < kTrN2; o4 += 4) {
-      float zbv[4], zbdv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int o = o4 + u;
-        float z = wc(a.b2, o), zd = 0.f;
-#pragma unroll
-        for (int k = 0; k < kTrN1; ++k) {
-          z = fmaf(wc(a.W2t, o * kTrN1 + k), h1[k], z);
-          zd = fmaf(wc(a.W2t, o * kTrN1 + k), h1d[k], zd);
+        for (int c = 0; c < 4; ++c) {
+          tb[c] = fmaf(db, sT[c * 64 + mp], fmaf(ddb, sTd[c * 64 + mp], tb[c]));
+          tdb[c] = fmaf(ddb, sT[c * 64 + mp], tdb[c]);
         }
-        const float t = tanh_fast(z), g = 1.0f - t * t;
-        const float zbd = g * hb2d[o];
-        const float zb = g * (hb2[o] - 2.0f * t * zd * hb2d[o]);
-#pragma unroll
-        for (int k = 0; k < kTrN1; ++k) {
-          hb1[k] = fmaf(wc(a.W2t, o * kTrN1 + k), zb, hb1[k]);
-          hb1d[k] = fmaf(wc(a.W2t, o * kTrN1 + k), zbd, hb1d[k]);
-        }
-        hb1[o % kTrN1] += hb2[o];
-        hb1d[o % kTrN1] += hb2d[o];
-        zbv[u] = zb;
-        zbdv[u] = zbd;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const unsigned off = (unsigned)(o4 + u) * ld32 + (unsigned)q;
-        Z2[off] = zbv[u];
-        Z2[off + pc32] = zbdv[u];
       }
     }
-    // first layer: h1' = (1 - h1^2) ws
+    wave_fence();
 #pragma unroll
-    for (int o4 = 0; o4 < kTrN1; o4 += 4) {
-      float zbv[4], wsv[4];
+    for (int c = 0; c < 4; ++c) {
+      sT[c * 64 + lane] = tb[c] * a.inv_sel;   // T-bar, T-dot-bar
+      sTd[c * 64 + lane] = tdb[c] * a.inv_sel;
+    }
+    wave_fence();
+    // row operands of G-bar (depths T-dot-bar_c, T-bar_c in turn) and G'-bar
+    float ag[4][2], agd[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int o = o4 + u;
-        const float g = 1.0f - h1[o] * h1[o];
-        const float gbar = wc(a.ws, o) * hb1d[o];
-        const float zb = g * (hb1[o] - 2.0f * h1[o] * gbar);
-        zbv[u] = zb;
-        wsv[u] = fmaf(pt.s, zb, g * hb1d[o]);
+    for (int t = 0; t < 4; ++t) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = 2 * h + (g >> 1);
+        ag[t][h] = ((g & 1) ? sT : sTd)[c * 64 + 16 * t + r];
       }
+      agd[t] = sTd[g * 64 + 16 * t + r];
+    }
+    wave_fence();
+    // --- pairs
+    for (int p0 = 0; p0 < n; p0 += 16) {
+      const bool valid = p0 + r < n;
+      const int pc = valid ? p0 + r : 0;
+      const float4 *gp = (const float4 *)(a.geom + (size_t)(off + pc) * kGeom);
+      const float4 g0 = gp[0], g1 = gp[1];
+      const int j = a.nlist[(size_t)i * a.sel + pc];
+      const int tj = a.types[j];
+      const float4 dj = delta[j];
+      const PairTangent pt = pair_tangent(g0, g1, di, dj);
+      const unsigned q = (unsigned)(off + pc);
+      // this lane's places in the operands (tr_row), from output 4 g on
+      float *x3 = X3 + tr_row(q, kTrN2) + 64 * g, *z3 = Z3 + tr_row(q, kTrN3) + 64 * g;
+      float *x2 = X2 + tr_row(q, kTrN1) + 64 * g, *z2 = Z2 + tr_row(q, kTrN2) + 64 * g;
+      TileL12 x;
+      tile_l12(a, w2, a.table + (size_t)(tj * a.ntypes + ti) * kTrN1, pt.s, lane, g, x);
+      if (valid) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const unsigned off = (unsigned)(o4 + u) * ld32 + (unsigned)q;
-        Z1[off] = zbv[u];
-        WS1[off] = wsv[u];
+        for (int v = 0; v < 4; ++v) {
+          x2[16 * v] = x.h1[v];
+          x2[16 * v + pc32 * kTrN1] = x.h1d[v];
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            x3[16 * (16 * t + v)] = x.h2[t][v];
+            x3[16 * (16 * t + v) + pc32 * kTrN2] = x.h2d[t][v];
+          }
+      }
+      floatx4 z[4], zd[4];
+      tile_l3(a, w3, ta, lane, r, g, x, z, zd);
+      // G-bar, G'-bar of the tile's outputs
+      float bg[2], bgd;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float lo = (g & 1) ? pt.Rt[2 * h] : pt.Rd[2 * h];
+        const float hi = (g & 1) ? pt.Rt[2 * h + 1] : pt.Rd[2 * h + 1];
+        bg[h] = (g & 2) ? hi : lo;
+      }
+      bgd = (g & 2) ? ((g & 1) ? pt.Rt[3] : pt.Rt[2]) : ((g & 1) ? pt.Rt[1] : pt.Rt[0]);
+      const floatx4 zero = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const floatx4 Gb = mfma4(ag[t][1], bg[1], mfma4(ag[t][0], bg[0], zero));
+        const floatx4 Gd = mfma4(agd[t], bgd, zero);
+        floatx4 zb, zbd;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float Gdb = Gd[v] * pt.sdot;
+          const float th = tanh_fast(z[t][v]), gg = 1.0f - th * th;
+          zbd[v] = gg * Gdb;
+          zb[v] = gg * (Gb[v] - 2.0f * th * zd[t][v] * Gdb);
+        }
+        *(floatx4 *)(ta + r * kTrRow + 16 * t + 4 * g) = zb;
+        *(floatx4 *)(tb_ + r * kTrRow + 16 * t + 4 * g) = zbd;
+        if (valid) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            z3[16 * (16 * t + v)] = zb[v];
+            z3[16 * (16 * t + v) + pc32 * kTrN3] = zbd[v];
+          }
+        }
+      }
+      wave_fence();
+      // h2-bar, h2'-bar: W3 z3-bar, then the [h2, h2] residual (G-bar[k] and
+      // G-bar[k + 32] both feed h2[k])
+      floatx4 hb[2], hbd[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) hb[t] = hbd[t] = zero;
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        const float b0 = ta[r * kTrRow + 4 * c + g], b1 = tb_[r * kTrRow + 4 * c + g];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const float wv = w3r[(t * 16 + c) * 64 + lane];
+          hb[t] = mfma4(wv, b0, hb[t]);
+          hbd[t] = mfma4(wv, b1, hbd[t]);
+        }
+      }
+      wave_fence();
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        floatx4 gb = zero, gdb = zero;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          gb = mfma4(ag[t + 2 * hh][0], bg[0], gb);
+          gb = mfma4(ag[t + 2 * hh][1], bg[1], gb);
+          gdb = mfma4(agd[t + 2 * hh], bgd, gdb);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          hb[t][v] += gb[v];
+          hbd[t][v] = fmaf(gdb[v], pt.sdot, hbd[t][v]);
+        }
+      }
+      // second layer in reverse: rows of outputs and their residual gradients
+      // in turn
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        floatx4 zb, zbd;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float th = x.t2[t][v], gg = 1.0f - th * th;
+          zbd[v] = gg * hbd[t][v];
+          zb[v] = gg * (hb[t][v] - 2.0f * th * x.zd2[t][v] * hbd[t][v]);
+        }
+        float *pa = ta + r * kTrRow + 2 * (16 * t + 4 * g);
+        float *pb = tb_ + r * kTrRow + 2 * (16 * t + 4 * g);
+        *(floatx4 *)pa = floatx4{zb[0], hb[t][0], zb[1], hb[t][1]};
+        *(floatx4 *)(pa + 4) = floatx4{zb[2], hb[t][2], zb[3], hb[t][3]};
+        *(floatx4 *)pb = floatx4{zbd[0], hbd[t][0], zbd[1], hbd[t][1]};
+        *(floatx4 *)(pb + 4) = floatx4{zbd[2], hbd[t][2], zbd[3], hbd[t][3]};
+        if (valid) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            z2[16 * (16 * t + v)] = zb[v];
+            z2[16 * (16 * t + v) + pc32 * kTrN2] = zbd[v];
+          }
+        }
+      }
+      wave_fence();
+      floatx4 hb1 = zero, hb1d = zero;
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        const float wv = w2r[c * 64 + lane];
+        hb1 = mfma4(wv, ta[r * kTrRow + 4 * c + g], hb1);
+        hb1d = mfma4(wv, tb_[r * kTrRow + 4 * c + g], hb1d);
+      }
+      wave_fence();
+      // first layer: h1' = (1 - h1^2) ws
+      if (valid) {
+        float *z1 = Z1 + tr_row(q, kTrN1) + 64 * g, *ws1 = WS1 + tr_row(q, kTrN1) + 64 * g;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float gg = 1.0f - x.h1[v] * x.h1[v];
+          const float gbar = wsv[v] * hb1d[v];
+          const float zb = gg * (hb1[v] - 2.0f * x.h1[v] * gbar);
+          z1[16 * v] = zb;
+          ws1[16 * v] = fmaf(pt.s, zb, gg * hb1d[v]);
+        }
+        if (g == 0) grp[q] = tj * a.ntypes + ti;
       }
     }
   }
@@ -662,15 +735,20 @@ __global__ __launch_bounds__(256) void k_wgrad(const float *__restrict__ X1,
   }
 }
 
-// Feature-major variant: Xt [kin][ldr], Zt [nout][ldr] hold one feature per
-// row and the pair rows along it; segment 2 (if seg2 > 0) starts at column
-// seg2.  Lane (c, q) of a 16-row step reads rows 4q..4q+3 of feature c as one
-// float4, which is the k-slice layout of the BF16 product; the FP32 product
+// Variant for the pair operands: Xt of kin features, Zt of nout features, each
+// in blocks of 16 rows, feature by feature inside a block (tr_row); segment 2
+// (if seg2 > 0, a multiple of 16) starts at row seg2.  Lane (c, q) of a 16-row
+// step reads rows 4q..4q+3 of feature c as one float4 (16 features' rows side by
+// side), which is the k-slice layout of the BF16 product; the FP32 product
 // takes the four components as four 16x16x4 steps.
+__device__ __forceinline__ size_t fm_row(size_t row, int nf) {
+  return (row >> 4) * (size_t)(16 * nf) + (row & 15);
+}
+
 template <int KT, int NT, bool BF, bool ONEHOT>
 __global__ __launch_bounds__(256) void k_wgrad_fm(const float *__restrict__ Xt,
-                                                  const float *__restrict__ Zt, size_t ldr,
-                                                  size_t seg2, int kin, int nout,
+                                                  const float *__restrict__ Zt, size_t seg2,
+                                                  int kin, int nout,
                                                   const int *__restrict__ rows_dev, int rows_max,
                                                   int rows_per_block,
                                                   const int32_t *__restrict__ group,
@@ -710,8 +788,9 @@ __global__ __launch_bounds__(256) void k_wgrad_fm(const float *__restrict__ Xt,
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) {
           const int c = k0 + 16 * kt + col;
-          const float *xp = Xt + (size_t)(c < kin ? c : 0) * ldr + base;
-          const floatx4 v0 = *(const floatx4 *)(xp + rq0), v1 = *(const floatx4 *)(xp + rq1a);
+          const float *xp = Xt + 16 * (c < kin ? c : 0);
+          const floatx4 v0 = *(const floatx4 *)(xp + fm_row(base + rq0, kin)),
+                        v1 = *(const floatx4 *)(xp + fm_row(base + rq1a, kin));
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             xv[kt][j] = (rv[j] && c < kin) ? v0[j] : 0.f;
@@ -721,8 +800,9 @@ __global__ __launch_bounds__(256) void k_wgrad_fm(const float *__restrict__ Xt,
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
           const int c = n0 + 16 * nt + col;
-          const float *zp = Zt + (size_t)(c < nout ? c : 0) * ldr + base;
-          const floatx4 v0 = *(const floatx4 *)(zp + rq0), v1 = *(const floatx4 *)(zp + rq1a);
+          const float *zp = Zt + 16 * (c < nout ? c : 0);
+          const floatx4 v0 = *(const floatx4 *)(zp + fm_row(base + rq0, nout)),
+                        v1 = *(const floatx4 *)(zp + fm_row(base + rq1a, nout));
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             zv[nt][j] = (rv[j] && c < nout) ? v0[j] : 0.f;
@@ -760,7 +840,8 @@ __global__ __launch_bounds__(256) void k_wgrad_fm(const float *__restrict__ Xt,
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) {
           const int c = k0 + 16 * kt + col;
-          const floatx4 v = *(const floatx4 *)(Xt + (size_t)(c < kin ? c : 0) * ldr + base + rq);
+          const floatx4 v =
+              *(const floatx4 *)(Xt + fm_row(base + rq, kin) + 16 * (c < kin ? c : 0));
 #pragma unroll
           for (int j = 0; j < 4; ++j) xv[kt][j] = (rv[j] && c < kin) ? v[j] : 0.f;
         }
@@ -768,7 +849,8 @@ __global__ __launch_bounds__(256) void k_wgrad_fm(const float *__restrict__ Xt,
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         const int c = n0 + 16 * nt + col;
-        const floatx4 v = *(const floatx4 *)(Zt + (size_t)(c < nout ? c : 0) * ldr + base + rq);
+        const floatx4 v =
+            *(const floatx4 *)(Zt + fm_row(base + rq, nout) + 16 * (c < nout ? c : 0));
 #pragma unroll
         for (int j = 0; j < 4; ++j) zv[nt][j] = (rv[j] && c < nout) ? v[j] : 0.f;
       }
@@ -896,7 +978,7 @@ void wgrad_t(const float *X1, const float *X2, int ldx, const float *Z1, const f
 }
 
 template <int KT, int NT, bool ONEHOT>
-void wgrad_fm_t(const float *Xt, const float *Zt, size_t ldr, size_t seg2, int kin, int nout,
+void wgrad_fm_t(const float *Xt, const float *Zt, size_t seg2, int kin, int nout,
                 const int *rows_dev, int rows_max, int bf16, const int32_t *group, float *part,
                 size_t part_cap, double *acc, hipStream_t s) {
   const int kin_pad = (kin + 15) / 16 * 16, nout_pad = (nout + 15) / 16 * 16;
@@ -909,10 +991,10 @@ void wgrad_fm_t(const float *Xt, const float *Zt, size_t ldr, size_t seg2, int k
   const int gx = std::max(1, (rows_max + rpb - 1) / rpb);
   const dim3 grid(gx, gy, gz);
   if (bf16 && !ONEHOT)
-    hipLaunchKernelGGL((k_wgrad_fm<KT, NT, true, false>), grid, dim3(256), 0, s, Xt, Zt, ldr,
+    hipLaunchKernelGGL((k_wgrad_fm<KT, NT, true, false>), grid, dim3(256), 0, s, Xt, Zt,
                        seg2, kin, nout, rows_dev, rows_max, rpb, group, part, kin_pad, nout_pad);
   else
-    hipLaunchKernelGGL((k_wgrad_fm<KT, NT, false, ONEHOT>), grid, dim3(256), 0, s, Xt, Zt, ldr,
+    hipLaunchKernelGGL((k_wgrad_fm<KT, NT, false, ONEHOT>), grid, dim3(256), 0, s, Xt, Zt,
                        seg2, kin, nout, rows_dev, rows_max, rpb, group, part, kin_pad, nout_pad);
   hipLaunchKernelGGL(k_reduce_parts, dim3(nblk((size_t)kin * nout, 16)), dim3(256), 0, s, part,
                      gx, kin_pad, nout_pad, kin, nout, acc);
@@ -933,11 +1015,35 @@ void launch_tr_energy_seed(const double *E, const double *Elab, double ca, doubl
   hipLaunchKernelGGL(k_tr_energy_seed, dim3(1), dim3(64), 0, s, E, Elab, ca, cl, a, le);
 }
 
-void launch_tr_tangent(const TrainPairArgs &a, const float4 *delta, float *Td, float *Xd, int ldD,
-                       hipStream_t s) {
-  if (a.nloc <= 0) return;
-  hipLaunchKernelGGL(k_tr_tangent, dim3(nblk(a.nloc, kWaves)), dim3(256), 0, s, a, delta, Td, Xd,
-                     ldD);
+namespace {
+
+// Persistent grid of a per-centre kernel of kTrWaves wavefronts: one workgroup
+// per CU (by LDS and registers), its dynamic LDS limit raised at the first
+// launch on a device.
+template <class K, class... A>
+hipError_t launch_per_centre(K kernel, size_t lds, int (&ready)[64], int nloc, hipStream_t s,
+                             A... args) {
+  int dev = 0, cus = 256;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess)
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess && (dev < 0 || dev >= 64 || !ready[dev])) {
+    e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds);
+    if (e == hipSuccess && dev >= 0 && dev < 64) ready[dev] = 1;
+  }
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, dim3(std::min(nloc, cus)), dim3(64 * kTrWaves), lds, s, args...);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_tr_tangent(const TrainPairArgs &a, const float4 *delta, float *Td, float *Xd,
+                             int ldD, hipStream_t s) {
+  if (a.nloc <= 0) return hipSuccess;
+  static int ready[64];
+  return launch_per_centre(k_tr_tangent, kTrTanLds, ready, a.nloc, s, a, delta, Td, Xd, ldD);
 }
 
 void launch_tr_fit_top(const float *t2, const float *y2, const float *yd1, const float *zd2,
@@ -957,19 +1063,14 @@ void launch_tr_fit_l0(const float *t1, const float *zd1, const float *yb1, const
                      nloc, H, ld, zb1);
 }
 
-void launch_tr_pair_rev(const TrainPairArgs &a, const float4 *delta, const float *Td,
-                        const float *Db, int ldD, size_t Pcap, size_t ldr, float *X3, float *Z3,
-                        float *X2, float *Z2, float *Z1, float *WS1, float *HB2, int *grp,
-                        hipStream_t s) {
-  if (a.nloc <= 0) return;
-  hipLaunchKernelGGL(k_tr_pair_rev, dim3(nblk(a.nloc, kWaves)), dim3(256), 0, s, a, delta, Td, Db,
-                     ldD, Pcap, ldr, X3, Z3, HB2, grp);
-  int dev = 0, cus = 256;
-  (void)hipGetDevice(&dev);
-  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  const unsigned blocks = std::min<unsigned>(nblk((size_t)a.nloc * a.sel, 256), 8u * cus);
-  hipLaunchKernelGGL(k_tr_pair_rev2, dim3(blocks), dim3(256), 0, s, a, a.pair_off + a.nloc, Pcap,
-                     ldr, HB2, grp, X2, Z2, Z1, WS1);
+hipError_t launch_tr_pair_rev(const TrainPairArgs &a, const float4 *delta, const float *Td,
+                              const float *Db, int ldD, size_t Pcap, float *X3,
+                              float *Z3, float *X2, float *Z2, float *Z1, float *WS1, int *grp,
+                              hipStream_t s) {
+  if (a.nloc <= 0) return hipSuccess;
+  static int ready[64];
+  return launch_per_centre(k_tr_pair_rev, kTrRevLds, ready, a.nloc, s, a, delta, Td, Db, ldD, Pcap,
+                           X3, Z3, X2, Z2, Z1, WS1, grp);
 }
 
 void tr_wgrad(const float *X1, const float *X2, int ldx, const float *Z1, const float *Z2, int ldz,
@@ -987,27 +1088,27 @@ void tr_wgrad(const float *X1, const float *X2, int ldx, const float *Z1, const 
                          part, part_cap, acc, s);
 }
 
-void tr_wgrad_fm(const float *Xt, const float *Zt, size_t ldr, size_t seg2, int kin, int nout,
+void tr_wgrad_fm(const float *Xt, const float *Zt, size_t seg2, int kin, int nout,
                  const int *rows_dev, int rows_max, int bf16, float *part, size_t part_cap,
                  double *acc, hipStream_t s) {
   if (rows_max <= 0) return;
   if (kin <= 16 && nout <= 32)
-    wgrad_fm_t<1, 2, false>(Xt, Zt, ldr, seg2, kin, nout, rows_dev, rows_max, bf16, nullptr,
+    wgrad_fm_t<1, 2, false>(Xt, Zt, seg2, kin, nout, rows_dev, rows_max, bf16, nullptr,
                             part, part_cap, acc, s);
   else
-    wgrad_fm_t<2, 4, false>(Xt, Zt, ldr, seg2, kin, nout, rows_dev, rows_max, bf16, nullptr,
+    wgrad_fm_t<2, 4, false>(Xt, Zt, seg2, kin, nout, rows_dev, rows_max, bf16, nullptr,
                             part, part_cap, acc, s);
 }
 
-void tr_colsum_fm(const float *Zt, size_t ldr, int ncol, const int *rows_dev, int rows_max,
+void tr_colsum_fm(const float *Zt, int ncol, const int *rows_dev, int rows_max,
                   const int32_t *group, int ngroups, float *part, size_t part_cap, double *acc,
                   hipStream_t s) {
   if (rows_max <= 0) return;
   if (ngroups <= 16)
-    wgrad_fm_t<1, 4, true>(nullptr, Zt, ldr, 0, ngroups, ncol, rows_dev, rows_max, 0, group, part,
+    wgrad_fm_t<1, 4, true>(nullptr, Zt, 0, ngroups, ncol, rows_dev, rows_max, 0, group, part,
                            part_cap, acc, s);
   else
-    wgrad_fm_t<4, 4, true>(nullptr, Zt, ldr, 0, ngroups, ncol, rows_dev, rows_max, 0, group, part,
+    wgrad_fm_t<4, 4, true>(nullptr, Zt, 0, ngroups, ncol, rows_dev, rows_max, 0, group, part,
                            part_cap, acc, s);
 }
 

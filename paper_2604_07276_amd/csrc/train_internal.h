@@ -42,8 +42,8 @@ int tr_seed_blocks(int n);
 void launch_tr_energy_seed(const double *E, const double *Elab, double ca, double cl, float *a,
                            double *le, hipStream_t s);
 // Tangent pass: T-dot [nloc][4][64] and D-dot rows [nloc][ldD].
-void launch_tr_tangent(const TrainPairArgs &a, const float4 *delta, float *Td, float *Xd, int ldD,
-                       hipStream_t s);
+hipError_t launch_tr_tangent(const TrainPairArgs &a, const float4 *delta, float *Td, float *Xd,
+                             int ldD, hipStream_t s);
 // Fitting tangent/reverse elementwise steps (two fitting layers of width H,
 // identity residual on the second):
 //   top: from t2, y2, y1-dot, z2-dot -> [z2-bar; z2-dot-bar] rows and a y2 - y2-dot rows;
@@ -54,24 +54,22 @@ void launch_tr_fit_top(const float *t2, const float *y2, const float *yd1, const
 void launch_tr_fit_l0(const float *t1, const float *zd1, const float *yb1, const float *w_out,
                       const float *a, int nloc, int H, int ld, float *zb1, hipStream_t s);
 // Reverse sweep of the descriptor and the embedding net per pair; writes the
-// weight-gradient operands feature-major (feature f of pair row r at
-// f * ldr + r; primal rows [0, P), tangent rows [Pcap, Pcap + P)):
-//   X3 [32][ldr] = h2 | h2', Z3 [64][ldr] = z3-bar | z3'-bar,
-//   X2 [16][ldr] = h1 | h1', Z2 [32][ldr] = z2-bar | z2'-bar,
-//   Z1 [16][ldr] = z1-bar, WS1 [16][ldr] = ws-bar per pair (primal rows only),
-//   grp [P] = t_j * ntypes + t_i.
-// Pcap and ldr are multiples of 16.
-// HB2 [64][ldr] is scratch between the two passes (h2-bar | h2'-bar).
-void launch_tr_pair_rev(const TrainPairArgs &a, const float4 *delta, const float *Td,
-                        const float *Db, int ldD, size_t Pcap, size_t ldr, float *X3, float *Z3,
-                        float *X2, float *Z2, float *Z1, float *WS1, float *HB2, int *grp,
-                        hipStream_t s);
-// As tr_wgrad and tr_colsum for feature-major operands (Xt [kin][ldr], Zt
-// [nout][ldr], group [rows]); the second segment starts at row seg2 (0: none).
-void tr_wgrad_fm(const float *Xt, const float *Zt, size_t ldr, size_t seg2, int kin, int nout,
+// weight-gradient operands, F features each, in blocks of 16 pair rows, feature
+// by feature inside a block (feature f of row r at (r / 16) 16 F + 16 f + r % 16;
+// primal rows [0, P), tangent rows [Pcap, Pcap + P), Pcap a multiple of 16):
+//   X3 (F = 32) = h2 | h2', Z3 (64) = z3-bar | z3'-bar, X2 (16) = h1 | h1',
+//   Z2 (32) = z2-bar | z2'-bar, Z1 (16) = z1-bar and WS1 (16) = ws-bar per pair
+//   (primal rows only); grp [P] = t_j * ntypes + t_i.
+hipError_t launch_tr_pair_rev(const TrainPairArgs &a, const float4 *delta, const float *Td,
+                              const float *Db, int ldD, size_t Pcap, float *X3, float *Z3,
+                              float *X2, float *Z2, float *Z1, float *WS1, int *grp,
+                              hipStream_t s);
+// As tr_wgrad and tr_colsum for operands in that layout (Xt of kin features, Zt
+// of nout or ncol); the second segment starts at row seg2 (0: none).
+void tr_wgrad_fm(const float *Xt, const float *Zt, size_t seg2, int kin, int nout,
                  const int *rows_dev, int rows_max, int bf16, float *part, size_t part_cap,
                  double *acc, hipStream_t s);
-void tr_colsum_fm(const float *Zt, size_t ldr, int ncol, const int *rows_dev, int rows_max,
+void tr_colsum_fm(const float *Zt, int ncol, const int *rows_dev, int rows_max,
                   const int32_t *group, int ngroups, float *part, size_t part_cap, double *acc,
                   hipStream_t s);
 // acc[kin][nout] += sum_r X1[r]^T Z1[r] + X2[r]^T Z2[r] over r < rows (rows
