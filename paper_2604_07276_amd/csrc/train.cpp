@@ -56,7 +56,6 @@ struct dp_trainer {
         *WS1 = nullptr;
   int *grp = nullptr;
   float *part = nullptr;
-  size_t part_cap = 0;
 
   ~dp_trainer() {
     if (arena) (void)hipFree(arena);
@@ -114,13 +113,41 @@ std::vector<char> make_image(const dp_trainer *t) {
   return img;
 }
 
+// The weight-gradient products and sums of one frame of N atoms (before the first
+// frame, when the model has no workspace yet, for their sizes only).
+TrWgrads weight_gradients(const dp_trainer *t, int N) {
+  const dp_model *m = t->m;
+  const auto &w = m->w;
+  const int T = m->ntypes, H0 = m->fit[0], H1 = m->fit[1];
+  const int ldD = m->ldD, ldf0 = m->ldf[0], ldf1 = m->ldf[1];
+  const size_t Pst = ((size_t)N * m->sel + 15) / 16 * 16;
+  const int *Pdev = w.pair_off + N;
+  const int Pmax = (int)Pst;
+  TrWgrads b;
+  b.product(w.dmat, t->Xd, ldD, t->Zb1, t->Zb1 + (size_t)N * ldf0, ldf0, m->M * m->axis, H0,
+            nullptr, N, false, t->acc + t->o_W0d);
+  b.product(w.z.empty() ? nullptr : w.z[0], t->Yd1, ldf0, t->Zb2, t->Zb2 + (size_t)N * ldf1,
+            ldf1, H0, H1, nullptr, N, false, t->acc + t->o_W1f);
+  b.product(t->X3, t->X3 + Pst * kTrN2, kTrN2, t->Z3, t->Z3 + Pst * kTrN3, kTrN3, kTrN2, kTrN3,
+            Pdev, Pmax, true, t->acc + t->o_W3);
+  b.product(t->X2, t->X2 + Pst * kTrN1, kTrN1, t->Z2, t->Z2 + Pst * kTrN2, kTrN2, kTrN1, kTrN2,
+            Pdev, Pmax, true, t->acc + t->o_W2);
+  b.colsum(t->Z3, kTrN3, kTrN3, Pdev, Pmax, true, nullptr, 1, t->acc + t->o_b3);
+  b.colsum(t->Z2, kTrN2, kTrN2, Pdev, Pmax, true, nullptr, 1, t->acc + t->o_b2);
+  b.colsum(t->Z1, kTrN1, kTrN1, Pdev, Pmax, true, t->grp, T * T, t->acc + t->o_tab);
+  b.colsum(t->WS1, kTrN1, kTrN1, Pdev, Pmax, true, nullptr, 1, t->acc + t->o_ws);
+  b.colsum(t->Zb2, ldf1, H1, nullptr, N, false, nullptr, 1, t->acc + t->o_b1f);
+  b.colsum(t->Zb1, ldf0, H0, nullptr, N, false, w.types_safe, T, t->acc + t->o_fb0);
+  b.colsum(t->WoR, ldf1, H1, nullptr, N, false, nullptr, 1, t->acc + t->o_wout);
+  return b;
+}
+
 int ensure_buffers(dp_trainer *t, int n, int nframes) {
   if (n <= t->cap_n && nframes <= t->cap_frames) return DP_OK;
   const int cn = std::max(n, t->cap_n), cf = std::max(nframes, t->cap_frames);
   dp_model *m = t->m;
   const size_t P = ((size_t)cn * m->sel + 15) / 16 * 16;
-  // pair operands: primal rows [0, P), tangent rows [P, 2 P), and one 16-row step of
-  // slack read (masked) past the last row
+  // pair operands: primal rows [0, P), tangent rows [P, 2 P)
   const size_t ldr = 2 * P + 16;
   const int ldD = m->ldD, ldf0 = m->ldf[0], ldf1 = m->ldf[1];
   const int nsq = tr_seed_blocks(cn);
@@ -148,8 +175,7 @@ int ensure_buffers(dp_trainer *t, int n, int nframes) {
                oGrp = take(sizeof(int) * (P + 16));
   if (ldr * kTrN3 >= ((size_t)1 << 32))
     return fail(DP_ERR_ARG, "natoms * sel = %zu pair rows exceed the trainer's limit", P);
-  const size_t part_cap = (size_t)1 << 22;
-  const size_t oPart = take(sizeof(float) * part_cap);
+  const size_t oPart = take(sizeof(float) * weight_gradients(t, cn).room());
   if (t->arena) {
     HIP_TRY(hipDeviceSynchronize());
     HIP_TRY(hipFree(t->arena));
@@ -183,7 +209,6 @@ int ensure_buffers(dp_trainer *t, int n, int nframes) {
   t->WS1 = (float *)(b + oWS1);
   t->grp = (int *)(b + oGrp);
   t->part = (float *)(b + oPart);
-  t->part_cap = part_cap;
   t->cap_n = cn;
   t->cap_frames = cf;
   return DP_OK;
@@ -259,30 +284,9 @@ int batch_gradient(dp_trainer *t, const double *d_frames, const int32_t *d_types
     // descriptor and embedding net
     HIP_TRY(launch_tr_pair_rev(pa, t->delta, t->Td, t->Db, ldD, Pst, t->X3, t->Z3, t->X2,
                                t->Z2, t->Z1, t->WS1, t->grp, s));
-    const int *Pdev = w.pair_off + N;
-    const int Pmax = (int)Pst;
-    tr_wgrad_fm(t->X3, t->Z3, Pst, kTrN2, kTrN3, Pdev, Pmax, bf, t->part, t->part_cap,
-                t->acc + t->o_W3, s);
-    tr_wgrad_fm(t->X2, t->Z2, Pst, kTrN1, kTrN2, Pdev, Pmax, bf, t->part, t->part_cap,
-                t->acc + t->o_W2, s);
-    tr_colsum_fm(t->Z3, kTrN3, Pdev, Pmax, nullptr, 1, t->part, t->part_cap,
-                 t->acc + t->o_b3, s);
-    tr_colsum_fm(t->Z2, kTrN2, Pdev, Pmax, nullptr, 1, t->part, t->part_cap,
-                 t->acc + t->o_b2, s);
-    tr_colsum_fm(t->Z1, kTrN1, Pdev, Pmax, t->grp, T * T, t->part, t->part_cap,
-                 t->acc + t->o_tab, s);
-    tr_colsum_fm(t->WS1, kTrN1, Pdev, Pmax, nullptr, 1, t->part, t->part_cap,
-                 t->acc + t->o_ws, s);
-    tr_wgrad(w.z[0], t->Yd1, ldf0, t->Zb2, t->Zb2 + (size_t)N * ldf1, ldf1, H0, H1, nullptr, N,
-             bf, t->part, t->part_cap, t->acc + t->o_W1f, s);
-    tr_colsum(t->Zb2, ldf1, H1, nullptr, N, nullptr, 1, t->part, t->part_cap, t->acc + t->o_b1f,
-              s);
-    tr_wgrad(w.dmat, t->Xd, ldD, t->Zb1, t->Zb1 + (size_t)N * ldf0, ldf0, m->M * m->axis, H0,
-             nullptr, N, bf, t->part, t->part_cap, t->acc + t->o_W0d, s);
-    tr_colsum(t->Zb1, ldf0, H0, nullptr, N, w.types_safe, T, t->part, t->part_cap,
-              t->acc + t->o_fb0, s);
-    tr_colsum(t->WoR, ldf1, H1, nullptr, N, nullptr, 1, t->part, t->part_cap, t->acc + t->o_wout,
-              s);
+    TrWgrads wg = weight_gradients(t, N);
+    wg.plan();
+    HIP_TRY(launch_tr_wgrads(wg, bf, t->part, s));
     HIP_TRY(hipGetLastError());
   }
   // results to the host

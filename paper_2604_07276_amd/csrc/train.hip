@@ -113,9 +113,11 @@ __device__ __forceinline__ PairTangent pair_tangent(const float4 g0, const float
 //
 // One lane per pair with scalar weights left a third of the lanes idle (84
 // neighbours in two chunks of 64) and, at 256 registers and more, one wavefront
-// per SIMD.  Per frame at 15,668 atoms: tangents 753 -> 251 us, adjoints
-// 1304 + 325 (a second kernel for the first two layers) -> 1058 us; at 192 atoms
-// 58 -> 26 and 85 + 18 -> 43 us.
+// per SIMD.  Per frame at 15,668 atoms: tangents 753 -> 248 us, adjoints
+// 1304 + 325 (a second kernel for the first two layers) -> 616 us; at 192 atoms
+// 58 -> 26 and 85 + 18 -> 40 us.  The adjoints write 1.7 GB of weight-gradient
+// operands (330 us at the rate of a large copy), one row per pair: with one row
+// per feature (320 streams, 64 bytes at a time) they took 1372 us.
 
 constexpr int kTrWaves = 12;             // wavefronts of a workgroup, three per SIMD
 constexpr int kTrRow = 68;               // LDS row of 64 values
@@ -366,15 +368,6 @@ __global__ void k_tr_fit_l0(const float *__restrict__ t1, const float *__restric
 
 // ------------------------------------------------------------- pair reverse
 
-// Element of feature 0 of pair row q in a weight-gradient operand of nf
-// features: blocks of 16 rows, feature by feature inside a block.  A tile's
-// stores then fall into one or two blocks of contiguous memory; one row per
-// feature over all pairs (320 streams a tile, 64 bytes at a time) bound the
-// writer: 1372 us a frame at 15,668 atoms, this order 1058 us.
-__device__ __forceinline__ unsigned tr_row(unsigned q, int nf) {
-  return (q >> 4) * (unsigned)(16 * nf) + (q & 15u);
-}
-
 // One wavefront per centre.  Lanes over m form T-bar and T-dot-bar from D-bar
 // and D-dot-bar (reverse of D = T^T T<, D-dot = T-dot^T T< + T^T T-dot<); per
 // tile of 16 pairs follow G-bar = (1/sel)(R~ T-bar + R~-dot T-dot-bar) and
@@ -413,7 +406,6 @@ __global__ __launch_bounds__(64 * kTrWaves, 3) void k_tr_pair_rev(
   float *sT = sDdb + 64 * 16, *sTd = sT + 4 * 64;
   float *ta = sDb, *tb_ = ta + kTrTile;  // the tiles' turns through LDS
   const int ax = a.axis;
-  const unsigned pc32 = (unsigned)Pcap;
   const floatx4 wsv = *(const floatx4 *)(a.ws + 4 * g);
   for (int i = w * (int)gridDim.x + blockIdx.x; i < a.nloc; i += kTrWaves * gridDim.x) {
     const int n = a.nnei[i];
@@ -480,25 +472,19 @@ __global__ __launch_bounds__(64 * kTrWaves, 3) void k_tr_pair_rev(
       const int tj = a.types[j];
       const float4 dj = delta[j];
       const PairTangent pt = pair_tangent(g0, g1, di, dj);
-      const unsigned q = (unsigned)(off + pc);
-      // this lane's places in the operands (tr_row), from output 4 g on
-      float *x3 = X3 + tr_row(q, kTrN2) + 64 * g, *z3 = Z3 + tr_row(q, kTrN3) + 64 * g;
-      float *x2 = X2 + tr_row(q, kTrN1) + 64 * g, *z2 = Z2 + tr_row(q, kTrN2) + 64 * g;
+      const size_t q = (size_t)(off + p0);  // the tile's first operand row
+      const int row1 = r * kTrN1 + 4 * g, row2 = r * kTrN2 + 4 * g, row3 = r * kTrN3 + 4 * g;
       TileL12 x;
       tile_l12(a, w2, a.table + (size_t)(tj * a.ntypes + ti) * kTrN1, pt.s, lane, g, x);
       if (valid) {
+float *x2 = X2 + q * kTrN1, *x3 = X3 + q * kTrN2;
+        *(floatx4 *)(x2 + row1) = x.h1;
+        *(floatx4 *)(x2 + Pcap * kTrN1 + row1) = x.h1d;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          x2[16 * v] = x.h1[v];
-          x2[16 * v + pc32 * kTrN1] = x.h1d[v];
+        for (int t = 0; t < 2; ++t) {
+          *(floatx4 *)(x3 + row2 + 16 * t) = x.h2[t];
+          *(floatx4 *)(x3 + Pcap * kTrN2 + row2 + 16 * t) = x.h2d[t];
         }
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            x3[16 * (16 * t + v)] = x.h2[t][v];
-            x3[16 * (16 * t + v) + pc32 * kTrN2] = x.h2d[t][v];
-          }
       }
       floatx4 z[4], zd[4];
       tile_l3(a, w3, ta, lane, r, g, x, z, zd);
@@ -527,11 +513,9 @@ __global__ __launch_bounds__(64 * kTrWaves, 3) void k_tr_pair_rev(
         *(floatx4 *)(ta + r * kTrRow + 16 * t + 4 * g) = zb;
         *(floatx4 *)(tb_ + r * kTrRow + 16 * t + 4 * g) = zbd;
         if (valid) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            z3[16 * (16 * t + v)] = zb[v];
-            z3[16 * (16 * t + v) + pc32 * kTrN3] = zbd[v];
-          }
+float *z3 = Z3 + q * kTrN3 + 16 * t;
+          *(floatx4 *)(z3 + row3) = zb;
+          *(floatx4 *)(z3 + Pcap * kTrN3 + row3) = zbd;
         }
       }
       wave_fence();
@@ -584,11 +568,9 @@ __global__ __launch_bounds__(64 * kTrWaves, 3) void k_tr_pair_rev(
         *(floatx4 *)pb = floatx4{zbd[0], hbd[t][0], zbd[1], hbd[t][1]};
         *(floatx4 *)(pb + 4) = floatx4{zbd[2], hbd[t][2], zbd[3], hbd[t][3]};
         if (valid) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            z2[16 * (16 * t + v)] = zb[v];
-            z2[16 * (16 * t + v) + pc32 * kTrN2] = zbd[v];
-          }
+float *z2 = Z2 + q * kTrN2 + 16 * t;
+          *(floatx4 *)(z2 + row2) = zb;
+          *(floatx4 *)(z2 + Pcap * kTrN2 + row2) = zbd;
         }
       }
       wave_fence();
@@ -602,16 +584,17 @@ __global__ __launch_bounds__(64 * kTrWaves, 3) void k_tr_pair_rev(
       wave_fence();
       // first layer: h1' = (1 - h1^2) ws
       if (valid) {
-        float *z1 = Z1 + tr_row(q, kTrN1) + 64 * g, *ws1 = WS1 + tr_row(q, kTrN1) + 64 * g;
+        floatx4 z1, ws1;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const float gg = 1.0f - x.h1[v] * x.h1[v];
           const float gbar = wsv[v] * hb1d[v];
-          const float zb = gg * (hb1[v] - 2.0f * x.h1[v] * gbar);
-          z1[16 * v] = zb;
-          ws1[16 * v] = fmaf(pt.s, zb, gg * hb1d[v]);
+          z1[v] = gg * (hb1[v] - 2.0f * x.h1[v] * gbar);
+          ws1[v] = fmaf(pt.s, z1[v], gg * hb1d[v]);
         }
-        if (g == 0) grp[q] = tj * a.ntypes + ti;
+        *(floatx4 *)(Z1 + q * kTrN1 + row1) = z1;
+        *(floatx4 *)(WS1 + q * kTrN1 + row1) = ws1;
+        if (g == 0) grp[q + r] = tj * a.ntypes + ti;
       }
     }
   }
@@ -619,289 +602,213 @@ __global__ __launch_bounds__(64 * kTrWaves, 3) void k_tr_pair_rev(
 
 // ------------------------------------------------------- weight gradients
 
-// part[blk][kin_pad][nout_pad] = sum over the block's rows of X^T Z for both
-// segments.  Block = 4 waves over one 16KT x 16NT output tile group; each
-// wave takes every 4th group of rows, the four waves are summed in LDS.
+// acc[k][n] += sum over rows of X[r][k] Z[r][n], for all the products of a
+// frame in one launch: blocks of rows of every product first, their partials
+// summed in FP64 by a second.  A product's own launch left the chip idle: a
+// dozen products of 4 to 45 us each at 192 atoms, and the two of the fitting net
+// (240 x 240 and smaller, 16 blocks of rows) waited for one 4-byte load per value
+// in turn, 266 us each at 15,668 atoms.  All products and sums of a frame: 390 ->
+// 25 us at 192 atoms (FP32), 1430 -> 460 us at 15,668 (BF16), where 2.2 GB of
+// operands are read (440 us at the rate of a large copy).
+//
+// A workgroup takes one block of rows and one 16 KT x 16 NT tile of outputs; its
+// four wavefronts share the rows, and their sums are added in LDS.  Lane (col,
+// quad) holds the outputs KT col .. KT col + KT - 1 (NT col .. for Z), so a row
+// of an operand tile is one contiguous load over 16 lanes; all loads of a step
+// are issued before its products (FP32: those of the next step).
+//
+// One step is 64 rows of the workgroup on FP32 operands: four matrix-core steps
+// j of the four rows of a wavefront's quads, 4 w + 16 j + quad, or for the pair
+// operands (pair_rows) 16 w + 4 quad + j.  On BF16 operands it is 128 rows, 32 a
+// wavefront, lane slots u < 4 rows 4 quad + u and slots 4 + u rows
+// 16 + 4 quad + u on both sides.  Rows past the block's last one count as zero.
+//
 // ONEHOT: the X operand is not read but generated, X[r][k] = (group[r] == k)
-// (group == nullptr: X[r][k] = (k == 0)), so the product sums Z by group.
+// (group == nullptr: X[r][k] = (k == 0)), so the product sums Z by group; always
+// on FP32 operands.
+constexpr int kWgTile = 257;  // a 16 x 16 tile of the shared sums, off the bank period
+constexpr int kWgRed = 4 * 8 * kWgTile;
+
+template <int N> struct FloatVec { typedef float __attribute__((ext_vector_type(N))) type; };
+template <> struct FloatVec<1> { typedef float type; };
+
+template <int N>
+__device__ __forceinline__ void load_cols(const float *p, float (&v)[N]) {
+  const typename FloatVec<N>::type x = *(const typename FloatVec<N>::type *)p;
+  if constexpr (N == 1) {
+    v[0] = x;
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = x[i];
+  }
+}
+
 template <int KT, int NT, bool BF, bool ONEHOT>
-__global__ __launch_bounds__(256) void k_wgrad(const float *__restrict__ X1,
-                                               const float *__restrict__ X2, int ldx,
-                                               const float *__restrict__ Z1,
-                                               const float *__restrict__ Z2, int ldz, int kin,
-                                               int nout, const int *__restrict__ rows_dev,
-                                               int rows_max, int rows_per_block,
-                                               const int32_t *__restrict__ group,
-                                               float *__restrict__ part, int kin_pad,
-                                               int nout_pad) {
-  __shared__ float red[4][KT * NT * 256];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int rows = rows_dev ? min(rows_dev[0], rows_max) : rows_max;
-  const int r0 = blockIdx.x * rows_per_block;
-  const int r1 = min(rows, r0 + rows_per_block);
-  const int k0 = blockIdx.y * 16 * KT, n0 = blockIdx.z * 16 * NT;
+__device__ __forceinline__ void wgrad_tile(const TrWgradJob &J, int bx, int by, int bz,
+                                           float *part, float *red) {
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int rows = J.rows_dev ? min(J.rows_dev[0], J.rows_max) : J.rows_max;
+  const int r0 = bx * J.rpb, r1 = min(rows, r0 + J.rpb);
+  const int k0 = by * 16 * KT, n0 = bz * 16 * NT;
+  const int col = lane & 15, quad = lane >> 4;
+  const int kc = k0 + KT * col, nc = n0 + NT * col;  // this lane's first outputs
+  const int xo = kc < J.kin ? kc : 0, zo = nc < J.nout ? nc : 0;
   floatx4 acc[KT][NT];
 #pragma unroll
   for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[kt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int col = lane & 15, quad = lane >> 4;
-  constexpr int RG = BF ? 32 : 4;  // rows per matrix-core step
-  const int nseg = (ONEHOT || X2 == nullptr) ? 1 : 2;
+  const int nseg = (ONEHOT || J.X2 == nullptr) ? 1 : 2;
   for (int seg = 0; seg < nseg; ++seg) {
-    const float *X = seg ? X2 : X1;
-    const float *Z = seg ? Z2 : Z1;
-    for (int rg = r0 + w * RG; rg < r1; rg += 4 * RG) {
-      if constexpr (!BF) {
-        const int r = rg + quad;
-        const bool rv = r < r1;
-        const size_t rr = (size_t)(rv ? r : r0);
-        float xv[KT], zv[NT];
-        if constexpr (ONEHOT) {
-          const int gr = group ? group[rr] : 0;
-#pragma unroll
-          for (int kt = 0; kt < KT; ++kt) xv[kt] = (rv && gr == k0 + 16 * kt + col) ? 1.f : 0.f;
-        } else {
-#pragma unroll
-          for (int kt = 0; kt < KT; ++kt) {
-            const int c = k0 + 16 * kt + col;
-            const float v = X[rr * ldx + (c < kin ? c : 0)];
-            xv[kt] = (rv && c < kin) ? v : 0.f;
-          }
-        }
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const int c = n0 + 16 * nt + col;
-          const float v = Z[rr * ldz + (c < nout ? c : 0)];
-          zv[nt] = (rv && c < nout) ? v : 0.f;
-        }
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            acc[kt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[kt], zv[nt], acc[kt][nt], 0, 0, 0);
-      } else {
-        // 32 rows per 16x16x32 step: lane slots u < 4 hold rows rg + 4q + u,
-        // slots 4 + u rows rg + 16 + 4q + u (the same rows on both operands)
-        static_assert(!ONEHOT, "group sums use FP32 operands");
-        floatx8 xv[KT], zv[NT];
+    const float *X = (seg ? J.X2 : J.X1) + xo;
+    const float *Z = (seg ? J.Z2 : J.Z1) + zo;
+    if constexpr (BF) {
+      static_assert(!ONEHOT, "group sums use FP32 operands");
+      for (int rg = r0 + 32 * w; rg < r1; rg += 128) {
+        float xv[8][KT], zv[8][NT];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const int r = rg + 16 * (u >> 2) + 4 * quad + (u & 3);
-          const bool rv = r < r1;
-          const size_t rr = (size_t)(rv ? r : r0);
-#pragma unroll
-          for (int kt = 0; kt < KT; ++kt) {
-            const int c = k0 + 16 * kt + col;
-            const float v = X[rr * ldx + (c < kin ? c : 0)];
-            xv[kt][u] = (rv && c < kin) ? v : 0.f;
-          }
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const int c = n0 + 16 * nt + col;
-            const float v = Z[rr * ldz + (c < nout ? c : 0)];
-            zv[nt][u] = (rv && c < nout) ? v : 0.f;
-          }
+          const size_t r = (size_t)min(rg + 16 * (u >> 2) + 4 * quad + (u & 3), r1 - 1);
+          load_cols<KT>(X + r * J.ldx, xv[u]);
+          load_cols<NT>(Z + r * J.ldz, zv[u]);
         }
         bf16x8 xb[KT], zb[NT];
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) xb[kt] = __builtin_convertvector(xv[kt], bf16x8);
+        for (int kt = 0; kt < KT; ++kt) {
+          floatx8 f;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) zb[nt] = __builtin_convertvector(zv[nt], bf16x8);
+          for (int u = 0; u < 8; ++u)
+            f[u] = (rg + 16 * (u >> 2) + 4 * quad + (u & 3) < r1 && kc + kt < J.kin) ? xv[u][kt]
+                                                                                    : 0.f;
+          xb[kt] = __builtin_convertvector(f, bf16x8);
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          floatx8 f;
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            f[u] = (rg + 16 * (u >> 2) + 4 * quad + (u & 3) < r1 && nc + nt < J.nout) ? zv[u][nt]
+                                                                                     : 0.f;
+          zb[nt] = __builtin_convertvector(f, bf16x8);
+        }
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt)
             acc[kt][nt] =
                 __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[kt], zb[nt], acc[kt][nt], 0, 0, 0);
+      }
+    } else {
+      // the rows of the next step are on their way during the products of this one
+      const int lr = J.pair_rows ? 16 * w + 4 * quad : 4 * w + quad, lj = J.pair_rows ? 1 : 16;
+      float xv[2][4][KT], zv[2][4][NT];
+      int gr[2][4];
+      auto fetch = [&](int rg, int b) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const size_t r = (size_t)min(rg + lr + lj * j, r1 - 1);
+          if constexpr (ONEHOT)
+            gr[b][j] = J.group ? J.group[r] : 0;
+          else
+            load_cols<KT>(X + r * J.ldx, xv[b][j]);
+          load_cols<NT>(Z + r * J.ldz, zv[b][j]);
+        }
+      };
+      auto step = [&](int rg, int b) {
+        fetch(rg + 64, 1 - b);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool rv = rg + lr + lj * j < r1;
+          float zj[NT];
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) zj[nt] = rv && nc + nt < J.nout ? zv[b][j][nt] : 0.f;
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt) {
+            float xj;
+            if constexpr (ONEHOT)
+              xj = rv && gr[b][j] == kc + kt ? 1.f : 0.f;
+            else
+              xj = rv && kc + kt < J.kin ? xv[b][j][kt] : 0.f;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+              acc[kt][nt] =
+                  __builtin_amdgcn_mfma_f32_16x16x4f32(xj, zj[nt], acc[kt][nt], 0, 0, 0);
+          }
+        }
+      };
+      if (r0 < r1) fetch(r0, 0);
+      for (int rg = r0; rg < r1; rg += 128) {
+        step(rg, 0);
+        if (rg + 64 < r1) step(rg + 64, 1);
       }
     }
   }
   // D[i][j]: register v of lane l holds i = 4 (l / 16) + v, j = l % 16
+  constexpr int kWave = KT * NT * kWgTile;
+  static_assert(4 * kWave <= kWgRed, "shared sums");
 #pragma unroll
   for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) red[w][((kt * NT + nt) * 4 + v) * 64 + lane] = acc[kt][nt][v];
+      for (int v = 0; v < 4; ++v)
+        red[w * kWave + (kt * NT + nt) * kWgTile + v * 64 + lane] = acc[kt][nt][v];
   __syncthreads();
+  const int nout_pad = (J.nout + 15) / 16 * 16;
   for (int e = threadIdx.x; e < KT * NT * 256; e += 256) {
-    const float sum = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
-    const int l = e & 63, v = (e >> 6) & 3, tile = e >> 8;
-    const int kt = tile / NT, nt = tile % NT;
-    const int ki = k0 + 16 * kt + 4 * (l >> 4) + v, nj = n0 + 16 * nt + (l & 15);
-    if (ki < kin_pad && nj < nout_pad)
-      part[((size_t)blockIdx.x * kin_pad + ki) * nout_pad + nj] = sum;
+    const int nl = e % (16 * NT), kl = e / (16 * NT);
+    const int ki = k0 + kl, nj = n0 + nl, i = kl / KT;
+    if (ki >= J.kin || nj >= nout_pad) continue;
+    const float *q =
+        red + ((kl % KT) * NT + nl % NT) * kWgTile + (i & 3) * 64 + 16 * (i >> 2) + nl / NT;
+    part[J.part + ((size_t)bx * J.kin + ki) * nout_pad + nj] =
+        ((q[0] + q[kWave]) + q[2 * kWave]) + q[3 * kWave];
   }
 }
 
-// Variant for the pair operands: Xt of kin features, Zt of nout features, each
-// in blocks of 16 rows, feature by feature inside a block (tr_row); segment 2
-// (if seg2 > 0, a multiple of 16) starts at row seg2.  Lane (c, q) of a 16-row
-// step reads rows 4q..4q+3 of feature c as one float4 (16 features' rows side by
-// side), which is the k-slice layout of the BF16 product; the FP32 product
-// takes the four components as four 16x16x4 steps.
-__device__ __forceinline__ size_t fm_row(size_t row, int nf) {
-  return (row >> 4) * (size_t)(16 * nf) + (row & 15);
-}
-
-template <int KT, int NT, bool BF, bool ONEHOT>
-__global__ __launch_bounds__(256) void k_wgrad_fm(const float *__restrict__ Xt,
-                                                  const float *__restrict__ Zt, size_t seg2,
-                                                  int kin, int nout,
-                                                  const int *__restrict__ rows_dev, int rows_max,
-                                                  int rows_per_block,
-                                                  const int32_t *__restrict__ group,
-                                                  float *__restrict__ part, int kin_pad,
-                                                  int nout_pad) {
-  __shared__ float red[4][KT * NT * 256];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int rows = rows_dev ? min(rows_dev[0], rows_max) : rows_max;
-  const int r0 = blockIdx.x * rows_per_block;
-  const int r1 = min(rows, r0 + rows_per_block);
-  const int k0 = blockIdx.y * 16 * KT, n0 = blockIdx.z * 16 * NT;
-  floatx4 acc[KT][NT];
-#pragma unroll
-  for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[kt][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int col = lane & 15, quad = lane >> 4;
-  const int nseg = (ONEHOT || seg2 == 0) ? 1 : 2;
-  for (int seg = 0; seg < nseg; ++seg) {
-    const size_t base = seg ? seg2 : 0;
-    if constexpr (BF) {
-      // BF16: 32 rows per gfx950 16x16x32 step; lane slots 0..3 hold rows
-      // rg + 4q + 0..3 and slots 4..7 rows rg + 16 + 4q + 0..3, on both
-      // operands.  A second half that starts past r1 re-reads the first
-      // half's rows (masked to zero).
-      static_assert(!ONEHOT, "group sums use FP32 operands");
-      for (int rg = r0 + w * 32; rg < r1; rg += 128) {
-        const int rq0 = rg + 4 * quad, rq1 = rq0 + 16;
-        const int rq1a = rq1 < r1 ? rq1 : rq0;
-        bool rv[8];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          rv[j] = rq0 + j < r1;
-          rv[4 + j] = rq1 + j < r1;
-        }
-        floatx8 xv[KT], zv[NT];
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt) {
-          const int c = k0 + 16 * kt + col;
-          const float *xp = Xt + 16 * (c < kin ? c : 0);
-          const floatx4 v0 = *(const floatx4 *)(xp + fm_row(base + rq0, kin)),
-                        v1 = *(const floatx4 *)(xp + fm_row(base + rq1a, kin));
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            xv[kt][j] = (rv[j] && c < kin) ? v0[j] : 0.f;
-            xv[kt][4 + j] = (rv[4 + j] && c < kin) ? v1[j] : 0.f;
-          }
-        }
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const int c = n0 + 16 * nt + col;
-          const float *zp = Zt + 16 * (c < nout ? c : 0);
-          const floatx4 v0 = *(const floatx4 *)(zp + fm_row(base + rq0, nout)),
-                        v1 = *(const floatx4 *)(zp + fm_row(base + rq1a, nout));
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            zv[nt][j] = (rv[j] && c < nout) ? v0[j] : 0.f;
-            zv[nt][4 + j] = (rv[4 + j] && c < nout) ? v1[j] : 0.f;
-          }
-        }
-        bf16x8 xb[KT], zb[NT];
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt) xb[kt] = __builtin_convertvector(xv[kt], bf16x8);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) zb[nt] = __builtin_convertvector(zv[nt], bf16x8);
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            acc[kt][nt] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[kt], zb[nt], acc[kt][nt], 0, 0, 0);
-      }
-      continue;
-    }
-    for (int rg = r0 + w * 16; rg < r1; rg += 64) {
-      const int rq = rg + 4 * quad;
-      bool rv[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rv[j] = rq + j < r1;
-      floatx4 xv[KT], zv[NT];
-      if constexpr (ONEHOT) {
-        const int4 gq = group ? *(const int4 *)(group + rq) : make_int4(0, 0, 0, 0);
-        const int gg[4] = {gq.x, gq.y, gq.z, gq.w};
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) xv[kt][j] = (rv[j] && gg[j] == k0 + 16 * kt + col) ? 1.f : 0.f;
-      } else {
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt) {
-          const int c = k0 + 16 * kt + col;
-          const floatx4 v =
-              *(const floatx4 *)(Xt + fm_row(base + rq, kin) + 16 * (c < kin ? c : 0));
-#pragma unroll
-          for (int j = 0; j < 4; ++j) xv[kt][j] = (rv[j] && c < kin) ? v[j] : 0.f;
-        }
-      }
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int c = n0 + 16 * nt + col;
-        const floatx4 v =
-            *(const floatx4 *)(Zt + fm_row(base + rq, nout) + 16 * (c < nout ? c : 0));
-#pragma unroll
-        for (int j = 0; j < 4; ++j) zv[nt][j] = (rv[j] && c < nout) ? v[j] : 0.f;
-      }
-      {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-              acc[kt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[kt][j], zv[nt][j],
-                                                                  acc[kt][nt], 0, 0, 0);
-      }
-    }
-  }
-#pragma unroll
-  for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) red[w][((kt * NT + nt) * 4 + v) * 64 + lane] = acc[kt][nt][v];
-  __syncthreads();
-  for (int e = threadIdx.x; e < KT * NT * 256; e += 256) {
-    const float sum = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
-    const int l = e & 63, v = (e >> 6) & 3, tile = e >> 8;
-    const int kt = tile / NT, nt = tile % NT;
-    const int ki = k0 + 16 * kt + 4 * (l >> 4) + v, nj = n0 + 16 * nt + (l & 15);
-    if (ki < kin_pad && nj < nout_pad)
-      part[((size_t)blockIdx.x * kin_pad + ki) * nout_pad + nj] = sum;
+template <bool BF>
+__global__ __launch_bounds__(256) void k_wgrads(TrWgrads B, float *__restrict__ part) {
+  __shared__ float red[kWgRed];
+  int n = 0;
+  while (n + B.job[n].members < B.n && (int)blockIdx.x >= B.job[n + B.job[n].members].blk0)
+    n += B.job[n].members;
+  const int l = blockIdx.x - B.job[n].blk0, m = 8 * B.job[n].members;
+  const int b = l / m * 8 + l % 8;
+  const TrWgradJob &J = B.job[n + l % m / 8];
+  if (b >= J.gx * J.gy * J.gz) return;
+  const int bx = b % J.gx, by = b / J.gx % J.gy, bz = b / (J.gx * J.gy);
+  switch (J.tile) {
+    case kWgX1: wgrad_tile<1, 2, BF, false>(J, bx, by, bz, part, red); break;
+    case kWgX2: wgrad_tile<2, 4, BF, false>(J, bx, by, bz, part, red); break;
+    case kWgSum: wgrad_tile<1, 4, false, true>(J, bx, by, bz, part, red); break;
+    default: wgrad_tile<4, 1, false, true>(J, bx, by, bz, part, red); break;
   }
 }
 
 // acc[k][n] += sum_b part[b][k][n] in a fixed order: thread (slice, e) sums
 // the blocks b = slice (mod 16) of output e in FP64, then the 16 slices are
 // added in slice order.
-__global__ __launch_bounds__(256) void k_reduce_parts(const float *__restrict__ part, int nblk,
-                                                      int kin_pad, int nout_pad, int kin,
-                                                      int nout, double *__restrict__ acc) {
+__global__ __launch_bounds__(256) void k_wgrad_sums(TrWgrads B, const float *__restrict__ part) {
   __shared__ double red[16][16];
+  int q = 0;
+  while (q + 1 < B.n && (int)blockIdx.x >= B.job[q + 1].sum0) ++q;
+  const TrWgradJob &J = B.job[q];
+  const int nout_pad = (J.nout + 15) / 16 * 16;
   const int el = threadIdx.x & 15, sl = threadIdx.x >> 4;
-  const int e = blockIdx.x * 16 + el;
-  const bool ok = e < kin * nout;
-  const int k = ok ? e / nout : 0, n = ok ? e % nout : 0;
+  const int e = ((int)blockIdx.x - J.sum0) * 16 + el;
+  const bool ok = e < J.kin * J.nout;
+  const int k = ok ? e / J.nout : 0, n = ok ? e % J.nout : 0;
+  const float *p = part + J.part + (size_t)k * nout_pad + n;
   double s = 0.0;
-  for (int b = sl; b < nblk; b += 16) s += (double)part[((size_t)b * kin_pad + k) * nout_pad + n];
+#pragma unroll 8
+  for (int b = sl; b < J.gx; b += 16) s += (double)p[(size_t)b * J.kin * nout_pad];
   red[sl][el] = s;
   __syncthreads();
   if (sl == 0 && ok) {
     double t = 0.0;
-    for (int q = 0; q < 16; ++q) t += red[q][el];
-    acc[e] += t;
+    for (int i = 0; i < 16; ++i) t += red[i][el];
+    J.acc[e] += t;
   }
 }
 
@@ -952,53 +859,6 @@ __global__ __launch_bounds__(256) void k_force_error(const double *__restrict__ 
 }
 
 inline unsigned nblk(size_t n, int b) { return (unsigned)((n + b - 1) / b); }
-
-template <int KT, int NT, bool ONEHOT>
-void wgrad_t(const float *X1, const float *X2, int ldx, const float *Z1, const float *Z2, int ldz,
-             int kin, int nout, const int *rows_dev, int rows_max, int bf16,
-             const int32_t *group, float *part, size_t part_cap, double *acc, hipStream_t s) {
-  const int kin_pad = (kin + 15) / 16 * 16, nout_pad = (nout + 15) / 16 * 16;
-  const int gy = (kin + 16 * KT - 1) / (16 * KT), gz = (nout + 16 * NT - 1) / (16 * NT);
-  const size_t per = (size_t)kin_pad * nout_pad;
-  // about two row blocks per compute unit, each a multiple of 64 rows
-  int rpb = std::max(1024, (rows_max + 511) / 512);
-  rpb = (rpb + 63) / 64 * 64;
-  while ((size_t)((rows_max + rpb - 1) / rpb) * per > part_cap) rpb *= 2;
-  const int gx = std::max(1, (rows_max + rpb - 1) / rpb);
-  const dim3 grid(gx, gy, gz);
-  if (bf16 && !ONEHOT)
-    hipLaunchKernelGGL((k_wgrad<KT, NT, true, false>), grid, dim3(256), 0, s, X1, X2, ldx, Z1, Z2,
-                       ldz, kin, nout, rows_dev, rows_max, rpb, group, part, kin_pad, nout_pad);
-  else
-    hipLaunchKernelGGL((k_wgrad<KT, NT, false, ONEHOT>), grid, dim3(256), 0, s, X1, X2, ldx, Z1,
-                       Z2, ldz, kin, nout, rows_dev, rows_max, rpb, group, part, kin_pad,
-                       nout_pad);
-  hipLaunchKernelGGL(k_reduce_parts, dim3(nblk((size_t)kin * nout, 16)), dim3(256), 0, s, part,
-                     gx, kin_pad, nout_pad, kin, nout, acc);
-}
-
-template <int KT, int NT, bool ONEHOT>
-void wgrad_fm_t(const float *Xt, const float *Zt, size_t seg2, int kin, int nout,
-                const int *rows_dev, int rows_max, int bf16, const int32_t *group, float *part,
-                size_t part_cap, double *acc, hipStream_t s) {
-  const int kin_pad = (kin + 15) / 16 * 16, nout_pad = (nout + 15) / 16 * 16;
-  const int gy = (kin + 16 * KT - 1) / (16 * KT), gz = (nout + 16 * NT - 1) / (16 * NT);
-  const size_t per = (size_t)kin_pad * nout_pad;
-  // row blocks of a multiple of 64 rows, about four per compute unit
-  int rpb = std::max(512, (rows_max + 1023) / 1024);
-  rpb = (rpb + 63) / 64 * 64;
-  while ((size_t)((rows_max + rpb - 1) / rpb) * per > part_cap) rpb *= 2;
-  const int gx = std::max(1, (rows_max + rpb - 1) / rpb);
-  const dim3 grid(gx, gy, gz);
-  if (bf16 && !ONEHOT)
-    hipLaunchKernelGGL((k_wgrad_fm<KT, NT, true, false>), grid, dim3(256), 0, s, Xt, Zt,
-                       seg2, kin, nout, rows_dev, rows_max, rpb, group, part, kin_pad, nout_pad);
-  else
-    hipLaunchKernelGGL((k_wgrad_fm<KT, NT, false, ONEHOT>), grid, dim3(256), 0, s, Xt, Zt,
-                       seg2, kin, nout, rows_dev, rows_max, rpb, group, part, kin_pad, nout_pad);
-  hipLaunchKernelGGL(k_reduce_parts, dim3(nblk((size_t)kin * nout, 16)), dim3(256), 0, s, part,
-                     gx, kin_pad, nout_pad, kin, nout, acc);
-}
 
 }  // namespace
 
@@ -1073,55 +933,84 @@ hipError_t launch_tr_pair_rev(const TrainPairArgs &a, const float4 *delta, const
                            X3, Z3, X2, Z2, Z1, WS1, grp);
 }
 
-void tr_wgrad(const float *X1, const float *X2, int ldx, const float *Z1, const float *Z2, int ldz,
-              int kin, int nout, const int *rows_dev, int rows_max, int bf16, float *part,
-              size_t part_cap, double *acc, hipStream_t s) {
+void TrWgrads::add(const float *X1, const float *X2, int ldx, const float *Z1, const float *Z2,
+                   int ldz, int kin, int nout, const int *rows_dev, int rows_max,
+                   bool pair_rows, const int32_t *group, bool onehot, double *acc) {
   if (rows_max <= 0) return;
-  if (kin <= 16 && nout <= 32)
-    wgrad_t<1, 2, false>(X1, X2, ldx, Z1, Z2, ldz, kin, nout, rows_dev, rows_max, bf16, nullptr,
-                         part, part_cap, acc, s);
-  else if (kin <= 32 && nout <= 64)
-    wgrad_t<2, 4, false>(X1, X2, ldx, Z1, Z2, ldz, kin, nout, rows_dev, rows_max, bf16, nullptr,
-                         part, part_cap, acc, s);
-  else
-    wgrad_t<4, 4, false>(X1, X2, ldx, Z1, Z2, ldz, kin, nout, rows_dev, rows_max, bf16, nullptr,
-                         part, part_cap, acc, s);
+  TrWgradJob &J = job[n++];
+  J = TrWgradJob{X1, X2, Z1, Z2, group, rows_dev, acc, ldx, ldz, kin, nout, rows_max, pair_rows};
+  J.tile = onehot ? (kin <= 16 ? kWgSum : kWgSumWide) : (kin <= 16 && nout <= 32 ? kWgX1 : kWgX2);
+  const int tk = J.tile == kWgX2 ? 32 : J.tile == kWgSumWide ? 64 : 16;
+  const int tn = J.tile == kWgX1 ? 32 : J.tile == kWgSumWide ? 16 : 64;
+  J.gy = (kin + tk - 1) / tk;
+  J.gz = (nout + tn - 1) / tn;
+  // blocks of rows, a multiple of 64: about four per compute unit of the pairs',
+  // two of the atoms'.  They fix the order of the sums.
+  const size_t per = (size_t)((kin + 15) / 16 * 16) * ((nout + 15) / 16 * 16);
+  J.rpb = pair_rows ? std::max(512, (rows_max + 1023) / 1024)
+                    : std::max(1024, (rows_max + 511) / 512);
+  J.rpb = (J.rpb + 63) / 64 * 64;
+  while ((size_t)((rows_max + J.rpb - 1) / J.rpb) * per > kTrPartMax) J.rpb *= 2;
+  J.gx = std::max(1, (rows_max + J.rpb - 1) / J.rpb);
 }
 
-void tr_wgrad_fm(const float *Xt, const float *Zt, size_t seg2, int kin, int nout,
-                 const int *rows_dev, int rows_max, int bf16, float *part, size_t part_cap,
-                 double *acc, hipStream_t s) {
-  if (rows_max <= 0) return;
-  if (kin <= 16 && nout <= 32)
-    wgrad_fm_t<1, 2, false>(Xt, Zt, seg2, kin, nout, rows_dev, rows_max, bf16, nullptr,
-                            part, part_cap, acc, s);
-  else
-    wgrad_fm_t<2, 4, false>(Xt, Zt, seg2, kin, nout, rows_dev, rows_max, bf16, nullptr,
-                            part, part_cap, acc, s);
+void TrWgrads::product(const float *X1, const float *X2, int ldx, const float *Z1,
+                       const float *Z2, int ldz, int kin, int nout, const int *rows_dev,
+                       int rows_max, bool pair_rows, double *acc) {
+  add(X1, X2, ldx, Z1, Z2, ldz, kin, nout, rows_dev, rows_max, pair_rows, nullptr, false, acc);
 }
 
-void tr_colsum_fm(const float *Zt, int ncol, const int *rows_dev, int rows_max,
-                  const int32_t *group, int ngroups, float *part, size_t part_cap, double *acc,
-                  hipStream_t s) {
-  if (rows_max <= 0) return;
-  if (ngroups <= 16)
-    wgrad_fm_t<1, 4, true>(nullptr, Zt, 0, ngroups, ncol, rows_dev, rows_max, 0, group, part,
-                           part_cap, acc, s);
-  else
-    wgrad_fm_t<4, 4, true>(nullptr, Zt, 0, ngroups, ncol, rows_dev, rows_max, 0, group, part,
-                           part_cap, acc, s);
+void TrWgrads::colsum(const float *Z, int ldz, int ncol, const int *rows_dev, int rows_max,
+                      bool pair_rows, const int32_t *group, int ngroups, double *acc) {
+  add(nullptr, nullptr, 0, Z, nullptr, ldz, ngroups, ncol, rows_dev, rows_max, pair_rows, group,
+      true, acc);
 }
 
-void tr_colsum(const float *Z, int ldz, int ncol, const int *rows_dev, int rows_max,
-               const int32_t *group, int ngroups, float *part, size_t part_cap, double *acc,
-               hipStream_t s) {
-  if (rows_max <= 0) return;
-  if (ngroups <= 16)
-    wgrad_t<1, 4, true>(nullptr, nullptr, 0, Z, nullptr, ldz, ngroups, ncol, rows_dev, rows_max,
-                        0, group, part, part_cap, acc, s);
+void TrWgrads::plan() {
+  size_t floats = 0;
+  int blk = 0, sum = 0;
+  for (int k = 0, m = 1; k < n; ++k) {
+    TrWgradJob &J = job[k];
+    if (--m == 0) {  // a new group
+      auto count = [](const TrWgradJob &j) { return j.gx * j.gy * j.gz; };
+      while (k + m + 1 < n && J.pair_rows && job[k + m + 1].pair_rows &&
+             count(job[k + m + 1]) == count(J))
+        ++m;
+      J.members = ++m;
+      J.blk0 = blk;
+      blk += J.members * ((count(J) + 7) / 8 * 8);
+    }
+    J.sum0 = sum;
+    J.part = floats;
+    sum += (int)nblk((size_t)J.kin * J.nout, 16);
+    floats += (size_t)J.gx * J.kin * ((J.nout + 15) / 16 * 16);
+  }
+  blocks = blk;
+  sums = sum;
+}
+
+size_t TrWgrads::room() const {
+  // the count of row blocks rises and falls with the rows, below these bounds
+  size_t floats = 0;
+  for (int k = 0; k < n; ++k) {
+    const TrWgradJob &J = job[k];
+    const size_t least = J.pair_rows ? 512 : 1024, most = J.pair_rows ? 1024 : 512;
+    floats += std::min((J.rows_max + least - 1) / least, most) * J.kin *
+              ((J.nout + 15) / 16 * 16);
+  }
+  return floats;
+}
+
+hipError_t launch_tr_wgrads(const TrWgrads &b, int bf16, float *part, hipStream_t s) {
+  if (b.n <= 0) return hipSuccess;
+  for (int k = 0; k < b.n; ++k)  // the rows are read as vectors
+    if (b.job[k].ldx % 4 || b.job[k].ldz % 4) return hipErrorInvalidValue;
+  if (bf16)
+    hipLaunchKernelGGL((k_wgrads<true>), dim3(b.blocks), dim3(256), 0, s, b, part);
   else
-    wgrad_t<4, 4, true>(nullptr, nullptr, 0, Z, nullptr, ldz, ngroups, ncol, rows_dev, rows_max,
-                        0, group, part, part_cap, acc, s);
+    hipLaunchKernelGGL((k_wgrads<false>), dim3(b.blocks), dim3(256), 0, s, b, part);
+  hipLaunchKernelGGL(k_wgrad_sums, dim3(b.sums), dim3(256), 0, s, b, part);
+  return hipGetLastError();
 }
 
 void launch_adam(float *theta, float *m, float *v, const double *g, int n, float lr, float b1,

@@ -54,35 +54,59 @@ void launch_tr_fit_top(const float *t2, const float *y2, const float *yd1, const
 void launch_tr_fit_l0(const float *t1, const float *zd1, const float *yb1, const float *w_out,
                       const float *a, int nloc, int H, int ld, float *zb1, hipStream_t s);
 // Reverse sweep of the descriptor and the embedding net per pair; writes the
-// weight-gradient operands, F features each, in blocks of 16 pair rows, feature
-// by feature inside a block (feature f of row r at (r / 16) 16 F + 16 f + r % 16;
-// primal rows [0, P), tangent rows [Pcap, Pcap + P), Pcap a multiple of 16):
-//   X3 (F = 32) = h2 | h2', Z3 (64) = z3-bar | z3'-bar, X2 (16) = h1 | h1',
+// weight-gradient operands, one row per pair (primal rows [0, P), tangent rows
+// [Pcap, Pcap + P)):
+//   X3 (32 wide) = h2 | h2', Z3 (64) = z3-bar | z3'-bar, X2 (16) = h1 | h1',
 //   Z2 (32) = z2-bar | z2'-bar, Z1 (16) = z1-bar and WS1 (16) = ws-bar per pair
 //   (primal rows only); grp [P] = t_j * ntypes + t_i.
 hipError_t launch_tr_pair_rev(const TrainPairArgs &a, const float4 *delta, const float *Td,
                               const float *Db, int ldD, size_t Pcap, float *X3, float *Z3,
                               float *X2, float *Z2, float *Z1, float *WS1, int *grp,
                               hipStream_t s);
-// As tr_wgrad and tr_colsum for operands in that layout (Xt of kin features, Zt
-// of nout or ncol); the second segment starts at row seg2 (0: none).
-void tr_wgrad_fm(const float *Xt, const float *Zt, size_t seg2, int kin, int nout,
-                 const int *rows_dev, int rows_max, int bf16, float *part, size_t part_cap,
-                 double *acc, hipStream_t s);
-void tr_colsum_fm(const float *Zt, int ncol, const int *rows_dev, int rows_max,
-                  const int32_t *group, int ngroups, float *part, size_t part_cap, double *acc,
-                  hipStream_t s);
-// acc[kin][nout] += sum_r X1[r]^T Z1[r] + X2[r]^T Z2[r] over r < rows (rows
-// from *rows_dev when set, else rows_max); FP32 (or BF16-operand) matrix-core
-// partials per row block, summed in fixed order in FP64.
-void tr_wgrad(const float *X1, const float *X2, int ldx, const float *Z1, const float *Z2, int ldz,
-              int kin, int nout, const int *rows_dev, int rows_max, int bf16, float *part,
-              size_t part_cap, double *acc, hipStream_t s);
-// acc[g][c] += sum over rows r with group[r] == g of Z[r][c] (group == nullptr: g = 0),
-// as a matrix-core product with a generated one-hot operand; ngroups <= 64.
-void tr_colsum(const float *Z, int ldz, int ncol, const int *rows_dev, int rows_max,
-               const int32_t *group, int ngroups, float *part, size_t part_cap, double *acc,
-               hipStream_t s);
+
+// Weight gradients of a frame: sums over rows r < rows (rows from *rows_dev when
+// set, else rows_max) as FP32 (or BF16-operand) matrix-core partials per block of
+// rows, summed in fixed order in FP64.
+struct TrWgradJob {
+  const float *X1, *X2, *Z1, *Z2;
+  const int32_t *group;
+  const int *rows_dev;
+  double *acc;
+  int ldx, ldz, kin, nout, rows_max, pair_rows;
+  int tile, rpb, gx, gy, gz;  // output tile; rows per block; blocks, tiles along k and n
+  // A group of members jobs shares its workgroups from blk0 on: eight blocks of
+  // rows (one per XCD) of the first job, the same of the second, ..., so jobs that
+  // read the same rows read them at about the same time.  Set at a group's first job.
+  int members, blk0;
+  int sum0;                   // first workgroup of the sums
+  size_t part;                // first partial
+};
+enum { kWgX1, kWgX2, kWgSum, kWgSumWide };   // output tiles, 16 x 32, 32 x 64, 16 x 64, 64 x 16
+constexpr size_t kTrPartMax = (size_t)1 << 22;  // partials of one job
+
+struct TrWgrads {
+  static constexpr int kMax = 11;
+  TrWgradJob job[kMax];
+  int n = 0, blocks = 0, sums = 0;
+  // acc[kin][nout] += sum_r X1[r]^T Z1[r] + X2[r]^T Z2[r] (X2 == nullptr: the first only);
+  // pair_rows: the order in which a wavefront takes the rows of the pair operands
+  void product(const float *X1, const float *X2, int ldx, const float *Z1, const float *Z2,
+               int ldz, int kin, int nout, const int *rows_dev, int rows_max, bool pair_rows,
+               double *acc);
+  // acc[g][c] += sum over rows r with group[r] == g of Z[r][c] (group == nullptr: g = 0),
+  // as a matrix-core product with a generated one-hot operand; ngroups <= 64.
+  void colsum(const float *Z, int ldz, int ncol, const int *rows_dev, int rows_max,
+              bool pair_rows, const int32_t *group, int ngroups, double *acc);
+  void plan();          // places the jobs' blocks and partials
+  size_t room() const;  // floats of the partials, for these row counts and all smaller ones
+
+ private:
+  void add(const float *X1, const float *X2, int ldx, const float *Z1, const float *Z2, int ldz,
+           int kin, int nout, const int *rows_dev, int rows_max, bool pair_rows,
+           const int32_t *group, bool onehot, double *acc);
+};
+// part: room() floats; leading dimensions are multiples of 4.
+hipError_t launch_tr_wgrads(const TrWgrads &b, int bf16, float *part, hipStream_t s);
 // Adam on FP32 master weights with bias corrections bc1 = 1 - b1^t, bc2 = 1 - b2^t.
 void launch_adam(float *theta, float *m, float *v, const double *g, int n, float lr, float b1,
                  float b2, float eps, float bc1, float bc2, hipStream_t s);
