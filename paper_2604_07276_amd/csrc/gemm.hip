@@ -1260,6 +1260,103 @@ __global__ __launch_bounds__(256) void k_splitk_finish(const float *__restrict__
   epi.template apply<1, NT>(acc, row0, nt0, ntt, lane, M, cs);
 }
 
+// Products of few rows (the fitting net of a small system: 192 rows, 240 x 240
+// weights): one wavefront per 16 x 16 tile of outputs, 128 depths of both
+// operands loaded while the 128 before them are multiplied.  The streaming
+// kernel pays a load latency and a barrier for every 32 of the depth and its
+// 64-row blocks occupy a dozen CUs; here two latencies are left and the chain of
+// the tile's own matrix-core steps, in the streaming kernel's order (the same
+// bits).
+// At 192 rows, FP32: 240 x 240 15 -> 6 us, depth 1024 21 -> 8 us, depth 1600 in
+// slices (two launches) 26 -> 12 us.  Up to 1024 rows: the three fitting products
+// and their adjoints 96 -> 55 us at 192 rows, 112 -> 80 at 581, 95 -> 90 at 980
+// (BF16), but 141 -> 157 at 1960 and 177 -> 277 at 4095, where every tile reads
+// its operands from L2 by itself.
+constexpr int kFewRows = 1024;
+
+template <int BF>
+__device__ __forceinline__ floatx4 few_tile(const float *xrow, const float *wrow, int nch) {
+  constexpr int P = 8;  // 16-deep chunks of a panel
+  floatx4 x[2][P], w[2][P];
+  floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto fetch = [&](int c0, int b) {
+#pragma unroll
+    for (int c = 0; c < P; ++c) {
+      const int k = 16 * min(c0 + c, nch - 1);
+      w[b][c] = *(const floatx4 *)(wrow + k);
+      x[b][c] = *(const floatx4 *)(xrow + k);
+    }
+  };
+  auto panel = [&](int c0, int b) {
+    if (c0 + P < nch) fetch(c0 + P, 1 - b);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (BF != 0) {
+#pragma unroll
+      for (int c = 0; c < P; c += 2)
+        if (c0 + c < nch) {
+          const floatx4 w1 = c0 + c + 1 < nch ? w[b][c + 1] : floatx4{0.f, 0.f, 0.f, 0.f};
+          acc = mfma_bf16x2(to_bf16x8(w[b][c], w1), to_bf16x8(x[b][c], x[b][c + 1]), acc);
+        }
+    } else {
+#pragma unroll
+      for (int c = 0; c < P; ++c)
+        if (c0 + c < nch) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) acc = mfma4(w[b][c][t], x[b][c][t], acc);
+        }
+    }
+  };
+  fetch(0, 0);
+  for (int c0 = 0; c0 < nch; c0 += 2 * P) {
+    panel(c0, 0);
+    if (c0 + P < nch) panel(c0 + P, 1);
+  }
+  return acc;
+}
+
+template <class Epi, int BF>
+__global__ __launch_bounds__(256, 3) void k_gemm_few(GemmArgs a, Epi epi) {
+  __shared__ float cs[4 * 16];
+  static_assert(Epi::kCols == 1, "one staged column vector");
+  const int M = a.Mptr ? *a.Mptr : a.Mmax;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4, ntt = a.Npad / 16;
+  const int row0 = blockIdx.x * 16, tile = blockIdx.y * 4 + wave;
+  if (row0 >= M) return;  // the whole workgroup
+  stage_cols<Epi, 4>(epi, blockIdx.y * 4, a.Npad, cs);
+  __syncthreads();
+  if (tile >= ntt) return;  // no barrier follows
+  floatx4 acc[1][1];
+  acc[0][0] = few_tile<BF>(a.X + (size_t)(row0 + r < M ? row0 + r : 0) * a.ldx + 4 * g,
+                           a.Wt + (size_t)(tile * 16 + r) * a.K + 4 * g, a.K / 16);
+  epi.template apply<1, 1>(acc, row0, tile, ntt, lane, M, cs + 16 * wave);
+}
+
+// Deeper products of few rows: wavefront z takes the depths of slice z, the
+// slices are added in LDS in slice order.
+constexpr int kFewSlices = 8;
+
+template <class Epi, int BF>
+__global__ __launch_bounds__(64 * kFewSlices, 2) void k_gemm_slices(GemmArgs a, int nslice,
+                                                                   Epi epi) {
+  __shared__ float cs[16];
+  __shared__ floatx4 part[kFewSlices][64];
+  static_assert(Epi::kCols == 1, "one staged column vector");
+  const int z = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4, ntt = a.Npad / 16, M = a.Mmax;
+  const int row0 = blockIdx.x * 16, tile = blockIdx.y, k0 = z * a.kslice;
+  stage_cols<Epi, 1>(epi, tile, a.Npad, cs);
+  if (z < nslice)
+    part[z][lane] = few_tile<BF>(a.X + (size_t)(row0 + r < M ? row0 + r : 0) * a.ldx + 4 * g + k0,
+                                 a.Wt + (size_t)(tile * 16 + r) * a.K + 4 * g + k0,
+                                 min(a.kslice, a.K - k0) / 16);
+  __syncthreads();
+  if (z) return;
+  floatx4 acc[1][1] = {{floatx4{0.f, 0.f, 0.f, 0.f}}};
+  for (int q = 0; q < nslice; ++q) acc[0][0] += part[q][lane];
+  epi.template apply<1, 1>(acc, row0, tile, ntt, lane, M, cs);
+}
+
 // Rows per wave: two 16-row tiles for the large pair-batched products,
 // one for the centre-batched fitting net (more blocks for fewer rows).
 template <class Epi>
@@ -1287,6 +1384,15 @@ void run(const GemmArgs &a, const Epi &e, bool full_rows, hipStream_t s) {
     if (!a.bf16 && a.wup > 0.f && a.K == 384 && ntt == 7 &&
         launch_split<7, 24, 4, 8>(a, e, 1, s))
       return;
+  }
+  if constexpr (std::is_same_v<Epi, EpiLinear> || std::is_same_v<Epi, EpiTanhRes> ||
+                std::is_same_v<Epi, EpiBwdTanh>) {
+    if (a.Mmax > 0 && a.Mmax <= kFewRows && !(a.bf16 && a.xbf16)) {
+      const dim3 grid((unsigned)((a.Mmax + 15) / 16), (unsigned)((ntt + 3) / 4));
+      if (a.bf16) hipLaunchKernelGGL((k_gemm_few<Epi, 1>), grid, dim3(256), 0, s, a, e);
+      else hipLaunchKernelGGL((k_gemm_few<Epi, 0>), grid, dim3(256), 0, s, a, e);
+      return;
+    }
   }
   // the FP32 QKV projection (384 output columns over a 100-wide embedding):
   // the whole weight block resident, X read once
@@ -1331,7 +1437,7 @@ bool gemm_tanh_res_split(const GemmArgs &a, const float *bias, const int32_t *ro
                          size_t scratch_floats, hipStream_t s) {
   // few rows: fewer than 64 row blocks of 64, so the unsplit product would
   // occupy a fraction of the CUs for the whole k loop
-  constexpr int kMaxRows = 4096, kSlices = 8, NT = 4;
+  constexpr int kMaxRows = 4096, kSlices = kFewSlices, NT = 4;
   const int M = a.Mmax;
   if (a.Mptr || M <= 0 || M >= kMaxRows || a.K < 512 || (a.bf16 && a.xbf16) || !scratch)
     return false;
@@ -1342,6 +1448,18 @@ bool gemm_tanh_res_split(const GemmArgs &a, const float *bias, const int32_t *ro
   GemmArgs as = a;
   as.kslice = kslice;
   as.kreal = 0;
+  if (M <= kFewRows) {
+    const EpiTanhRes e{bias, row_type, bias_ld, nullptr, 0,    RES_NONE,
+                       0,    y,        ldy,     tout,    ldt, a.Nreal};
+    const dim3 grid((unsigned)((M + 15) / 16), (unsigned)(a.Npad / 16));
+    if (a.bf16)
+      hipLaunchKernelGGL((k_gemm_slices<EpiTanhRes, 1>), grid, dim3(64 * kFewSlices), 0, s, as,
+                         nslice, e);
+    else
+      hipLaunchKernelGGL((k_gemm_slices<EpiTanhRes, 0>), grid, dim3(64 * kFewSlices), 0, s, as,
+                         nslice, e);
+    return true;
+  }
   const EpiPartial ep{scratch, a.Npad, slice};
   const int ntt = a.Npad / 16;
   const dim3 grid((unsigned)((M + 63) / 64), (unsigned)((ntt + NT - 1) / NT), (unsigned)nslice);
