@@ -23,6 +23,7 @@
 // so probabilities never leave registers in the forward pass.
 #include <cfloat>
 
+#include "attn_classes.h"
 #include "dpa1_internal.h"
 #include "ln_res.h"
 #include "split.h"
@@ -1738,25 +1739,7 @@ __global__ __launch_bounds__(bwds_threads<NPAD>(), NPAD <= 96 ? 3 : 2) void k_at
 // results do not depend on it.
 __global__ void k_attn_classes(const int *__restrict__ nnei, int nloc, int active,
                                int *__restrict__ ccount, int *__restrict__ clist) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x & 63;
-  const int n = i < nloc ? nnei[i] : 0;
-  const int nat = n > 0 ? (n - 1) >> 5 : -1;
-  int cls = nat;
-  if (cls >= 0)
-    while (cls < 3 && !((active >> cls) & 1)) ++cls;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const unsigned long long bn = __ballot(nat == c);
-    if (bn != 0ull && lane == __ffsll((long long)bn) - 1) atomicAdd(&ccount[4 + c], __popcll(bn));
-    const unsigned long long b = __ballot(cls == c);
-    if (b == 0ull) continue;
-    const int leader = __ffsll((long long)b) - 1;
-    int pos0 = 0;
-    if (lane == leader) pos0 = atomicAdd(&ccount[c], __popcll(b));
-    pos0 = __shfl(pos0, leader);
-    if (cls == c) clist[(size_t)c * nloc + pos0 + __popcll(b & ((1ull << lane) - 1ull))] = i;
-  }
+  attn_class_lists(blockIdx.x * blockDim.x + threadIdx.x, nnei, nloc, active, ccount, clist);
 }
 
 // ------------------------------------------------------------------ descriptor

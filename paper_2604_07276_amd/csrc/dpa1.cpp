@@ -364,7 +364,7 @@ size_t carve_topo(dp_model *m, char *base, int nloc, int nall, int ncell) {
   w.nlist = c.take<int>((size_t)nall * m->sel);
   w.nnei = c.take<int>(nall);
   w.pair_off = c.take<int>(nloc + 1);
-  w.ccount = c.take<int>(8);
+  w.ccount = (int *)(m->flags + 1);  // one copy to the host takes both
   w.clist = c.take<int>(4 * (size_t)nloc);
   w.T = c.take<float>(NL * 4 * m->M);
   w.dmat = c.take<float>(NL * m->ldD);
@@ -559,10 +559,6 @@ int make_grid(const dp_model *m, const double *box, const double *bbox_lo,
   return DP_OK;
 }
 
-__global__ void k_fill_int(int *p, int n, int v) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) p[k] = v;
-}
 // Start of a step: the flags and attention class counts (block 0) and the
 // per-cell atom counters of the binning (all blocks), in one launch.
 __global__ void k_init_step(DevFlags *f, int *ccount, int *cell_count, int *cell_fill,
@@ -581,19 +577,6 @@ __global__ void k_init_step(DevFlags *f, int *ccount, int *cell_count, int *cell
     cell_count[k] = 0;
     cell_fill[k] = 0;
   }
-}
-// Capacity check of the pair arena (one block): a step with more neighbour
-// pairs than the arena holds records its count and gets no pair work at all
-// (every neighbour count, locals and ghosts, and every pair offset set to 0),
-// so no kernel indexes past the arena; the workspace grows at the next call.
-__global__ __launch_bounds__(1024) void k_pair_guard(int *pair_off, int *nnei, int nloc, int nall,
-                                                     long cap, DevFlags *f) {
-  const int total = pair_off[nloc];
-  __syncthreads();  // every thread has read the total before any is cleared
-  if ((long)total <= cap) return;
-  if (threadIdx.x == 0) f->pair_overflow = total;
-  for (int k = threadIdx.x; k < nall; k += blockDim.x) nnei[k] = 0;
-  for (int k = threadIdx.x; k <= nloc; k += blockDim.x) pair_off[k] = 0;
 }
 __global__ void k_bbox(const double *x, int n, double *out) {
   __shared__ double red[6][256];
@@ -662,35 +645,28 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
   const int *Pptr = w.pair_off + nloc;
   const int ne = (int)m->emb.size(), na = m->n_attn, nf = (int)m->fit.size();
 
-  RUN("init", hipLaunchKernelGGL(k_init_step, dim3((grid.ncell + 255) / 256), dim3(256), 0, s,
-                                 m->flags, w.ccount, w.cell_count, w.cell_fill, grid.ncell));
-  RUN("check_types", launch_check_types(d_types, nall, m->ntypes, m->flags, w.types_safe, s));
+  if (nall <= kBinAtoms && grid.ncell <= kBinCells) {
+    RUN("cells", launch_bin_small(d_coords, d_types, nall, m->ntypes, grid, m->flags, w.ccount,
+                                  w.types_safe, w.cell_start, w.cell_atoms, s));
+  } else {
+    RUN("init", hipLaunchKernelGGL(k_init_step, dim3((grid.ncell + 255) / 256), dim3(256), 0, s,
+                                   m->flags, w.ccount, w.cell_count, w.cell_fill, grid.ncell));
+    RUN("check_types", launch_check_types(d_types, nall, m->ntypes, m->flags, w.types_safe, s));
+    RUN("cell_bin", launch_cell_bin(d_coords, nall, grid, w.atom_cell, w.cell_count, s));
+    RUN("cell_scan", launch_scan(w.cell_count, grid.ncell, w.cell_start, s));
+    RUN("cell_fill", launch_cell_fill(w.atom_cell, nall, w.cell_start, w.cell_fill, w.cell_atoms,
+                                      s));
+  }
   d_types = w.types_safe;
-  RUN("cell_bin", launch_cell_bin(d_coords, nall, grid, w.atom_cell, w.cell_count, s));
-  RUN("cell_scan", launch_scan(w.cell_count, grid.ncell, w.cell_start, s));
-  RUN("cell_fill", launch_cell_fill(w.atom_cell, nall, w.cell_start, w.cell_fill, w.cell_atoms, s));
   RUN("nlist", launch_nlist(d_coords, nloc, nall, grid, m->rcut, sel, w.cell_start, w.cell_atoms,
                             w.nlist, w.nnei, m->flags, s));
-  RUN("pair_scan", launch_scan(w.nnei, nloc, w.pair_off, s));
-  if (m->cap_pairs < 0 || m->want_pairs > m->cap_pairs || m->cap_pairs_nloc != m->cap_nloc) {
-    // lay the pair arena out from this step's pair count (the only blocking
-    // point of a step, at the first step of a workspace and after growth)
-    int total = 0;
-    HIP_TRY(hipMemcpyAsync(&total, w.pair_off + nloc, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    int rc = ensure_pairs(m, std::max<long>(total, m->want_pairs));
-    if (rc) return rc;
-  } else {
-    RUN("pair_guard", hipLaunchKernelGGL(k_pair_guard, dim3(1), dim3(1024), 0, s, w.pair_off,
-                                         w.nnei, nloc, nall, m->cap_pairs, m->flags));
-  }
-  const int Pmax = (int)std::min<long>((long)nloc * sel, m->cap_pairs);
   // attention classes to launch: those that held centres in a recent step
   // (the host copy of the counts lags the device by a step or more; a stale
   // choice costs padding, never correctness), always the top one
   const int ncls = attn_class_count(sel);
-  int active = (1 << ncls) - 1;
-  if (m->ccount_host[4] >= 0) {
+  auto active_classes = [&] {
+    int active = (1 << ncls) - 1;
+    if (m->ccount_host[4] < 0) return active;
     active = 1 << (ncls - 1);
     for (int c = 0; c < ncls - 1; ++c)
       if (m->ccount_host[4 + c] > 0) active |= 1 << c;
@@ -703,14 +679,36 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
         active |= 1 << c;
         break;
       }
+    return active;
+  };
+  int active;
+  bool listed = false;
+  if (m->cap_pairs < 0 || m->want_pairs > m->cap_pairs || m->cap_pairs_nloc != m->cap_nloc) {
+    // lay the pair arena out from this step's pair count (the only blocking
+    // point of a step, at the first step of a workspace and after growth)
+    RUN("pair_scan", launch_scan(w.nnei, nloc, w.pair_off, s));
+    int total = 0;
+    HIP_TRY(hipMemcpyAsync(&total, w.pair_off + nloc, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    int rc = ensure_pairs(m, std::max<long>(total, m->want_pairs));
+    if (rc) return rc;
+    active = active_classes();
+  } else {
+    // few centres: the scan's block lists the attention classes too (a launch of
+    // their own, 4.7 us, is as fast from about 4096 centres on)
+    active = active_classes();
+    listed = na > 0 && nloc <= 4096;
+    RUN("pair_scan", launch_pair_scan(w.nnei, nloc, nall, m->cap_pairs, w.pair_off, m->flags,
+                                      active, w.ccount, listed ? w.clist : nullptr, s));
   }
+  const int Pmax = (int)std::min<long>((long)nloc * sel, m->cap_pairs);
   // the top class is always launched (nothing above it takes its centres);
   // when it held none recently, on a small grid
   int small = 0;
   if (m->ccount_host[4] >= 0 && m->ccount_host[4 + ncls - 1] == 0) small = 1 << (ncls - 1);
   m->cls_active = active;
   m->cls_small = small;
-  if (na > 0)
+  if (na > 0 && !listed)
     RUN("attn_classes", launch_attn_classes(w.nnei, nloc, active, w.ccount, w.clist, s));
   RUN("env_embed1",
       launch_env_embed1(d_coords, d_types, grid, nloc, sel, m->rcut, m->rcut_smth, w.nlist,
@@ -782,9 +780,8 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
   if (d_energy)
     RUN("reduce", launch_reduce(w.e, w.vir_part, nloc, d_energy, nullptr, d_atom_energy, s));
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(m->flags_host, m->flags, sizeof(DevFlags), hipMemcpyDeviceToHost, s));
-  if (na > 0 && nloc > 0)
-    HIP_TRY(hipMemcpyAsync(m->ccount_host, w.ccount, 8 * sizeof(int), hipMemcpyDeviceToHost, s));
+  const size_t status = sizeof(DevFlags) + (na > 0 && nloc > 0 ? 8 * sizeof(int) : 0);
+  HIP_TRY(hipMemcpyAsync(m->flags_host, m->flags, status, hipMemcpyDeviceToHost, s));
   m->last = s;
   m->have_step = true;
   m->last_nloc = nloc;
@@ -796,7 +793,8 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
 // Adjoint half: from unit seeds de_i/de_i down to g_ij = de_i/dd_ij, then the
 // weighted gather sign * (-sum_i wgt_i de_i/dx_k) and the virial.
 int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
-                     double *d_virial, hipStream_t s) {
+                     double *d_virial, hipStream_t s, double *d_energy = nullptr,
+                     double *d_atom_energy = nullptr) {
   auto &w = m->w;
   const dp_model::FwdState &fs = m->fwd;
   const double *d_coords = fs.coords;
@@ -860,14 +858,6 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
                                     sel, m->M, m->axis, ln_mode, gam, xh, rs, w.te[ne - 1],
                                     dG_cur, dnext, w.dRt, s));
   }
-  if (na == 0) {
-    RUN("zero_attn_grads", {
-      hipLaunchKernelGGL(k_fill_int, dim3((Pmax + 255) / 256), dim3(256), 0, s, (int *)w.gw,
-                         Pmax, 0);
-      hipLaunchKernelGGL(k_fill_int, dim3((4 * Pmax + 255) / 256), dim3(256), 0, s,
-                         (int *)w.gr, 4 * Pmax, 0);
-    });
-  }
   for (int a = na - 1; a >= 0; --a) {
     const auto &A = m->attn[a];
     const split::Scale sqkv = split::scale_of(A.qkv_max), so = split::scale_of(A.o_max);
@@ -930,11 +920,12 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
                                    s));
     }
   }
-  RUN("env_bwd", launch_env_bwd(w.geom, w.gs, w.dRt, w.gw, w.gr, Pptr, Pmax, 0.f, w.g, s));
+  RUN("env_bwd", launch_env_bwd(w.geom, w.gs, w.dRt, na > 0 ? w.gw : nullptr,
+                                na > 0 ? w.gr : nullptr, Pptr, Pmax, 0.f, w.g, s));
   RUN("forces", launch_forces(d_coords, grid, nloc, nall, sel, w.nlist, w.nnei, w.pair_off, w.g,
                               wgt, sign, d_out, w.vir_part, s));
-  if (d_virial)
-    RUN("reduce", launch_reduce(w.e, w.vir_part, nloc, nullptr, d_virial, nullptr, s));
+  if (d_virial || d_energy)
+    RUN("reduce", launch_reduce(w.e, w.vir_part, nloc, d_energy, d_virial, d_atom_energy, s));
   HIP_TRY(hipGetLastError());
   m->last = s;
   return DP_OK;
@@ -943,9 +934,10 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
 int enqueue_step(dp_model *m, const double *d_coords, const int32_t *d_types, const CellGrid &grid,
                  int nloc, int nall, double *d_energy, double *d_forces, double *d_virial,
                  double *d_atom_energy, hipStream_t s) {
-  int rc = enqueue_forward(m, d_coords, d_types, grid, nloc, nall, d_energy, d_atom_energy, s);
+  // energy and virial are reduced by one launch, after the adjoint
+  int rc = enqueue_forward(m, d_coords, d_types, grid, nloc, nall, nullptr, nullptr, s);
   if (rc) return rc;
-  return enqueue_backward(m, nullptr, 1.0, d_forces, d_virial, s);
+  return enqueue_backward(m, nullptr, 1.0, d_forces, d_virial, s, d_energy, d_atom_energy);
 }
 
 int check_flags(dp_model *m) {
@@ -1021,11 +1013,14 @@ int dp_create(const char *weights_path, double rcut, int sel, dp_model **out) {
   if (rc == DP_OK && !(m->rcut_smth < rcut))
     rc = fail(DP_ERR_ARG, "rcut %g must exceed rcut_smth %g", rcut, m->rcut_smth);
   if (rc == DP_OK) {
-    hipError_t e = hipMalloc(&m->flags, sizeof(DevFlags));
+    const size_t status = sizeof(DevFlags) + 8 * sizeof(int);
+    hipError_t e = hipMalloc(&m->flags, status);
     if (e == hipSuccess) e = hipMalloc(&m->bbox, 6 * sizeof(double));
-    if (e == hipSuccess) e = hipHostMalloc(&m->flags_host, sizeof(DevFlags));
-    if (e == hipSuccess) e = hipHostMalloc(&m->ccount_host, 8 * sizeof(int));
-    if (e == hipSuccess) m->ccount_host[4] = -1;  // no counts yet: every class active
+    if (e == hipSuccess) e = hipHostMalloc(&m->flags_host, status);
+    if (e == hipSuccess) {
+      m->ccount_host = (int *)(m->flags_host + 1);
+      m->ccount_host[4] = -1;  // no counts yet: every class active
+    }
     if (e == hipSuccess) e = hipStreamCreate(&m->own);
     if (e == hipSuccess) e = attn_prepare();
     if (e != hipSuccess) rc = fail(DP_ERR_DEVICE, "device setup failed: %s", hipGetErrorString(e));

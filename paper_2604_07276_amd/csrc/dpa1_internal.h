@@ -56,6 +56,17 @@ void launch_check_types(const int32_t *types, int nall, int ntypes, DevFlags *fl
 void launch_cell_bin(const double *coords, int nall, CellGrid grid, int *atom_cell,
                      int *cell_count, hipStream_t s);
 void launch_scan(const int *in, int n, int *out_excl, hipStream_t s);  // out[n] = total
+// Systems of at most this many atoms and cells are binned by one block, which
+// also sets the flags and clears ccount: flags and types checked, cell starts
+// and members.
+constexpr int kBinAtoms = 8192, kBinCells = 4096;
+void launch_bin_small(const double *coords, const int32_t *types, int nall, int ntypes,
+                      CellGrid grid, DevFlags *flags, int *ccount, int32_t *safe,
+                      int *cell_start, int *cell_atoms, hipStream_t s);
+// Pair offsets with the capacity check, and with clist != nullptr the attention
+// class lists as launch_attn_classes would make them.
+void launch_pair_scan(int *nnei, int nloc, int nall, long cap, int *pair_off, DevFlags *flags,
+                      int active, int *ccount, int *clist, hipStream_t s);
 void launch_cell_fill(const int *atom_cell, int nall, const int *cell_start, int *cell_fill,
                       int *cell_atoms, hipStream_t s);
 void launch_nlist(const double *coords, int nloc, int nall, CellGrid grid, double rcut,

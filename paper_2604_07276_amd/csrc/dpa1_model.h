@@ -140,7 +140,7 @@ struct dp_model {
   } w;
   dpa1::DevFlags *flags = nullptr;       // device
   dpa1::DevFlags *flags_host = nullptr;  // pinned
-  int *ccount_host = nullptr;            // pinned [8]: class counts of a recent step
+  int *ccount_host = nullptr;            // behind them, [8]: class counts of a recent step
   int cls_active = 0;                    // attention classes launched by the last forward
   int cls_small = 0;                     // of those, the ones launched on a small grid
   double *bbox = nullptr;          // device [6]: bounding box for open boundaries
@@ -163,7 +163,6 @@ struct dp_model {
     if (flags) (void)hipFree(flags);
     if (bbox) (void)hipFree(bbox);
     if (flags_host) (void)hipHostFree(flags_host);
-    if (ccount_host) (void)hipHostFree(ccount_host);
     if (own) (void)hipStreamDestroy(own);
   }
 };

@@ -65,7 +65,8 @@ __global__ void k_env_bwd(const float *__restrict__ geom, const float *__restric
   const float s = gp[G_S], rx = gp[G_RX], ry = gp[G_RY], rz = gp[G_RZ];
   const float sw = gp[G_SW], r = gp[G_R], dsw_dr = gp[G_DSW];
   const float4 dR = *(const float4 *)(dRt + 4 * (size_t)p);
-  const float4 ga = *(const float4 *)(gr + 4 * (size_t)p);
+  // without attention layers nothing but the descriptor reaches sw and rhat
+  const float4 ga = gr ? *(const float4 *)(gr + 4 * (size_t)p) : make_float4(0.f, 0.f, 0.f, 0.f);
   // R~ = (s, s rhat)
   const float ds = gs[p] + dR.x + dR.y * rx + dR.z * ry + dR.w * rz;
   float drx = ga.x + s * dR.y;
@@ -73,7 +74,7 @@ __global__ void k_env_bwd(const float *__restrict__ geom, const float *__restric
   float drz = ga.z + s * dR.w;
   // s = sw / r
   const float inv_r = 1.0f / r;
-  const float dsw = gw[p] + ds * inv_r;
+  const float dsw = (gw ? gw[p] : 0.f) + ds * inv_r;
   const float dr = -ds * sw * inv_r * inv_r + dsw * dsw_dr;
   // rhat = d / r: tangential projection
   const float proj = drx * rx + dry * ry + drz * rz;
@@ -169,7 +170,12 @@ __global__ __launch_bounds__(512) void k_reduce(const float *__restrict__ e,
                                                  double *__restrict__ energy,
                                                  double *__restrict__ virial,
                                                  double *__restrict__ atom_energy) {
-  // energy == nullptr skips the energy, virial == nullptr the virial
+  // energy == nullptr skips the energy, virial == nullptr the virial; of two
+  // blocks the first takes the energy, the second the virial
+  if (gridDim.x == 2) {
+    if (blockIdx.x == 0) virial = nullptr;
+    else energy = nullptr;
+  }
   constexpr int T = 512, W = T / 64;
   __shared__ double red[10][W];
   const int t = threadIdx.x;
@@ -257,7 +263,7 @@ void launch_forces(const double *coords, CellGrid grid, int nloc, int nall, int 
 
 void launch_reduce(const float *e, const double *vir_part, int nloc, double *energy,
                    double *virial, double *atom_energy, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(512), 0, s, e, vir_part, nloc, energy, virial,
+  hipLaunchKernelGGL(k_reduce, dim3(energy && virial ? 2 : 1), dim3(512), 0, s, e, vir_part, nloc, energy, virial,
                      atom_energy);
 }
 

@@ -1,0 +1,84 @@
+"""Binning, neighbour lists and pair offsets at the edges of their routes.
+
+Up to 8192 atoms and 4096 cells one block bins the atoms (1024 threads, several
+atoms and cells each), beyond that five launches; the pair offsets come from one
+block with chunks of a multiple of four centres, which also lists the attention
+classes of up to 4096 centres.  Lists are compared with the oracle's, the
+energies of a repeated step (the first lays the workspace out and takes a path
+of its own) with the first one's, and the two attention routes through them.
+"""
+
+import numpy as np
+import pytest
+
+from oracle import dpa1_oracle as orc
+from paper_2604_07276_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+RC, SEL = 6.0, 120
+
+
+def gas(n, length, seed):
+    """n atoms in a periodic cube: a jittered subset of a grid, at least 0.9 A apart."""
+    rng = np.random.default_rng(seed)
+    side = int(np.ceil(n ** (1 / 3)))
+    step = length / side
+    assert step > 1.3
+    g = np.stack(np.meshgrid(*[(np.arange(side) + 0.5) * step] * 3, indexing="ij"), -1)
+    x = rng.permutation(g.reshape(-1, 3))[:n] + rng.uniform(-0.2, 0.2, (n, 3))
+    return x, rng.integers(0, 5, n).astype(np.int32), np.diag([length] * 3)
+
+
+@pytest.mark.parametrize("n,length", [(5, 13.0), (600, 112.0), (1023, 30.0), (1025, 30.0),
+                                      (4097, 46.0), (8192, 58.0), (8193, 58.0)])
+def test_lists_at_route_edges(n, length, tmp_path):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_07276_amd import binding
+    print(f"case: cells, {n} atoms, box {length}", flush=True)
+    p = str(tmp_path / "w.bin")
+    synth.make_weights(p, seed=2, shape=synth.STUDENT_SHAPE)
+    x, types, box = gas(n, length, n)
+    m = binding.Model(p, RC, SEL)
+    try:
+        first = m.compute(x, types, box, n, 0, True)
+        again = m.compute(x, types, box, n, 0, True)
+        nl, nn = m.debug_nlist(n)
+        bad = types.copy()
+        bad[n - 1] = 7
+        with pytest.raises(binding.DPError):
+            m.compute(x, bad, box, n, 0)
+        last = m.compute(x, types, box, n, 0, True)
+    finally:
+        m.close()
+    ref = orc.neighbor_list(x, box, RC, np.arange(n))
+    for i in range(n):
+        k = len(ref[i])
+        assert nn[i] == k and np.array_equal(nl[i, :k], ref[i]) and np.all(nl[i, k:] == -1), i
+    for a, b, c in zip(first, again, last):
+        assert np.array_equal(a, b) and np.array_equal(a, c)
+
+
+@pytest.mark.parametrize("n", [4096, 4097])
+def test_attention_lists_at_route_edges(n, tmp_path):
+    """The classes listed by the scan's block and by a launch of their own: the same bits as the
+    first step, whose classes are always listed by the launch."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_07276_amd import binding
+    print(f"case: attention class lists, {n} atoms", flush=True)
+    p = str(tmp_path / "w.bin")
+    synth.make_weights(p, seed=2, shape=synth.ModelShape())
+    x, types, box = gas(n, 46.0, n)
+    m = binding.Model(p, RC, SEL)
+    try:
+        first = m.compute(x, types, box, n, 0, True)
+        for _ in range(2):
+            again = m.compute(x, types, box, n, 0, True)
+            for a, b in zip(first, again):
+                assert np.array_equal(a, b)
+    finally:
+        m.close()
