@@ -968,167 +968,289 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
 
 // ------------------------------------------------------------ fused adjoint
 //
-// FP32 classes of up to 96 neighbours: one workgroup per centre runs both
+// BF16 classes of up to 96 neighbours: the wavefronts of a centre run both
 // halves of the adjoint.  Phase Q (wavefront = query tile) forms dA^T, the
 // softmax adjoint, dS and dQ as the query-tile kernel does and leaves
-// A = P H and dS of the centre in LDS ([query][key], row stride NPAD + 4),
-// with the query-side sums and the key-side sums reduced over its 16
-// queries; phase K (wavefront = key tile) forms dV = A^T dO and dK = dS^T Q
-// from them.  Against the two-kernel form the centre's logits and gate
-// records are read once, and dA and the per-pair statistics never go to
+// A = P H and dS of the centre in LDS ([query][key], rounded to BF16 as the
+// products take them), with the query-side sums and the key-side sums reduced
+// over its 16 queries; phase K (wavefront = key tile) forms dV = A^T dO and
+// dK = dS^T Q from them.  Against the two-kernel form the centre's logits and
+// gate records are read once, and dA and the per-pair statistics never go to
 // memory.  dQ, dK and dV are accumulated in the same order as there; only
 // the key-side sums are added in another order.
+//
+// LDS holds every operand in BF16, row-major: V, K, dO and Q rows in turn, each
+// stored by the wavefront that owns the row, and A and dS.  Where a product
+// contracts over rows, gfx950's transposing LDS read (ds_read_b64_tr_b16) brings
+// four rows of one column per lane, so nothing is stored transposed.  That is
+// 78 KB for the 96 class instead of 142 KB in FP32, and two centres to a CU, in
+// one workgroup of 12 wavefronts (k_attn_bwd_s says why) instead of one of six.
+// The sums over a query tile's 16 lanes run on the vector ALU.  15,668 centres of
+// the 96 class: 1.20 -> 0.88 ms a layer, 3 GB of pair rows and logits (0.6 ms at
+// the rate of a large copy); a second read of the logits instead of the second
+// exponential 0.94 ms.
 template <int NPAD>
-constexpr int fused_ld() { return NPAD + 4; }
+constexpr int bwdf_centres() { return 12 / (NPAD / 16); }
+constexpr int kLDB = 144;  // row of 128 features: 72 dwords, 8 mod 64 banks
+template <int NPAD>
+constexpr int fused_ld() { return NPAD + 8; }
 
 template <int NPAD>
+constexpr size_t bwdf_centre_lds() {
+  return sizeof(float4) * NPAD * (2 + NPAD / 16)  // kg, qside, key-side sums per query tile
+         + 2 * NPAD * (kLDB + 2 * fused_ld<NPAD>());
+}
+template <int NPAD>
 size_t bwdf_lds() {
-  constexpr int W = NPAD / 16;
-  return sizeof(float4) * NPAD * (2 + W)  // kg, qside, key-side sums per query tile
-         + sizeof(float) * stage_floats<NPAD>() + sizeof(float) * 2 * NPAD * fused_ld<NPAD>();
+  return bwdf_centres<NPAD>() * bwdf_centre_lds<NPAD>();
+}
+
+// One 16-row tile of a BF16 pair tensor as load_rows gives it, kept in BF16.
+__device__ __forceinline__ void load_rows_b(const float *rows, int col, int ld, int base, int n,
+                                            int row, int g, bf16x4 (&v)[8]) {
+  const __bf16 *rb = (const __bf16 *)rows + (size_t)base * ld + col;
+  const int off = (row < n ? row : 0) * ld + 4 * g;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) v[c] = *(const bf16x4 *)(rb + off + 16 * c);
+}
+// The lane's own row into X[row][kLDB]; rows past n as zeros.
+__device__ __forceinline__ void store_rows_b(__bf16 *X, int row, bool ok, int g,
+                                             const bf16x4 (&v)[8]) {
+  const bf16x4 zero = to_bf16(floatx4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+  for (int c = 0; c < 8; ++c) *(bf16x4 *)(X + row * kLDB + 16 * c + 4 * g) = ok ? v[c] : zero;
+}
+__device__ __forceinline__ bf16x8 pair_b(const bf16x4 &lo, const bf16x4 &hi) {
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// Rows 4g .. 4g + 3 of column r of a 16 x 16 tile: each lane names four columns
+// of one row (row 4g + r / 4, columns 4 (r % 4)), p = tr_at(tile).
+__device__ __forceinline__ int tr_at(int ld, int r, int g) {
+  return (4 * g + (r >> 2)) * ld + 4 * (r & 3);
+}
+__device__ __forceinline__ bf16x4 tr_read(const __bf16 *p) {
+  typedef short shortx4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) shortx4 *lds_ptr;
+  return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)p));
+}
+// acc[ft] += contraction over the rows of tiles 'tile' and 'tile' + 1 of X (xt at
+// tr_at of X), B operand bt.  Output lane layout: own row r, features 16 ft + 4 g + v.
+__device__ __forceinline__ void accum_tr(const __bf16 *xt, int tile, const bf16x8 &bt,
+                                         floatx4 (&acc)[8]) {
+  const __bf16 *x = xt + tile * 16 * kLDB;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    bf16x4 x0[4], x1[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      x0[f] = tr_read(x + (4 * h + f) * 16);
+      x1[f] = tr_read(x + 16 * kLDB + (4 * h + f) * 16);
+    }
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+      acc[4 * h + f] = mfma_bf16x2(pair_b(x0[f], x1[f]), bt, acc[4 * h + f]);
+  }
+}
+
+// The value of lane i ^ S of the 16 lanes of a group, on the vector ALU: a
+// rotation by 8, a permutation of quads, and for 4 a shift up for the even quads
+// and one down for the odd ones.
+template <int S>
+__device__ __forceinline__ float xor16(float x) {
+  if constexpr (S == 4) {
+    const int v = __builtin_bit_cast(int, x);
+    const int lo = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, false);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(lo, v, 0x114, 0xf, 0xa, false));
+  } else {
+    return dpp<S == 8 ? kDppXor8 : S == 2 ? 0x4E : kDppXor1>(x);
+  }
 }
 
 // Sum of 16 per-lane values over the 16 lanes of a lane group (those that
 // share lane / 16): after four halving steps lane r of the group holds the
 // total of value r (30 exchanges instead of 64).  Both halves are exchanged
 // and the lane keeps one sum: a select between two array elements would be
-// turned into an indexed access and push the array out of registers.
-__device__ __forceinline__ float reduce16_transposed(float (&v)[16], int r) {
+// turned into an indexed access and push the array out of registers.  On the
+// vector ALU, not through LDS: they were 180 of a wavefront's 480 LDS
+// operations (0.98 -> 0.94 ms a layer).
+template <int S>
+__device__ __forceinline__ void halve16(float (&v)[16], int r) {
+  const bool up = (r & S) != 0;
 #pragma unroll
-  for (int s = 8; s >= 1; s >>= 1) {
-    const bool up = (r & s) != 0;
-#pragma unroll
-    for (int j = 0; j < s; ++j) {
-      const float lo = v[j], hi = v[j + s];
-      const float lo_t = lo + __shfl_xor(lo, s);
-      const float hi_t = hi + __shfl_xor(hi, s);
-      v[j] = up ? hi_t : lo_t;
-    }
+  for (int j = 0; j < S; ++j) {
+    const float lo_t = v[j] + xor16<S>(v[j]);
+    const float hi_t = v[j + S] + xor16<S>(v[j + S]);
+    v[j] = up ? hi_t : lo_t;
   }
+}
+__device__ __forceinline__ float reduce16_transposed(float (&v)[16], int r) {
+  halve16<8>(v, r);
+  halve16<4>(v, r);
+  halve16<2>(v, r);
+  halve16<1>(v, r);
   return v[0];
 }
 
-// BF: BF16 matrix-core operands (tiles taken in pairs, every class has an
-// even number) and BF16 storage of QKV, dO and dQKV, as in the two-kernel
-// form; LDS and the elementwise work stay FP32.
+// Lane indices that the optimiser cannot connect with those of an earlier
+// phase, so that no address is kept in registers from one to the next.
+#define FRESH_LANES                                    \
+  int lane_ = lane;                                    \
+  asm volatile("" : "+v"(lane_));                      \
+  const int r = lane_ & 15, g = lane_ >> 4;            \
+  const int kk = wave * 16 + r;                        \
+  const bool kok = kk < n;                             \
+  (void)kok;
+
 template <int NPAD>
-__global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd_f(
+__global__ __launch_bounds__(768, 3) void k_attn_bwd_f(
     const float *__restrict__ qkv, const float *__restrict__ dO,
     const float *__restrict__ geom, const int *__restrict__ pair_off,
     const int *__restrict__ nnei, const int *__restrict__ clist, const int *__restrict__ ccount,
-    int sel, float shift, const float *__restrict__ lam, const float2 *__restrict__ fstat,
+    float shift, const float *__restrict__ lam, const float2 *__restrict__ fstat,
     float *__restrict__ dqkv, float *__restrict__ gw, float *__restrict__ gr, int accumulate) {
   constexpr int NT = NPAD / 16;
+  constexpr int C = bwdf_centres<NPAD>();
   constexpr int LDF = fused_ld<NPAD>();
   extern __shared__ float4 smem[];
-  float4 *kg = smem;                       // [NPAD] rhat, sw
+  __shared__ unsigned bar[C];  // arrivals at the barriers of each centre
+  const int part = __builtin_amdgcn_readfirstlane((int)threadIdx.x / (NT * 64));
+  float4 *kg = smem + part * (bwdf_centre_lds<NPAD>() / sizeof(float4));  // [NPAD] rhat, sw
   float4 *qside = kg + NPAD;               // [NPAD] query-side sums of each neighbour
   float4 *ksum = qside + NPAD;             // [NT][NPAD] key-side sums, per query tile
-  float *buf = (float *)(ksum + NT * NPAD);  // V rows, K^T, dO rows, Q^T in turn
-  float *As = buf + stage_floats<NPAD>();  // [NPAD][LDF] A = P H
-  float *Ds = As + NPAD * LDF;             // [NPAD][LDF] dS
+  __bf16 *buf = (__bf16 *)(ksum + NT * NPAD);  // V, K, dO, Q rows in turn
+  __bf16 *As = buf + NPAD * kLDB;          // [NPAD][LDF] A = P H
+  __bf16 *Ds = As + NPAD * LDF;            // [NPAD][LDF] dS
   const int ld = kQKV * 128;
   const float inv_sqrt_d = 0.08838834764831845f;
   const int cnt = *ccount;
-  // the V rows and gate records of a centre are loaded during the dK
+  // the V and dO rows and gate records of a centre are loaded during the dK
   // product of the previous one
-  float4 sv[8];
+  bf16x4 vrow[8], dov[8];
   float4 gv;
   float gl = 0.f;
   int n_nx = 0, base_nx = 0;
-  if ((int)blockIdx.x < cnt) {
-    const int tid = fresh_tid();
-    const int i0 = clist[blockIdx.x];
-    n_nx = nnei[i0];
-    base_nx = pair_off[i0];
-    stage_rows_load<NPAD, true>(qkv, 256, ld, base_nx, n_nx, tid, sv);  // V
+  auto fetch = [&](int at, int tid) {  // (past the last centre: that one again)
+    const int i = clist[min(at, cnt - 1)];
+    n_nx = __builtin_amdgcn_readfirstlane(nnei[i]);
+    base_nx = __builtin_amdgcn_readfirstlane(pair_off[i]);
+    const int row = (tid >> 6) * 16 + (tid & 15), g = (tid & 63) >> 4;
+    load_rows_b(qkv, 256, ld, base_nx, n_nx, row, g, vrow);
+    load_rows_b(dO, 0, 128, base_nx, n_nx, row, g, dov);
     gv = gate_load(geom, base_nx, n_nx, tid, gl);
-  }
-  for (int it = blockIdx.x; it < cnt; it += gridDim.x) {
-    const int tid = fresh_tid();
-    const int wave = tid >> 6;
+  };
+  // part p takes the centres p grids further on: with fewer centres than
+  // workgroups every centre has a CU to itself
+  const int step = (int)gridDim.x * C;
+  const int first = (int)blockIdx.x + part * (int)gridDim.x;
+  CentreBarrier<C, NT> barrier(bar, part);
+  if (first >= cnt) return;  // one centre's wavefronts, no shared barrier follows
+  fetch(first, fresh_tid() - part * NT * 64);
+  for (int it = first; it < cnt; it += step) {
+    const int tid = fresh_tid() - part * NT * 64;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
-    const int r = lane & 15, g = lane >> 4;
     const int n = n_nx;
     const int base = base_nx;
     const int ntile = (n + 15) >> 4;
-    const int q = wave * 16 + r;
-    const bool qok = q < n;
-    floatx4 dov[8];
-    load_rows<true>(dO, 0, 128, base, n, q, g, dov);
-    stage_rows_store<NPAD>(buf, tid, n, sv);
-    gate_store<NPAD>(kg, nullptr, tid, n, gv, gl);
-    __syncthreads();
+    bf16x4 krow[8];  // K, read while dA^T is formed
+    {
+      FRESH_LANES
+      store_rows_b(buf, kk, kok, g, vrow);
+      gate_store<NPAD>(kg, nullptr, tid, n, gv, gl);
+      load_rows_b(qkv, 128, ld, base, n, kk, g, krow);
+    }
+    barrier();
 
     // ---------------- phase Q: dA^T, dS, dQ, A and dS to LDS, both sides' sums
-    float4 kpre[8];  // K, read while dA^T is formed
-    stage_t_load<NPAD, true>(qkv, 128, ld, base, n, tid, kpre);
-    floatx4 da[NT];
-    if (wave < ntile) qk_lds<NT, true>(buf, r, g, dov, da);  // lane: query r, keys 4g + v
-    __syncthreads();
-    stage_t_store<NPAD>(buf, tid, n, kpre);  // K^T
-    __syncthreads();
+    floatx4 da[NT];  // lane: query r, keys 4g + v
     if (wave < ntile) {
+      FRESH_LANES
+#pragma unroll
+      for (int kt = 0; kt < NT; ++kt) da[kt] = floatx4{0.f, 0.f, 0.f, 0.f};
+      const __bf16 *xb = buf + r * kLDB + 4 * g;
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        bf16x4 a0[NT], a1[NT];
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt) {
+          a0[kt] = *(const bf16x4 *)(xb + kt * 16 * kLDB + 32 * h);
+          a1[kt] = *(const bf16x4 *)(xb + kt * 16 * kLDB + 32 * h + 16);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const bf16x8 bb = pair_b(dov[2 * h], dov[2 * h + 1]);
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt) da[kt] = mfma_bf16x2(pair_b(a0[kt], a1[kt]), bb, da[kt]);
+      }
+    }
+    barrier();
+    {
+      FRESH_LANES
+      store_rows_b(buf, kk, kok, g, krow);
+    }
+    barrier();
+    if (wave < ntile) {
+      FRESH_LANES
+      const int q = kk;
+      const bool qok = kok;
       const int qr = qok ? q : 0;
       const float4 gq = kg[q];
       const float wq = qok ? gq.w : 0.f;
       const float2 fs = fstat[base + qr];
       const float m = fs.x, invz = fs.y;
       const float *lp = lam + (size_t)(base + qr) * kLamLd + 4 * g;
-      // pass 1: probabilities P (kept in registers) and logits lam (to Ds) of the
-      // query's row, and D_q = sum_k P H dA (= dO . o, without o)
+      // pass 1: probabilities P of the query's row, and D_q = sum_k P H dA
+      // (= dO . o, without o)
       float dq = 0.f;
-      floatx4 pk[NT];  // P of the query's row (pass 1 -> pass 2)
-      {
-        floatx4 lcur = *(const floatx4 *)lp, lnxt;
+      floatx4 lk[NT];  // lam of the query's row; P is formed again in pass 2
 #pragma unroll
-        for (int kt = 0; kt < NT; ++kt) {
-          if (kt + 1 < NT) lnxt = *(const floatx4 *)(lp + 16 * (kt + 1));
-          floatx4 lv;
+      for (int kt = 0; kt < NT; ++kt) lk[kt] = *(const floatx4 *)(lp + 16 * kt);
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int k = kt * 16 + 4 * g + v;
-            const bool ok = qok && k < n;
-            const float4 gk = kg[k];
-            const float c = gq.x * gk.x + gq.y * gk.y + gq.z * gk.z;
-            const float lm = ok ? lcur[v] : 0.f;
-            const float l = (lm + shift) * (wq * gk.w) - shift;
-            const float p = ok ? exp_hw(l - m) * invz : 0.f;
-            dq += p * (wq * gk.w * c) * da[kt][v];
-            pk[kt][v] = p;
-            lv[v] = lm;
-          }
-          *(floatx4 *)(Ds + q * LDF + kt * 16 + 4 * g) = lv;
-          lcur = lnxt;
+      for (int kt = 0; kt < NT; ++kt) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int k = kt * 16 + 4 * g + v;
+          const bool ok = qok && k < n;
+          const float4 gk = kg[k];
+          const float c = gq.x * gk.x + gq.y * gk.y + gq.z * gk.z;
+          const float lm = ok ? lk[kt][v] : 0.f;
+          const float l = (lm + shift) * (wq * gk.w) - shift;
+          const float p = ok ? exp_hw(l - m) * invz : 0.f;
+          dq += p * (wq * gk.w * c) * da[kt][v];
+          lk[kt][v] = lm;
         }
-        dq = sum_groups(dq);
+        asm volatile("" : "+v"(dq));  // summed here, not after the last tile
       }
+      dq = sum_groups(dq);
+      // pass 2 reads the gates again: with indices that the optimiser
+      // knows, it would keep pass 1's values (a hundred registers) instead
+      int g2 = g;
+      asm volatile("" : "+v"(g2));
       floatx4 dqacc[8];
 #pragma unroll
       for (int ft = 0; ft < 8; ++ft) dqacc[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
       float dwq = 0.f, drqx = 0.f, drqy = 0.f, drqz = 0.f;
-      floatx4 dsp;  // dS of the even tile of a pair
-      // pass 2: the softmax adjoint; A = P H and dS replace P and lam
+      const __bf16 *xt = buf + tr_at(kLDB, r, g);
+      bf16x4 dsp;  // dS of the even tile of a pair
+      // pass 2: the softmax adjoint
 #pragma unroll
       for (int kt = 0; kt < NT; ++kt) {
-        const floatx4 pv = pk[kt];
-        const floatx4 lv = *(const floatx4 *)(Ds + q * LDF + kt * 16 + 4 * g);
         floatx4 ds, at;
         float ks[16];  // key-side terms: X w_q, Y rhat_q (x, y, z) for the four keys
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int k = kt * 16 + 4 * g + v;
+          const int k = kt * 16 + 4 * g2 + v;
           const float4 gk = kg[k];
           const float c = gq.x * gk.x + gq.y * gk.y + gq.z * gk.z;
           const float ww = wq * gk.w;
-          const float lm = lv[v];
-          const float p = pv[v];
+          const float lm = lk[kt][v];
+          const float l = (lm + shift) * (wq * gk.w) - shift;
+          const float p = qok && k < n ? exp_hw(l - m) * invz : 0.f;
           const float h = ww * c;
           const float dH = da[kt][v] * p;
           const float dL = p * (da[kt][v] * h - dq);
           ds[v] = dL * ww * inv_sqrt_d;
           at[v] = p * h;
-          const float X = dL * (lm + shift) + dH * c;
+          const float X = fmaf(dH, c, dL * (lm + shift));
           const float Y = dH * ww;
           dwq += X * gk.w;
           drqx += Y * gk.x;
@@ -1139,15 +1261,16 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
           ks[8 + v] = Y * gq.y;
           ks[12 + v] = Y * gq.z;
         }
-        *(floatx4 *)(As + q * LDF + kt * 16 + 4 * g) = at;
-        *(floatx4 *)(Ds + q * LDF + kt * 16 + 4 * g) = ds;
+        const bf16x4 dsb = to_bf16(ds);
+        *(bf16x4 *)(As + q * LDF + kt * 16 + 4 * g) = to_bf16(at);
+        *(bf16x4 *)(Ds + q * LDF + kt * 16 + 4 * g) = dsb;
         // lane r now holds the wavefront's total of term r / 4 for key
         // 4g + r % 4 of this tile
         const float kt_sum = reduce16_transposed(ks, r);
         ((float *)ksum)[(wave * NPAD + kt * 16 + 4 * g + (r & 3)) * 4 + (r >> 2)] = kt_sum;
         // dQ = dS K, tiles taken in pairs
-        if (kt % 2 == 0) dsp = ds;
-        else accum_lds2<NPAD>(buf, kt - 1, r, g, dsp, ds, dqacc);
+        if (kt % 2 == 0) dsp = dsb;
+        else accum_tr(xt, kt - 1, pair_b(dsp, dsb), dqacc);
       }
       dwq = sum_groups(dwq);
       drqx = sum_groups(drqx);
@@ -1160,40 +1283,31 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
         for (int ft = 0; ft < 8; ++ft) stp4<true>(dp, 16 * ft, dqacc[ft]);
       }
     }
-    __syncthreads();
+    barrier();
+    bf16x4 qrow[8];  // Q, read while dV is formed
     {
-      // dO rows for phase K: each wavefront writes the rows it holds (zeros
-      // past n) instead of reading them from memory a second time
-      float *xr = buf + q * kLDR + 4 * g;
-#pragma unroll
-      for (int c = 0; c < 8; ++c)
-        *(floatx4 *)(xr + 16 * c) = qok ? dov[c] : floatx4{0.f, 0.f, 0.f, 0.f};
+      FRESH_LANES
+      store_rows_b(buf, kk, kok, g, dov);
+      load_rows_b(qkv, 0, ld, base, n, kk, g, qrow);
     }
-    __syncthreads();
+    barrier();
 
     // ---------------- phase K: dV = A^T dO, dK = dS^T Q, key-side sums
-    float4 qpre[8];  // Q, read while dV is formed
-    stage_t_load<NPAD, true>(qkv, 0, ld, base, n, tid, qpre);
-    const int kk = wave * 16 + r;
-    const bool kok = kk < n;
+    const bf16x4 zero = to_bf16(floatx4{0.f, 0.f, 0.f, 0.f});
     if (wave < ntile) {
+      FRESH_LANES
       floatx4 dvacc[8];
 #pragma unroll
       for (int ft = 0; ft < 8; ++ft) dvacc[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
-      floatx4 atp;  // A^T of the even tile of a pair
+      const __bf16 *at = As + tr_at(LDF, r, g) + wave * 16;  // lane: key r, queries 4g + v
+      const __bf16 *xt = buf + tr_at(kLDB, r, g);
+      // tiles in pairs; A of query tiles at or past ntile (not written for this
+      // centre) is zero
 #pragma unroll
-      for (int qt = 0; qt < NT; ++qt) {
-        if (qt >= ntile) {
-          // an unpaired last tile meets a zero partner
-          if (qt % 2 == 1 && qt - 1 < ntile)
-            accum_rows2(buf, qt - 1, r, g, atp, floatx4{0.f, 0.f, 0.f, 0.f}, dvacc);
-          continue;
-        }
-        floatx4 at;  // lane: key r, queries 4g + v
-#pragma unroll
-        for (int v = 0; v < 4; ++v) at[v] = As[(qt * 16 + 4 * g + v) * LDF + kk];
-        if (qt % 2 == 0) atp = at;
-        else accum_rows2(buf, qt - 1, r, g, atp, at, dvacc);
+      for (int qt = 0; qt < NT; qt += 2) {
+        if (qt >= ntile) continue;
+        const bf16x4 a0 = tr_read(at + qt * 16 * LDF), a1 = tr_read(at + (qt + 1) * 16 * LDF);
+        accum_tr(xt, qt, pair_b(a0, qt + 1 < ntile ? a1 : zero), dvacc);
       }
       if (kok) {
         float *dp = pt_at<true>(dqkv, (size_t)(base + kk) * ld + 256 + 4 * g);
@@ -1201,37 +1315,25 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
         for (int ft = 0; ft < 8; ++ft) stp4<true>(dp, 16 * ft, dvacc[ft]);
       }
     }
-    __syncthreads();
-    stage_t_store<NPAD>(buf, tid, n, qpre);  // Q^T
-    __syncthreads();
+    barrier();
     {
-      const int itn = it + (int)gridDim.x;
-      if (itn < cnt) {
-        const int inx = clist[itn];
-        n_nx = nnei[inx];
-        base_nx = pair_off[inx];
-        stage_rows_load<NPAD, true>(qkv, 256, ld, base_nx, n_nx, tid, sv);  // next V
-        gv = gate_load(geom, base_nx, n_nx, tid, gl);
-      }
+      FRESH_LANES
+      store_rows_b(buf, kk, kok, g, qrow);
     }
+    barrier();
+    fetch(it + step, fresh_tid() - part * NT * 64);
     if (wave < ntile) {
+      FRESH_LANES
       floatx4 dkacc[8];
 #pragma unroll
       for (int ft = 0; ft < 8; ++ft) dkacc[ft] = floatx4{0.f, 0.f, 0.f, 0.f};
-      // tiles in pairs; dS of query tiles at or past ntile (not written for
-      // this centre) is zero
+      const __bf16 *dt = Ds + tr_at(LDF, r, g) + wave * 16;
+      const __bf16 *xt = buf + tr_at(kLDB, r, g);
 #pragma unroll
       for (int qt = 0; qt < NT; qt += 2) {
         if (qt >= ntile) continue;
-        floatx4 d0, d1;
-        const bool ok1 = qt + 1 < ntile;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          d0[v] = Ds[(qt * 16 + 4 * g + v) * LDF + kk];
-          const float x1 = Ds[((qt + 1) * 16 + 4 * g + v) * LDF + kk];
-          d1[v] = ok1 ? x1 : 0.f;
-        }
-        accum_lds2<NPAD>(buf, qt, r, g, d0, d1, dkacc);
+        const bf16x4 d0 = tr_read(dt + qt * 16 * LDF), d1 = tr_read(dt + (qt + 1) * 16 * LDF);
+        accum_tr(xt, qt, pair_b(d0, qt + 1 < ntile ? d1 : zero), dkacc);
       }
       if (kok) {
         float *dp = pt_at<true>(dqkv, (size_t)(base + kk) * ld + 128 + 4 * g);
@@ -1262,7 +1364,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 64 ? 2 : 1) void k_attn_bwd
         }
       }
     }
-    __syncthreads();  // LDS is restaged for the next centre
+    barrier();  // LDS is restaged for the next centre
   }
 }
 
@@ -1421,16 +1523,6 @@ __device__ __forceinline__ float reduce16_dpp(float (&v)[16], int r) {
   const float lo = v[0] + dpp<kDppXor1>(v[0]), hi = v[1] + dpp<kDppXor1>(v[1]);
   return (r & 1) ? hi : lo;
 }
-
-// Lane indices that the optimiser cannot connect with those of an earlier
-// phase, so that no address is kept in registers from one to the next.
-#define FRESH_LANES                                    \
-  int lane_ = lane;                                    \
-  asm volatile("" : "+v"(lane_));                      \
-  const int r = lane_ & 15, g = lane_ >> 4;            \
-  const int kk = wave * 16 + r;                        \
-  const bool kok = kk < n;                             \
-  (void)kok;
 
 template <int NPAD>
 __global__ __launch_bounds__(bwds_threads<NPAD>(), NPAD <= 96 ? 3 : 2) void k_attn_bwd_s(
@@ -2273,7 +2365,7 @@ hipError_t prepare_class(int dev, int cus, int cls) {
     if (e == hipSuccess)
       e = prepare(k_attn_bwd_s<NPAD>, bwds_threads<NPAD>(), bwds_lds<NPAD>(), 1);
   } else if constexpr (NPAD <= 96) {
-    if (e == hipSuccess) e = prepare(k_attn_bwd_f<NPAD>, th, bwdf_lds<NPAD>(), 8);
+    if (e == hipSuccess) e = prepare(k_attn_bwd_f<NPAD>, 768, bwdf_lds<NPAD>(), 8);
   } else {
     if (e == hipSuccess) e = prepare(k_attn_bwd_q<NPAD>, th, bwdq_lds<NPAD>(), 4);
     if (e == hipSuccess) e = prepare(k_attn_bwd_k<NPAD>, th, bwdk_lds<NPAD>(), 5);
@@ -2380,9 +2472,9 @@ void launch_attn_bwd_fused_class(int cls, const AttnArgs &a, const float *qkv, c
                          a.geom, a.pair_off, a.nnei, cl, cc, a.shift, lam, (const float2 *)fstat,
                          dqkv, gw, gr, accumulate);
     else if constexpr (NP <= 96)
-      hipLaunchKernelGGL(k_attn_bwd_f<NP>, grid, dim3(NP / 16 * 64), bwdf_lds<NP>(), s, qkv, dO,
-                         a.geom, a.pair_off, a.nnei, cl, cc, a.sel, a.shift, lam,
-                         (const float2 *)fstat, dqkv, gw, gr, accumulate);
+      hipLaunchKernelGGL(k_attn_bwd_f<NP>, grid, dim3(768), bwdf_lds<NP>(), s, qkv, dO, a.geom,
+                         a.pair_off, a.nnei, cl, cc, a.shift, lam, (const float2 *)fstat, dqkv, gw,
+                         gr, accumulate);
   });
 }
 
