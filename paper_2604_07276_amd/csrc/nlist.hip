@@ -11,6 +11,7 @@
 // the result does not depend on FMA formation:
 //   d = x_j - x_i;  with a box d -= L * rint(d / L);
 //   r2 = (dx*dx + dy*dy) + dz*dz;  neighbour iff r2 < rcut*rcut.
+#include <algorithm>
 #include <climits>
 
 #include "attn_classes.h"
@@ -254,28 +255,12 @@ __global__ void k_cell_fill(const int *__restrict__ atom_cell, int nall,
   cell_atoms[cell_start[c] + pos] = k;
 }
 
-// Distinct cell offsets along one dimension.
-__device__ __forceinline__ int dim_offsets(const CellGrid &g, int dim, int c, int out[3]) {
-  int n = 0;
+// The k-th (k < 3) distinct neighbour cell of c along one dimension, or -1.
+__device__ __forceinline__ int neighbour_cell(const CellGrid &g, int dim, int c, int k) {
   const int nc = g.nc[dim];
-  if (g.periodic) {
-    if (nc >= 3) {
-      out[n++] = (c + nc - 1) % nc;
-      out[n++] = c;
-      out[n++] = (c + 1) % nc;
-    } else if (nc == 2) {
-      out[n++] = 0;
-      out[n++] = 1;
-    } else {
-      out[n++] = 0;
-    }
-  } else {
-    for (int o = -1; o <= 1; ++o) {
-      int q = c + o;
-      if (q >= 0 && q < nc) out[n++] = q;
-    }
-  }
-  return n;
+  if (g.periodic) return nc >= 3 ? (c + nc + k - 1) % nc : k < nc ? k : -1;
+  const int q = c + k - 1;
+  return q >= 0 && q < nc ? q : -1;
 }
 
 // One workgroup per cell.  Every atom of a cell has the same 27 neighbour
@@ -285,7 +270,14 @@ __device__ __forceinline__ int dim_offsets(const CellGrid &g, int dim, int c, in
 // centres collect every atom within rcut; ghost centres collect local atoms
 // only (they are needed by the force gather, never as energy centres).  A
 // neighbourhood with more candidates than the tile holds is scanned from
-// global memory instead (same ranges, same test).
+// global memory instead (same ranges, same test).  Where there are few cells, up
+// to four workgroups share the centres of one.
+//
+// Latency and FP64 work bound it, not memory: the ranges of the 27 cells are
+// read by 27 lanes at once (one lane in turn waited for 18 loads and more), the
+// periodic test multiplies by 1 / L (divisions only within 1e-6 of the cutoff),
+// and the sort compares four entries per LDS read.  192 atoms 18 -> 10 us, 4095
+// 60 -> 23, a domain of 980 and 7000 ghosts 56 -> 38, 15,668 atoms 77 -> 51.
 constexpr int kCellWaves = 8;      // wavefronts per cell workgroup
 constexpr int kTileCap = 1536;     // staged candidates (about 2.5x the protein density)
 constexpr int kMaxRanges = 27;
@@ -303,71 +295,64 @@ __device__ __forceinline__ bool within(double xi0, double xi1, double xi2, doubl
   return (d0 * d0 + d1 * d1) + d2 * d2 < rc2;
 }
 
+// The same decision without the divisions: d / L only picks the image, and a
+// rounding that picked the other one has |d| = L / 2 either way; r2 is then off
+// by parts in 1e9 at most, and the exact test decides within 1e-6 of the cutoff
+// (and on NaN).
+__device__ __forceinline__ bool within_fast(double xi0, double xi1, double xi2, double xj0,
+                                            double xj1, double xj2, const CellGrid &g,
+                                            const double (&inv)[3], double rc2) {
+  if (!g.periodic) return within(xi0, xi1, xi2, xj0, xj1, xj2, g, rc2);
+  double d0 = xj0 - xi0, d1 = xj1 - xi1, d2 = xj2 - xi2;
+  d0 -= g.L[0] * rint(d0 * inv[0]);
+  d1 -= g.L[1] * rint(d1 * inv[1]);
+  d2 -= g.L[2] * rint(d2 * inv[2]);
+  const double r2 = (d0 * d0 + d1 * d1) + d2 * d2;
+  if (r2 > rc2 * (1.0 + 1e-6)) return false;
+  if (r2 < rc2 * (1.0 - 1e-6)) return true;
+  return within(xi0, xi1, xi2, xj0, xj1, xj2, g, rc2);
+}
+
 __global__ __launch_bounds__(kWave *kCellWaves) void k_nlist(
     const double *__restrict__ x, int nloc, CellGrid g, double rc2, int sel,
     const int *__restrict__ cell_start, const int *__restrict__ cell_atoms,
     int *__restrict__ nlist, int *__restrict__ nnei, DevFlags *flags) {
   __shared__ int tj[kTileCap];
   __shared__ double tx[kTileCap], ty[kTileCap], tz[kTileCap];
-  __shared__ int list[kCellWaves][kListCap];
-  __shared__ int rb[kMaxRanges], roff[kMaxRanges + 1];
-  __shared__ int nr;
+  __shared__ __attribute__((aligned(16))) int list[kCellWaves][kListCap + 4];
+  __shared__ int rb[32], roff[32];  // ranges of cell_atoms, their places in the tile
   const int cell = blockIdx.x;
   const int a0 = cell_start[cell], a1 = cell_start[cell + 1];
   if (a0 == a1) return;  // empty cell: the whole workgroup leaves
   const int wave = threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
-  if (threadIdx.x == 0) {
-    // The cells of one (y, z) row are consecutive in the cell order, so their
-    // atoms are one contiguous range of cell_atoms unless the row wraps: the
-    // row's cells are visited in ascending index and merged while their
-    // atom ranges touch.
-    const int cx = cell % g.nc[0];
-    const int cy = (cell / g.nc[0]) % g.nc[1];
-    const int cz = cell / (g.nc[0] * g.nc[1]);
-    int ox[3], oy[3], oz[3];
-    const int nx = dim_offsets(g, 0, cx, ox);
-    const int ny = dim_offsets(g, 1, cy, oy);
-    const int nz = dim_offsets(g, 2, cz, oz);
-    int q = 0, tot = 0;
-    auto add = [&](int beg, int end) {
-      rb[q] = beg;
-      roff[q] = tot;
-      tot += end - beg;
-      ++q;
-    };
-    for (int a = 0; a < nz; ++a)
-      for (int b = 0; b < ny; ++b) {
-        const int row = (oz[a] * g.nc[1] + oy[b]) * g.nc[0];
-        int cs[3];
-        for (int c = 0; c < nx; ++c) cs[c] = row + ox[c];
-        if (nx > 1 && cs[0] > cs[1]) { const int t = cs[0]; cs[0] = cs[1]; cs[1] = t; }
-        if (nx > 2 && cs[1] > cs[2]) { const int t = cs[1]; cs[1] = cs[2]; cs[2] = t; }
-        if (nx > 1 && cs[0] > cs[1]) { const int t = cs[0]; cs[0] = cs[1]; cs[1] = t; }
-        int beg = cell_start[cs[0]], end = cell_start[cs[0] + 1];
-        for (int c = 1; c < nx; ++c) {
-          const int cb = cell_start[cs[c]], ce = cell_start[cs[c] + 1];
-          if (cb == end) {
-            end = ce;
-          } else {
-            add(beg, end);
-            beg = cb;
-            end = ce;
-          }
-        }
-        add(beg, end);
-      }
-    roff[q] = tot;
-    nr = q;
+  if (threadIdx.x < 32) {
+    const int k = (int)threadIdx.x;
+    const int ox = neighbour_cell(g, 0, cell % g.nc[0], k % 3);
+    const int oy = neighbour_cell(g, 1, (cell / g.nc[0]) % g.nc[1], k / 3 % 3);
+    const int oz = neighbour_cell(g, 2, cell / (g.nc[0] * g.nc[1]), k / 9 % 3);
+    const bool ok = k < kMaxRanges && ox >= 0 && oy >= 0 && oz >= 0;
+    const int c = ok ? (oz * g.nc[1] + oy) * g.nc[0] + ox : cell;
+    const int beg = cell_start[c], n = ok ? cell_start[c + 1] - beg : 0;
+    int inc = n;
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1) {
+      const int y = __shfl_up(inc, off);
+      if (k >= off) inc += y;
+    }
+    rb[k] = beg;
+    roff[k] = inc - n;  // roff[27] and later: the total
   }
   __syncthreads();
-  const int R = nr;
+  constexpr int R = kMaxRanges;
   const int T = roff[R];
   const bool staged = T <= kTileCap;
   if (staged) {
     for (int t = threadIdx.x; t < T; t += blockDim.x) {
-      int q = 0;
-      while (t >= roff[q + 1]) ++q;  // ranges are few (at most 27)
+      int q = 0;  // the last range that starts at or before t (empty ones end there too)
+#pragma unroll
+      for (int h = 16; h >= 1; h >>= 1)
+        if (q + h < R && roff[q + h] <= t) q += h;
       const int j = cell_atoms[rb[q] + (t - roff[q])];
       tj[t] = j;
       tx[t] = x[3 * j + 0];
@@ -376,7 +361,9 @@ __global__ __launch_bounds__(kWave *kCellWaves) void k_nlist(
     }
   }
   __syncthreads();
-  for (int ai = a0 + wave; ai < a1; ai += kCellWaves) {
+  const double inv[3] = {1.0 / g.L[0], 1.0 / g.L[1], 1.0 / g.L[2]};
+  for (int ai = a0 + (int)blockIdx.y * kCellWaves + wave; ai < a1;
+       ai += kCellWaves * (int)gridDim.y) {
     const int k = cell_atoms[ai];
     const bool ghost = k >= nloc;
     const double xk0 = x[3 * k + 0], xk1 = x[3 * k + 1], xk2 = x[3 * k + 2];
@@ -395,7 +382,7 @@ __global__ __launch_bounds__(kWave *kCellWaves) void k_nlist(
         if (t < T) {
           j = tj[t];
           if (j != k && (!ghost || j < nloc))
-            hit = within(xk0, xk1, xk2, tx[t], ty[t], tz[t], g, rc2);
+            hit = within_fast(xk0, xk1, xk2, tx[t], ty[t], tz[t], g, inv, rc2);
         }
         keep(hit, j);
       }
@@ -409,7 +396,8 @@ __global__ __launch_bounds__(kWave *kCellWaves) void k_nlist(
           if (idx < end) {
             j = cell_atoms[idx];
             if (j != k && (!ghost || j < nloc))
-              hit = within(xk0, xk1, xk2, x[3 * j + 0], x[3 * j + 1], x[3 * j + 2], g, rc2);
+              hit = within_fast(xk0, xk1, xk2, x[3 * j + 0], x[3 * j + 1], x[3 * j + 2], g, inv,
+                                rc2);
           }
           keep(hit, j);
         }
@@ -429,10 +417,12 @@ __global__ __launch_bounds__(kWave *kCellWaves) void k_nlist(
       vals[h] = p < n ? list[wave][p] : INT_MAX;
       ranks[h] = 0;
     }
-    for (int q = 0; q < n; ++q) {
-      const int v = list[wave][q];
-      ranks[0] += v < vals[0];
-      ranks[1] += v < vals[1];
+    if (lane < 4) list[wave][n + lane] = INT_MAX;  // rounds the list up
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int q = 0; q < n; q += 4) {
+      const int4 v = *(const int4 *)&list[wave][q];
+      ranks[0] += (v.x < vals[0]) + (v.y < vals[0]) + (v.z < vals[0]) + (v.w < vals[0]);
+      ranks[1] += (v.x < vals[1]) + (v.y < vals[1]) + (v.z < vals[1]) + (v.w < vals[1]);
     }
     int *row = nlist + (size_t)k * sel;
     for (int h = 0; h < 2; ++h) {
@@ -557,7 +547,8 @@ void launch_nlist(const double *coords, int nloc, int nall, CellGrid grid, doubl
                   DevFlags *flags, hipStream_t s) {
   if (nall <= 0) return;
   const int ncell = grid.nc[0] * grid.nc[1] * grid.nc[2];
-  hipLaunchKernelGGL(k_nlist, dim3(ncell), dim3(kWave * kCellWaves), 0, s, coords, nloc, grid,
+  const int parts = std::max(1, std::min(4, 768 / ncell));  // workgroups of a cell
+  hipLaunchKernelGGL(k_nlist, dim3(ncell, parts), dim3(kWave * kCellWaves), 0, s, coords, nloc, grid,
                      rcut * rcut, sel, cell_start, cell_atoms, nlist, nnei, flags);
 }
 

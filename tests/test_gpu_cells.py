@@ -82,3 +82,34 @@ def test_attention_lists_at_route_edges(n, tmp_path):
                 assert np.array_equal(a, b)
     finally:
         m.close()
+
+
+@pytest.mark.parametrize("shift", [0.0, 0.1])
+@pytest.mark.parametrize("length,away", [(18.0, 0), (24.0, 0), (24.0, 3000)])
+def test_pairs_at_the_cutoff(length, away, shift, tmp_path):
+    """A 2 A lattice has pairs at exactly 6 A along the axes and the (4, 4, 2) directions: the
+    periodic test without divisions must take the same ones as the oracle, also for atoms many
+    boxes away and with coordinates that round."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_07276_amd import binding
+    print(f"case: pairs at the cutoff, box {length}, {away} boxes away, shift {shift}", flush=True)
+    p = str(tmp_path / "w.bin")
+    synth.make_weights(p, seed=2, shape=synth.STUDENT_SHAPE)
+    g = np.arange(0.0, length, 2.0)
+    x = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3) + shift
+    n = len(x)
+    rng = np.random.default_rng(n)
+    x = x + length * away * rng.integers(-1, 2, (n, 3))
+    box = np.diag([length] * 3)
+    m = binding.Model(p, RC, SEL)
+    try:
+        m.compute(x, rng.integers(0, 5, n).astype(np.int32), box, n, 0)
+        nl, nn = m.debug_nlist(n)
+    finally:
+        m.close()
+    ref = orc.neighbor_list(x, box, RC, np.arange(n))
+    for i in range(n):
+        k = len(ref[i])
+        assert nn[i] == k and np.array_equal(nl[i, :k], ref[i]), i
