@@ -19,7 +19,9 @@
  * (Sec. II-B, DPA-1); forces F = -dE/dx (Eq. (2)).
  *
  * Precision: neighbour search and minimum-image pair vectors in FP64; the
- * network in FP32 (FP32 MFMA); energy, force and virial reductions in FP64.
+ * network in FP32 (FP32 MFMA; the products of the attention adjoint on FP32
+ * values split into two f16 terms, FP32 accumulation, errors no larger than
+ * the FP32 MFMA's); energy, force and virial reductions in FP64.
  * Results are deterministic: the same inputs give bit-identical outputs.
  *
  * Ownership: the caller owns every array it passes.  A dp_model owns its

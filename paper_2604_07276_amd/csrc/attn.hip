@@ -1824,7 +1824,7 @@ __global__ __launch_bounds__(bwds_threads<NPAD>(), NPAD <= 96 ? 3 : 2) void k_at
 // is not launched: the host deactivates classes that were empty in an
 // earlier step, and a centre that falls into one after all is computed by
 // the next larger active class (more padding, the same result: the host
-// keeps the largest class of the fused FP32 adjoint active, so the fallback
+// keeps the largest class of the fused BF16 adjoint active, so the fallback
 // never changes the kind of adjoint).  Positions
 // are taken with one atomic per wavefront and class, so the order inside a
 // list varies from run to run; every centre is computed on its own, so
