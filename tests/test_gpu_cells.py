@@ -113,3 +113,26 @@ def test_pairs_at_the_cutoff(length, away, shift, tmp_path):
     for i in range(n):
         k = len(ref[i])
         assert nn[i] == k and np.array_equal(nl[i, :k], ref[i]), i
+
+
+@pytest.mark.parametrize("atoms", [1, 3])
+def test_attention_free_model_without_pairs(atoms, tmp_path):
+    """Atoms out of each other's reach: no pair row exists, so no pair kernel has a grid."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_07276_amd import binding
+    print(f"case: no pairs, {atoms} atoms", flush=True)
+    p = str(tmp_path / "w.bin")
+    synth.make_weights(p, seed=2, shape=synth.STUDENT_SHAPE)
+    x = np.arange(3.0 * atoms).reshape(atoms, 3) * 20.0
+    types = np.arange(atoms, dtype=np.int32)
+    m = binding.Model(p, RC, SEL)
+    try:
+        for _ in range(2):
+            E, F, V, _ = m.compute(x, types, None, atoms, 0)
+    finally:
+        m.close()
+    r = orc.compute(orc.load_model(p), x, types, None, atoms, 0, RC, SEL)
+    assert abs(E - r.energy) <= 1e-6 * atoms
+    assert not F.any() and not V.any()
