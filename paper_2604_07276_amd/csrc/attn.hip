@@ -480,6 +480,7 @@ __global__ __launch_bounds__(C * NPAD / 16 * 64, OP ? (C == 2 && NPAD == 96 ? 3 
   const int ld = kQKV * 128;
   const float inv_sqrt_d = 0.08838834764831845f;  // 1/sqrt(128)
   const int cnt = *ccount;
+  if ((int)blockIdx.x >= cnt) return;  // no centre for the whole workgroup
   if constexpr (OP) {
     for (int idx = threadIdx.x; idx < op.Nreal * 32; idx += blockDim.x) {
       const int row = idx >> 5, c4 = idx & 31;
@@ -1823,8 +1824,8 @@ __global__ __launch_bounds__(bwds_threads<NPAD>(), NPAD <= 96 ? 3 : 2) void k_at
 // top class active, so every centre is listed.  A class that is not active
 // is not launched: the host deactivates classes that were empty in an
 // earlier step, and a centre that falls into one after all is computed by
-// the next larger active class (more padding, the same result: the host
-// keeps the largest class of the fused BF16 adjoint active, so the fallback
+// the next larger active class (more padding, the same result: in BF16 the
+// host keeps the largest class of the fused adjoint active, so the fallback
 // never changes the kind of adjoint).  Positions
 // are taken with one atomic per wavefront and class, so the order inside a
 // list varies from run to run; every centre is computed on its own, so
@@ -2323,15 +2324,14 @@ int g_grid[kMaxDevices][10][4];
 
 int g_desc_grid[kMaxDevices][2];  // fused descriptor / projection adjoint: FP32, BF16
 
-// Blocks of the grid of a class that held no centres in a recent step: an
-// empty launch of the full persistent grid costs ~20 us.
-constexpr int kSmallGrid = 32;
-
-int grid_for(int kind, int cls, int small = 0) {
+// The persistent grid, also of a class that held no centres in a recent step: the
+// step may hold thousands after all (on 32 workgroups a step of 15,668 centres
+// took 62 ms instead of 11), and an empty launch of it takes what one of 32
+// workgroups takes (6.0 us with events around it).
+int grid_for(int kind, int cls) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) dev = 0;
-  const int gsz = g_grid[dev][kind][cls] > 0 ? g_grid[dev][kind][cls] : 1024;
-  return ((small >> cls) & 1) && gsz > kSmallGrid ? kSmallGrid : gsz;
+  return g_grid[dev][kind][cls] > 0 ? g_grid[dev][kind][cls] : 1024;
 }
 
 template <class K>
@@ -2436,7 +2436,7 @@ void launch_attn_fwd_class(int cls, const AttnArgs &a, const float *qkv, float *
   if (a.nloc <= 0) return;
   const int *cl = a.clist + (size_t)cls * a.nloc, *cc = a.ccount + cls;
   if (op && op->Nreal <= kFwdMaxCols) {
-    const dim3 grid(grid_for(a.bf16 ? 9 : 7, cls, a.small));
+    const dim3 grid(grid_for(a.bf16 ? 9 : 7, cls));
     ATTN_CLASS_SWITCH(cls, {
       constexpr int C = fwd_centres<NP>();
       hipLaunchKernelGGL((k_attn_fwd<NP, BFV, true, C>), grid, dim3(C * NP / 16 * 64),
@@ -2444,13 +2444,13 @@ void launch_attn_fwd_class(int cls, const AttnArgs &a, const float *qkv, float *
                          a.sel, a.shift, out, lam, (float2 *)fstat, *op);
     });
   } else if (op) {
-    const dim3 grid(grid_for(a.bf16 ? 6 : 2, cls, a.small));
+    const dim3 grid(grid_for(a.bf16 ? 6 : 2, cls));
     ATTN_CLASS_SWITCH(cls, hipLaunchKernelGGL((k_attn_fwd<NP, BFV, true, 1>), grid,
                                               dim3(NP / 16 * 64), fwd_lds<NP>(1, op->Nreal), s,
                                               qkv, a.geom, a.pair_off, a.nnei, cl, cc, a.sel,
                                               a.shift, out, lam, (float2 *)fstat, *op));
   } else {
-    const dim3 grid(grid_for(a.bf16 ? 3 : 0, cls, a.small));
+    const dim3 grid(grid_for(a.bf16 ? 3 : 0, cls));
     ATTN_CLASS_SWITCH(cls, hipLaunchKernelGGL((k_attn_fwd<NP, BFV, false, 1>), grid,
                                               dim3(NP / 16 * 64), fwd_lds<NP>(1, 0), s, qkv,
                                               a.geom, a.pair_off, a.nnei, cl, cc, a.sel, a.shift,
@@ -2465,7 +2465,7 @@ void launch_attn_bwd_fused_class(int cls, const AttnArgs &a, const float *qkv, c
                                  float *gr, int accumulate, hipStream_t s) {
   if (a.nloc <= 0 || !attn_bwd_fused(a, cls)) return;
   const int *cl = a.clist + (size_t)cls * a.nloc, *cc = a.ccount + cls;
-  const dim3 grid(grid_for(a.bf16 ? 8 : 1, cls, a.small));
+  const dim3 grid(grid_for(a.bf16 ? 8 : 1, cls));
   ATTN_CLASS_SWITCH(cls, {
     if constexpr (!BFV)
       hipLaunchKernelGGL(k_attn_bwd_s<NP>, grid, dim3(bwds_threads<NP>()), bwds_lds<NP>(), s, qkv, dO,
@@ -2482,7 +2482,7 @@ void launch_attn_bwd_q(const AttnArgs &a, const float *qkv, const float *o, cons
                        const float *lam, const float *fstat, float *dqkv, float *astat,
                        float *qside, float *dA, hipStream_t s) {
   if (a.nloc <= 0) return;
-  hipLaunchKernelGGL(k_attn_bwd_q<128>, dim3(grid_for(4, 3, a.small)), dim3(512), bwdq_lds<128>(),
+  hipLaunchKernelGGL(k_attn_bwd_q<128>, dim3(grid_for(4, 3)), dim3(512), bwdq_lds<128>(),
                      s, qkv, o, dO, a.geom, a.pair_off, a.nnei, a.clist + 3 * (size_t)a.nloc,
                      a.ccount + 3, a.sel, a.shift, lam, (const float2 *)fstat, dqkv,
                      (float4 *)astat, (float4 *)qside, dA);
@@ -2492,7 +2492,7 @@ void launch_attn_bwd_k(const AttnArgs &a, const float *qkv, const float *dO, con
                        const float *dA, float *dqkv, const float *astat, const float *qside,
                        float *gw, float *gr, int accumulate, hipStream_t s) {
   if (a.nloc <= 0) return;
-  hipLaunchKernelGGL(k_attn_bwd_k<128>, dim3(grid_for(5, 3, a.small)), dim3(512), bwdk_lds<128>(),
+  hipLaunchKernelGGL(k_attn_bwd_k<128>, dim3(grid_for(5, 3)), dim3(512), bwdk_lds<128>(),
                      s, qkv, dO, a.geom, a.pair_off, a.nnei, a.clist + 3 * (size_t)a.nloc,
                      a.ccount + 3, a.shift, lam, dA, dqkv, (const float4 *)astat,
                      (const float4 *)qside, gw, gr, accumulate);

@@ -664,21 +664,21 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
   // (the host copy of the counts lags the device by a step or more; a stale
   // choice costs padding, never correctness), always the top one
   const int ncls = attn_class_count(sel);
+  constexpr int kKeepClass = 1024;
   auto active_classes = [&] {
     int active = (1 << ncls) - 1;
     if (m->ccount_host[4] < 0) return active;
     active = 1 << (ncls - 1);
     for (int c = 0; c < ncls - 1; ++c)
       if (m->ccount_host[4 + c] > 0) active |= 1 << c;
-    // in BF16 the largest class with the fused adjoint stays launched, so that
-    // a centre is always computed by the same kind of adjoint (fused or not)
-    // and results do not depend on which classes were empty before
-    const AttnArgs probe{nullptr, nullptr, nullptr, nullptr, nullptr, nloc, sel, 0.f, m->bf16};
-    for (int c = ncls - 2; c >= 0; --c)
-      if (attn_bwd_fused(probe, c) && !attn_bwd_fused(probe, ncls - 1)) {
-        active |= 1 << c;
-        break;
-      }
+    // Of four classes the third stays launched.  In BF16 a centre is then always
+    // computed by the same kind of adjoint (fused or not) and results do not
+    // depend on which classes were empty before.  In FP32 it spares the centres
+    // of a step after a sparser one (systems that take turns on a handle) the
+    // padding to 128 slots; for few centres the launches of an empty class cost
+    // more over the steps (4 of 4.7 us in 520 at 600 centres of 40 neighbours)
+    // than that padding in the one step (0.79 -> 0.91 ms at 71 neighbours).
+    if (ncls == 4 && (m->bf16 || nloc > kKeepClass)) active |= 1 << 2;
     return active;
   };
   int active;
@@ -702,12 +702,7 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
                                       active, w.ccount, listed ? w.clist : nullptr, s));
   }
   const int Pmax = (int)std::min<long>((long)nloc * sel, m->cap_pairs);
-  // the top class is always launched (nothing above it takes its centres);
-  // when it held none recently, on a small grid
-  int small = 0;
-  if (m->ccount_host[4] >= 0 && m->ccount_host[4 + ncls - 1] == 0) small = 1 << (ncls - 1);
   m->cls_active = active;
-  m->cls_small = small;
   if (na > 0 && !listed)
     RUN("attn_classes", launch_attn_classes(w.nnei, nloc, active, w.ccount, w.clist, s));
   RUN("env_embed1",
@@ -733,7 +728,7 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
   // attention layers
   const int D = m->dattn, ldM = m->ldM;
   const AttnArgs aa{w.geom, w.pair_off, w.nnei,       w.clist,      w.ccount,
-                    nloc,   sel,        (float)m->shift, m->bf16, m->cls_small};
+                    nloc,   sel,        (float)m->shift, m->bf16};
   for (int a = 0; a < na; ++a) {
     const auto &A = m->attn[a];
     // in BF16 mode QKV, o, dO and dQKV are stored in BF16 (matrix-core operands only)
@@ -806,7 +801,7 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
   const int ne = (int)m->emb.size(), na = m->n_attn, nf = (int)m->fit.size();
   const int D = m->dattn, ldM = m->ldM;
   const AttnArgs aa{w.geom, w.pair_off, w.nnei,       w.clist,      w.ccount,
-                    nloc,   sel,        (float)m->shift, m->bf16, m->cls_small};
+                    nloc,   sel,        (float)m->shift, m->bf16};
   const bool emb_fused = ne == 3 && emb_fused_supported(m->lde[0], m->lde[1], m->lde[2]);
   EmbLaunch el{};
   if (emb_fused)

@@ -188,9 +188,6 @@ struct AttnArgs {
   int nloc, sel;
   float shift;
   int bf16;  // 1: BF16 matrix-core operands (FP32 accumulate)
-  // bit c: class c held no centres in a recent step; its persistent grid is
-  // kept to a few blocks (any count is still processed, only more slowly)
-  int small = 0;
 };
 // Output projection and layer norm of an attention layer, applied by the
 // forward itself (in BF16 mode with BF16 operands): W_O^T [kAttnOpCols][128]; bias, gamma, beta with
