@@ -428,7 +428,9 @@ size_t carve_pairs(dp_model *m, char *base, size_t P, bool shared) {
   w.dGb = c.take<float>(P * m->ldM);
   w.dY = c.take<float>(P * m->ldM);
   w.dO = c.take<float>(P * std::max(m->dattn, 16));
-  w.dqkv = c.take<float>(P * 3 * std::max(m->dattn, 16));
+  // (also the scratch of the first fitting layer's split product)
+  w.dqkv = c.take<float>(std::max(P * 3 * std::max(m->dattn, 16),
+                                  gemm_split_floats(m->cap_nloc, m->ldD, m->ldf[0])));
   w.dRt = c.take<float>(P * 4);
   w.gw = c.take<float>(P);
   w.gr = c.take<float>(P * 4);
@@ -756,10 +758,9 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
     GemmArgs a{w.dmat, m->ldD, L.Wt, m->ldD, L.ldout, L.fout, nullptr, nloc, m->bf16};
     // few centres (a small domain): the long-k first layer split over k, with
     // the attention adjoint's dQKV buffer (unused until the adjoint) as scratch
-    const size_t scratch = (size_t)(m->cap_pairs + 64) * 3 * std::max(m->dattn, 16);
     RUN("fit_fwd", {
       if (!gemm_tanh_res_split(a, m->fb0, d_types, L.ldout, w.z[0], L.ldout, w.tf[0], L.ldout,
-                               w.dqkv, m->cap_pairs >= 0 ? scratch : 0, s))
+                               w.dqkv, s))
         gemm_tanh_res(a, m->fb0, d_types, L.ldout, nullptr, 0, RES_NONE, 0, w.z[0], L.ldout,
                       w.tf[0], L.ldout, s);
     });

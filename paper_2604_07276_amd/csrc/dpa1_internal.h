@@ -113,11 +113,13 @@ void gemm_tanh_res(const GemmArgs &a, const float *bias, const int32_t *row_type
 // layer of a small domain): slices of the k range run as separate
 // workgroups into partial sums in scratch, one pass adds them in slice
 // order and applies the epilogue.  Returns false, launching nothing, when
-// the shape does not call for it or scratch (floats) is too small; the
-// caller then runs gemm_tanh_res.
+// the shape does not call for it; the caller then runs gemm_tanh_res.  Only the
+// shape decides, so that equal inputs give equal bits whatever the handle computed
+// before: scratch holds gemm_split_floats(rows, K, Npad) floats, for rows >= a.Mmax.
+size_t gemm_split_floats(int rows, int K, int npad);
 bool gemm_tanh_res_split(const GemmArgs &a, const float *bias, const int32_t *row_type,
                          int bias_ld, float *y, int ldy, float *tout, int ldt, float *scratch,
-                         size_t scratch_floats, hipStream_t s);
+                         hipStream_t s);
 // y = acc + b (b may be null); ybf16: y stored in BF16
 void gemm_linear(const GemmArgs &a, const float *bias, float *y, int ldy, hipStream_t s,
                  int ybf16 = 0);

@@ -15,6 +15,7 @@
 // 16-byte vectors along k straight from global memory (W is stored
 // transposed, Wt[n][k]); the k index of a 16-wide chunk is permuted
 // identically on both operands, which leaves the contraction unchanged.
+#include <algorithm>
 #include <type_traits>
 
 #include "dpa1_internal.h"
@@ -1432,19 +1433,27 @@ void gemm_tanh_res(const GemmArgs &a, const float *bias, const int32_t *row_type
   run(a, e, false, s);
 }
 
+// few rows: fewer than 64 row blocks of 64, so the unsplit product would
+// occupy a fraction of the CUs for the whole k loop
+constexpr int kSplitRows = 4096, kSplitDepth = 512;
+
+// Up to kFewRows rows the slices are added in LDS and need no scratch.
+size_t gemm_split_floats(int rows, int K, int npad) {
+  return K < kSplitDepth || rows <= kFewRows
+             ? 0
+             : (size_t)kFewSlices * std::min(rows, kSplitRows - 1) * npad;
+}
+
 bool gemm_tanh_res_split(const GemmArgs &a, const float *bias, const int32_t *row_type,
                          int bias_ld, float *y, int ldy, float *tout, int ldt, float *scratch,
-                         size_t scratch_floats, hipStream_t s) {
-  // few rows: fewer than 64 row blocks of 64, so the unsplit product would
-  // occupy a fraction of the CUs for the whole k loop
-  constexpr int kMaxRows = 4096, kSlices = kFewSlices, NT = 4;
+                         hipStream_t s) {
+  constexpr int kSlices = kFewSlices, NT = 4;
   const int M = a.Mmax;
-  if (a.Mptr || M <= 0 || M >= kMaxRows || a.K < 512 || (a.bf16 && a.xbf16) || !scratch)
+  if (a.Mptr || M <= 0 || M >= kSplitRows || a.K < kSplitDepth || (a.bf16 && a.xbf16))
     return false;
   const int kslice = ((a.K + kSlices - 1) / kSlices + 31) / 32 * 32;  // whole 32-deep chunks
   const int nslice = (a.K + kslice - 1) / kslice;
   const size_t slice = (size_t)M * a.Npad;
-  if ((size_t)nslice * slice > scratch_floats) return false;
   GemmArgs as = a;
   as.kslice = kslice;
   as.kreal = 0;

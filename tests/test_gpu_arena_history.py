@@ -1,0 +1,57 @@
+"""The same inputs give the same bits whatever the handle computed before.
+
+The first fitting layer is summed in slices for up to 4095 centres; whether it
+is must not depend on the size that earlier steps gave the workspace.  Sparse
+systems, whose own workspace is small, are computed on a fresh handle and again
+after a larger, denser system on the same handle.
+"""
+
+import numpy as np
+import pytest
+
+from paper_2604_07276_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+RC, SEL = 6.0, 120
+
+
+def dimers(atoms):
+    """Pairs of atoms 2 A apart, 9 A from each other: one neighbour to an atom."""
+    side = int(np.ceil((atoms / 2) ** (1 / 3)))
+    at = 9.0 * np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    x = np.repeat(at, 2, axis=0)
+    x[1::2, 0] += 2.0
+    x += np.random.default_rng(atoms).uniform(-0.2, 0.2, x.shape)
+    return x[:atoms], np.random.default_rng(1).integers(0, 5, atoms).astype(np.int32)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("model", ["student", "dpa1"])
+@pytest.mark.parametrize("atoms", [2, 15, 1024, 1025, 1500, 4095])
+def test_bits_do_not_depend_on_earlier_steps(atoms, model, precision, tmp_path):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_07276_amd import binding
+    print(f"case: {atoms} sparse atoms after a larger system, {model}, {precision}", flush=True)
+    p = str(tmp_path / "w.bin")
+    shape = synth.STUDENT_SHAPE if model == "student" else synth.ModelShape()
+    synth.make_weights(p, seed=3, shape=shape)
+    if atoms == 15:
+        s = synth.open_cluster(15, 5.0, 5, seed=15)
+        x, types = s.coords, s.types
+    else:
+        x, types = dimers(atoms)
+    n = max(1100, atoms + 1)
+    larger = synth.lattice_system(n, (n / 0.1) ** (1 / 3), (0.64, 0.10, 0.03, 0.22, 0.01), seed=0)
+    m = binding.Model(p, RC, SEL)
+    try:
+        m.set_precision(binding.PREC_FP32 if precision == "fp32" else binding.PREC_BF16)
+        first = m.compute(x, types, None, atoms, 0, True)
+        m.compute(larger.coords, larger.types, larger.box, n, 0)
+        again = m.compute(x, types, None, atoms, 0, True)
+    finally:
+        m.close()
+    assert first[0] == again[0]
+    assert all(np.array_equal(a, b) for a, b in zip(first[1:], again[1:]))
