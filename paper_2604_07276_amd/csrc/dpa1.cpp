@@ -86,6 +86,17 @@ int upload(dp_model *m, const std::vector<float> &h, float **out) {
   return DP_OK;
 }
 
+// Scales of the rows of w (ld entries each) as two-term f16 operands.
+std::vector<float> split_scales(const std::vector<float> &w, int ld) {
+  std::vector<float> up(w.size() / ld);
+  for (size_t r = 0; r < up.size(); ++r) {
+    float m = 0.f;
+    for (int k = 0; k < ld; ++k) m = std::max(m, std::fabs(w[r * ld + k]));
+    up[r] = split::scale_of(m).up;
+  }
+  return up;
+}
+
 // W is [fin][fout] row-major FP64.
 int make_linear(dp_model *m, const std::vector<double> &W, const std::vector<double> &b, int fin,
                 int fout, int ldin, int ldout, Linear &L) {
@@ -220,14 +231,12 @@ int dpa1::load_weights_image(dp_model *m, const std::vector<char> &buf, bool ref
     dp_model::Attn at = refresh ? m->attn[a] : dp_model::Attn{};
     std::vector<float> wt((size_t)3 * D * ldM, 0.f), wb((size_t)ldM * 3 * D, 0.f),
         bqkv(3 * D, 0.f);
-    at.qkv_max = at.o_max = 0.f;
     const std::vector<double> *Ws[3] = {&Wq, &Wk, &Wv};
     const std::vector<double> *Bs[3] = {&bq, &bk, &bv};
     for (int s = 0; s < 3; ++s) {
       for (int k = 0; k < Mw; ++k)
         for (int o = 0; o < D; ++o) {
           const float v = (float)(*Ws[s])[(size_t)k * D + o];
-          at.qkv_max = std::max(at.qkv_max, std::fabs(v));
           wt[(size_t)(s * D + o) * ldM + k] = v;
           wb[(size_t)k * 3 * D + s * D + o] = v;
         }
@@ -238,7 +247,6 @@ int dpa1::load_weights_image(dp_model *m, const std::vector<char> &buf, bool ref
     for (int k = 0; k < D; ++k)
       for (int o = 0; o < Mw; ++o) {
         const float v = (float)Wo[(size_t)k * Mw + o];
-        at.o_max = std::max(at.o_max, std::fabs(v));
         wto[(size_t)o * D + k] = v;
         wbo[(size_t)k * ldM + o] = v;
       }
@@ -247,7 +255,9 @@ int dpa1::load_weights_image(dp_model *m, const std::vector<char> &buf, bool ref
       gav[o] = (float)ga[o];
       bev[o] = (float)be[o];
     }
-    if ((rc = upload(m, wt, &at.Wt_qkv)) || (rc = upload(m, wb, &at.Wb_qkv)) ||
+    const std::vector<float> upq = split_scales(wb, 3 * D), upo = split_scales(wbo, ldM);
+    if ((rc = upload(m, upq, &at.up_qkv)) || (rc = upload(m, upo, &at.up_o)) ||
+        (rc = upload(m, wt, &at.Wt_qkv)) || (rc = upload(m, wb, &at.Wb_qkv)) ||
         (rc = upload(m, bqkv, &at.b_qkv)) || (rc = upload(m, wto, &at.Wt_o)) ||
         (rc = upload(m, wbo, &at.Wb_o)) || (rc = upload(m, bov, &at.b_o)) ||
         (rc = upload(m, gav, &at.gamma)) || (rc = upload(m, bev, &at.beta)))
@@ -856,7 +866,6 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
   }
   for (int a = na - 1; a >= 0; --a) {
     const auto &A = m->attn[a];
-    const split::Scale sqkv = split::scale_of(A.qkv_max), so = split::scale_of(A.o_max);
     if (m->recompute && m->shared_layer != a) {
       // the shared buffers hold another layer: recompute this layer's forward
       // from its stored input G[a] (the same kernels, so the same values)
@@ -877,7 +886,7 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
       }
       m->shared_layer = a;
     }
-    GemmArgs g1{w.dY, ldM, A.Wb_o, ldM, D, D, Pptr, Pmax, m->bf16, 0, m->M, 0, so.up, so.down};
+    GemmArgs g1{w.dY, ldM, A.Wb_o, ldM, D, D, Pptr, Pmax, m->bf16, 0, m->M, 0, A.up_o};
     if (!(desc_fused && a == na - 1))  // else dO came with the descriptor adjoint
       RUN("oproj_bwd", gemm_linear(g1, nullptr, w.dO, D, s, m->bf16));
     for (int cls = 0; cls < attn_class_count(sel); ++cls)
@@ -891,8 +900,8 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
       RUN("attn_bwd_k_n128", launch_attn_bwd_k(aa, w.qkv[a], w.dO, w.lam[a], w.dA, w.dqkv,
                                                w.astat, w.qside, w.gw, w.gr, a != na - 1, s));
     }
-    GemmArgs g2{w.dqkv, 3 * D, A.Wb_qkv, 3 * D, ldM, m->M,    Pptr,
-                Pmax,   m->bf16, m->bf16, 0,  0,   sqkv.up, sqkv.down};
+    GemmArgs g2{w.dqkv, 3 * D, A.Wb_qkv, 3 * D, ldM, m->M, Pptr, Pmax, m->bf16, m->bf16, 0, 0,
+                A.up_qkv};
     const int mode = a > 0 ? 0 : (emb_fused ? 2 : 1);
     const float *gam = a > 0 ? m->attn[a - 1].gamma : nullptr;
     const float *xh = a > 0 ? w.xhat[a - 1] : nullptr;

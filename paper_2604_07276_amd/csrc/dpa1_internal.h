@@ -97,9 +97,9 @@ struct GemmArgs {
   int xbf16;      // with bf16: X is stored in BF16 (row stride ldx in elements)
   int kreal;      // 0, or the depth up to which X and W hold data (zeros past it)
   int kslice;     // 0, or split k: grid slice z covers depths [z kslice, (z + 1) kslice)
-  // power-of-two scale of W for two-term f16 operands and its inverse
-  // (split.h); 0: FP32 matrix-core operands
-  float wup, wdown;
+  // power-of-two scales of the rows of W^T for two-term f16 operands (split.h);
+  // null: FP32 matrix-core operands
+  const float *wup;
 };
 
 enum ResMode { RES_NONE = 0, RES_IDENT = 1, RES_DOUBLE = 2, RES_BCAST = 3, RES_FOLD = 4 };

@@ -480,6 +480,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_lds(GemmArgs a, Epi epi) {
 // 4.9 TB/s), output projection 0.33 -> 0.28 ms (1.26 GB), against FP32 MFMAs
 // on 64-row (32-row) tiles.  Output columns past Nreal read a clamped W row
 // (the epilogue zeroes or skips them).
+// Every row of W^T (an output column) has its own scale, given back in the
+// epilogue: with one for the whole matrix a row 2^28 above the others (that of
+// a feature which is always zero may be) left them 11 bits.
 // KT = 1: X and W hold data only in the first four columns of the last 16-wide
 // chunk, KS ends there, and every lane group reads group 0's values of W
 // against X's zeros.
@@ -488,16 +491,20 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_gemm_split(GemmArgs a, Epi ep
   constexpr int KS = KT == 1 ? 16 * (KCH - 1) + 4 : 16 * KCH;  // staged depth
   // row stride of 4 mod 8 dwords: eight rows' 16-byte reads touch 32 banks
   constexpr int LDW = KS % 8 == 4 ? KS : KS + 4;
-  extern __shared__ float wsm[];  // packed W^T [nst][LDW], then the column vectors
+  // packed W^T [nst][LDW], its rows' inverse scales, then the column vectors
+  extern __shared__ float wsm[];
   split::packx4 *wp = (split::packx4 *)wsm;
   const int M = a.Mptr ? *a.Mptr : a.Mmax;
   const int nst = min(NT * 16, a.Nreal);  // staged rows of W^T
   for (int idx = threadIdx.x; idx < nst * (KS / 4); idx += 64 * WAVES) {
     const int n = idx / (KS / 4), c4 = idx % (KS / 4);
     const floatx4 v = *(const floatx4 *)(a.Wt + (size_t)n * a.K + 4 * c4);
-    wp[n * (LDW / 4) + c4] = split::pack(v * a.wup);
+    wp[n * (LDW / 4) + c4] = split::pack(v * a.wup[n]);
   }
-  float *cs = wsm + nst * LDW;  // [Epi::kCols][NT * 16]
+  const int nsc = (nst + 3) & ~3;
+  float *wd = wsm + nst * LDW;  // [nsc]
+  for (int n = threadIdx.x; n < nsc; n += 64 * WAVES) wd[n] = split::down_of(a.wup[min(n, nst - 1)]);
+  float *cs = wd + nsc;  // [Epi::kCols][NT * 16]
   stage_cols<Epi, NT>(epi, 0, a.Npad, cs);
   __syncthreads();
   const int wave = threadIdx.x >> 6;
@@ -544,9 +551,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_gemm_split(GemmArgs a, Epi ep
       for (int nt = 0; nt < NT; ++nt) acc[0][nt] = split::mfma(w[nt], hi, acc[0][nt]);
       x[0][c] = *(const floatx4 *)(xn + 16 * c);
     }
-    const float d = sc.down * a.wdown;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[0][nt] *= d;
+    for (int nt = 0; nt < NT; ++nt)
+      acc[0][nt] *= *(const floatx4 *)(wd + min(nt * 16 + 4 * g, nsc - 4)) * sc.down;
     epi.template apply<1, NT>(acc, row0, 0, ntt, lane, M, cs);
   }
 }
@@ -1181,7 +1188,7 @@ bool launch_split(const GemmArgs &a, const Epi &e, int per_cu, hipStream_t s) {
   constexpr int LDW = KS % 8 == 4 ? KS : KS + 4;
   static int ready[64];
   const int nst = a.Nreal < NT * 16 ? a.Nreal : NT * 16;
-  const size_t lds = sizeof(float) * ((size_t)nst * LDW + Epi::kCols * NT * 16);
+  const size_t lds = sizeof(float) * ((size_t)nst * LDW + (nst + 3) / 4 * 4 + Epi::kCols * NT * 16);
   if (lds > raised_lds(k_gemm_split<NT, KCH, KT, WAVES, Epi>, ready)) return false;
   const long tiles = (a.Mmax + WAVES * 16L - 1) / (WAVES * 16L);
   const long cap = (long)per_cu * cu_count();
@@ -1370,19 +1377,19 @@ void run(const GemmArgs &a, const Epi &e, bool full_rows, hipStream_t s) {
   // the load latency of each k step (measured best against 1, 2 and 8)
   if (!full_rows && a.Mmax < 65536 && nt > 4) nt = 4;
   // FP32 adjoints of the attention layers' projections over the 97- to
-  // 112-wide embedding (their weights come with a scale): two-term f16
+  // 112-wide embedding (their weights come with scales): two-term f16
   // operands, whatever the number of rows, so that a row's bits do not depend
   // on how many others there are (16 k rows 29 -> 24 us, 41 k rows 58 -> 39 us,
   // 1.31 M rows 1.15 -> 0.79 ms for QKV).  Widths above 105 do not fit LDS
   // with 384 deep rows and stay on FP32 operands.
   if constexpr (std::is_same_v<Epi, EpiLinear>) {
-    if (!a.bf16 && a.wup > 0.f && a.K == 112 && ntt == 8 &&
+    if (!a.bf16 && a.wup && a.K == 112 && ntt == 8 &&
         (a.kreal > 96 && a.kreal <= 100 ? launch_split<8, 7, 1, 8>(a, e, 2, s)
                                         : launch_split<8, 7, 4, 8>(a, e, 2, s)))
       return;
   }
   if constexpr (std::is_same_v<Epi, EpiQKVBwd>) {
-    if (!a.bf16 && a.wup > 0.f && a.K == 384 && ntt == 7 &&
+    if (!a.bf16 && a.wup && a.K == 384 && ntt == 7 &&
         launch_split<7, 24, 4, 8>(a, e, 1, s))
       return;
   }

@@ -57,6 +57,11 @@ __host__ __device__ __forceinline__ Scale scale_of(float m) {
   return s;
 }
 
+// The inverse of scale_of's up.
+__device__ __forceinline__ float down_of(float up) {
+  return __builtin_bit_cast(float, (254u << 23) - __builtin_bit_cast(uint32_t, up));
+}
+
 // Four scaled values, each as hi | lo << 16.
 __device__ __forceinline__ packx4 pack(const floatx4 &x) {
   packx4 o;

@@ -1,0 +1,86 @@
+"""How many bits the adjoint's two-term f16 operands keep.
+
+Force errors against the FP64 oracle, relative to the forces' root mean square
+and averaged likewise.  The whole model in FP32 (torch, logits included) is off
+by 1.1e-6 to 6.4e-6 on these systems; products whose lower terms are
+dropped, or whose operands are rounded to f16, by 2.5e-4 and more.  The bound is
+three times the former.
+
+Weights whose scales are far apart: a feature that is zero leaves its rows of
+W_QKV free, 2^28 above the others' here (a scale for the whole matrix would
+leave those 11 bits, 2.1e-4 and more in the forces).
+"""
+
+import numpy as np
+import pytest
+
+from oracle import dpa1_oracle as orc
+from paper_2604_07276_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+RC, SEL = 6.0, 120
+F_REL = 2e-5
+
+
+def compact_cluster(atoms, seed):
+    """The grid points nearest to a grid's centre, 0.95 A apart with a little jitter: every pair
+    of up to 121 atoms is within the cutoff."""
+    rng = np.random.default_rng(seed)
+    g = np.stack(np.meshgrid(*[np.arange(-4, 5) * 0.95] * 3, indexing="ij"), -1).reshape(-1, 3)
+    x = g[np.argsort((g * g).sum(1), kind="stable")[:atoms]]
+    return x + rng.uniform(-0.03, 0.03, x.shape), rng.integers(0, 5, atoms).astype(np.int32)
+
+
+def system(name):
+    kind, atoms = name[0], int(name[1:])
+    if kind == "c":
+        return compact_cluster(atoms, atoms - 1)
+    s = synth.open_cluster(atoms, {9: 4.0, 41: 4.0, 150: 9.0}[atoms], 5, seed=atoms)
+    return s.coords, s.types
+
+
+def dead_feature(t, m=17, e=28):
+    """Feature m of the attention layers' inputs is zero, its weights there 2^e of the others'."""
+    for name in ("emb2.W", "emb2.b", "attn0.ln_gamma", "attn0.ln_beta"):
+        t[name][..., m] = 0.0
+    for a in (0, 1):
+        for q in "qkv":
+            t[f"attn{a}.W{q}"][m] *= 2.0 ** e
+
+
+def check(shape, weights, name, tmp_path):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_07276_amd import binding
+    p = str(tmp_path / "w.bin")
+    synth.write_weights(p, shape, weights)
+    x, types = system(name)
+    m = binding.Model(p, RC, SEL)
+    try:
+        _, F, _, _ = m.compute(x, types, None, len(x), 0)
+    finally:
+        m.close()
+    r = orc.compute(orc.load_model(p), x, types, None, len(x), 0, RC, SEL).forces
+    err = np.sqrt(np.mean((F - r) ** 2) / np.mean(r ** 2))
+    print(f"relative force error {err:.1e}", flush=True)
+    assert err <= F_REL
+
+
+@pytest.mark.parametrize("name", ["o9", "o41", "o150", "c17", "c34", "c66", "c98", "c121"])
+@pytest.mark.parametrize("width", [97, 100, 104, 112])
+def test_split_operands_keep_fp32(width, name, tmp_path):
+    print(f"case: split operands, width {width}, system {name}", flush=True)
+    shape = synth.ModelShape(emb=(25, 50, width))
+    check(shape, synth.draw_weights(shape, 2), name, tmp_path)
+
+
+@pytest.mark.parametrize("name", ["o41", "c34", "c98"])
+@pytest.mark.parametrize("width", [97, 104, 105])
+def test_rows_of_other_scales(width, name, tmp_path):
+    print(f"case: a dead feature, width {width}, system {name}", flush=True)
+    shape = synth.ModelShape(emb=(25, 50, width))
+    t = synth.draw_weights(shape, 2)
+    dead_feature(t)
+    check(shape, t, name, tmp_path)
