@@ -20,8 +20,11 @@
  *
  * Precision: neighbour search and minimum-image pair vectors in FP64; the
  * network in FP32 (FP32 MFMA; the products of the attention adjoint on FP32
- * values split into two f16 terms, FP32 accumulation, errors no larger than
- * the FP32 MFMA's); energy, force and virial reductions in FP64.
+ * values split into two f16 terms with FP32 accumulation: 22 to 24 bits of
+ * every value down to 2^-17 of the largest in its row of an operand, 2^-39 of
+ * that one below, with each row scaled by itself and the weights' attention
+ * channels balanced when they are loaded); energy, force and virial reductions
+ * in FP64.
  * Results are deterministic: the same inputs give bit-identical outputs.
  *
  * Ownership: the caller owns every array it passes.  A dp_model owns its

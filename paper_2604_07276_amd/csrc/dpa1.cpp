@@ -97,6 +97,50 @@ std::vector<float> split_scales(const std::vector<float> &w, int ld) {
   return up;
 }
 
+// The two factors of an attention channel, W_Q and W_K (columns) or W_V (column)
+// and W_O (row), may trade a power of two without changing a bit of the logits
+// or of the output, but a row of Q, K, V or dO in which one channel lies far above
+// the others leaves these fewer bits as two-term f16 operands (with 2^26 on one
+// factor and 2^-26 on the other forces were off by 5e-5 of their size).  Factors
+// 2^16 or more apart are brought together; a factor beside a zero one has no
+// effect and becomes zero.  x[c], y[c]: the largest magnitude of channel c.
+// Returns by what power of two x is divided and y multiplied, per channel.
+constexpr int kDropChannel = INT_MIN;
+std::vector<int> balance_channels(const std::vector<double> &x, const std::vector<double> &y) {
+  std::vector<int> e(x.size(), 0);
+  for (size_t c = 0; c < x.size(); ++c) {
+    if (!std::isfinite(x[c]) || !std::isfinite(y[c]) || (x[c] == 0 && y[c] == 0)) continue;
+    if (x[c] == 0 || y[c] == 0) {
+      e[c] = kDropChannel;
+      continue;
+    }
+    const int apart = std::ilogb(x[c]) - std::ilogb(y[c]);
+    if (std::abs(apart) >= 16) e[c] = apart / 2;
+  }
+  return e;
+}
+
+// Largest magnitudes of the channels of w (its columns, or its rows), raised to
+// those already in m.
+void raise_max(std::vector<double> &m, const std::vector<double> &w, bool rows) {
+  const size_t ld = rows ? w.size() / m.size() : m.size();
+  for (size_t r = 0; r < w.size() / ld; ++r)
+    for (size_t c = 0; c < ld; ++c) {
+      double &v = m[rows ? r : c];
+      v = std::fabs(w[r * ld + c]) <= v ? v : std::fabs(w[r * ld + c]);  // (keeps a NaN)
+    }
+}
+void scale_channels(std::vector<double> &w, const std::vector<int> &e, int sign, bool rows) {
+  const size_t ld = rows ? w.size() / e.size() : e.size();
+  if (std::all_of(e.begin(), e.end(), [](int s) { return s == 0; })) return;
+  for (size_t r = 0; r < w.size() / ld; ++r)
+    for (size_t c = 0; c < ld; ++c) {
+      const int s = e[rows ? r : c];
+      double &v = w[r * ld + c];
+      if (s) v = s == kDropChannel ? 0.0 : std::ldexp(v, sign * s);
+    }
+}
+
 // W is [fin][fout] row-major FP64.
 int make_linear(dp_model *m, const std::vector<double> &W, const std::vector<double> &b, int fin,
                 int fout, int ldin, int ldout, Linear &L) {
@@ -228,6 +272,18 @@ int dpa1::load_weights_image(dp_model *m, const std::vector<char> &buf, bool ref
     std::vector<double> Wo = rd.arr((size_t)D * Mw), bo = rd.arr(Mw);
     std::vector<double> ga = rd.arr(Mw), be = rd.arr(Mw);
     if (!rd.ok) return fail(DP_ERR_WEIGHTS, "truncated weights");
+    {
+      std::vector<double> mq(D, 0.0), mk(D, 0.0), mv(D, 0.0), mo(D, 0.0);
+      raise_max(mq, Wq, false), raise_max(mq, bq, false);
+      raise_max(mk, Wk, false), raise_max(mk, bk, false);
+      raise_max(mv, Wv, false), raise_max(mv, bv, false);
+      raise_max(mo, Wo, true);
+      const std::vector<int> eqk = balance_channels(mq, mk), evo = balance_channels(mv, mo);
+      scale_channels(Wq, eqk, -1, false), scale_channels(bq, eqk, -1, false);
+      scale_channels(Wk, eqk, 1, false), scale_channels(bk, eqk, 1, false);
+      scale_channels(Wv, evo, -1, false), scale_channels(bv, evo, -1, false);
+      scale_channels(Wo, evo, 1, true);
+    }
     dp_model::Attn at = refresh ? m->attn[a] : dp_model::Attn{};
     std::vector<float> wt((size_t)3 * D * ldM, 0.f), wb((size_t)ldM * 3 * D, 0.f),
         bqkv(3 * D, 0.f);

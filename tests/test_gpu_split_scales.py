@@ -84,3 +84,25 @@ def test_rows_of_other_scales(width, name, tmp_path):
     t = synth.draw_weights(shape, 2)
     dead_feature(t)
     check(shape, t, name, tmp_path)
+
+
+def scaled_channel(t, what, f=17, e=30):
+    """Channel f of the attention layers: one factor 2^-e of itself (or zero), the other 2^e."""
+    for a in (0, 1):
+        low, high = {"vo": (("Wv", "bv"), ("Wo",)), "ov": (("Wo",), ("Wv", "bv")),
+                     "qk": (("Wq", "bq"), ("Wk", "bk")), "kq": (("Wk", "bk"), ("Wq", "bq"))}[what[:2]]
+        for names, factor in ((low, 0.0 if what.endswith("0") else 2.0 ** -e), (high, 2.0 ** e)):
+            for n in names:
+                w = t[f"attn{a}.{n}"]
+                w[(f,) if n == "Wo" else (..., f)] *= factor
+
+
+@pytest.mark.parametrize("name", ["o41", "c34", "c98"])
+@pytest.mark.parametrize("what", ["vo", "ov", "qk", "kq", "vo0", "ov0", "qk0", "kq0"])
+def test_channels_of_other_scales(what, name, tmp_path):
+    """V and W_O (or Q and K) trade a factor of 2^30 in one channel: the function is the same."""
+    print(f"case: channel scales {what}, system {name}", flush=True)
+    shape = synth.ModelShape()
+    t = synth.draw_weights(shape, 2)
+    scaled_channel(t, what)
+    check(shape, t, name, tmp_path)
