@@ -361,6 +361,20 @@ int dpa1::load_weights_image(dp_model *m, const std::vector<char> &buf, bool ref
     for (int a = 0; a < T; ++a) ebv[a] = (float)eb[a];
     m->b_out = (float)bo[0];
     if ((rc = upload(m, wov, &m->w_out))) return rc;
+    // The attention adjoint's two-term f16 operands take their scales from the
+    // range [2^-100, 2^127] of row maxima.  The adjoint is linear in w_out, so
+    // a model in a very large or small energy unit seeds it with w_out brought
+    // near one, and the forces are taken back in FP64.
+    m->seed = m->w_out;
+    double most = 0.0;
+    for (double v : wo) most = std::max(most, std::fabs(v));
+    const int unit = most > 0 && std::isfinite(most) ? std::ilogb(most) : 0;
+    if (m->n_attn > 0 && std::abs(unit) >= 32) {
+      for (int o = 0; o < m->fit.back(); ++o) wov[o] = (float)std::ldexp(wo[o], -unit);
+      m->seed = nullptr;
+      m->seed_unit = std::ldexp(1.0, unit);
+      if ((rc = upload(m, wov, &m->seed))) return rc;
+    }
     if ((rc = upload(m, ebv, &m->ebias))) return rc;
   }
   return DP_OK;
@@ -838,7 +852,8 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
                                  L.ldout, w.tf[l], L.ldout, s));
   }
   RUN("energy", launch_energy(w.z[nf - 1], w.tf[nf - 1], m->ldf[nf - 1], m->fit[nf - 1],
-                              m->w_out, m->b_out, m->ebias, d_types, nloc, w.e, w.fa[nf - 1], s));
+                              m->w_out, m->seed, m->b_out, m->ebias, d_types, nloc, w.e,
+                              w.fa[nf - 1], s));
   if (d_energy)
     RUN("reduce", launch_reduce(w.e, w.vir_part, nloc, d_energy, nullptr, d_atom_energy, s));
   HIP_TRY(hipGetLastError());
@@ -884,7 +899,7 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
     if (l == nf - 1) {
       if (L.res == RES_IDENT) {
         mode = RES_BCAST;
-        res = m->w_out;
+        res = m->seed;
       }
     } else {
       res = w.fdz[l];
@@ -984,7 +999,7 @@ int enqueue_backward(dp_model *m, const double *wgt, double sign, double *d_out,
   RUN("env_bwd", launch_env_bwd(w.geom, w.gs, w.dRt, na > 0 ? w.gw : nullptr,
                                 na > 0 ? w.gr : nullptr, Pptr, Pmax, 0.f, w.g, s));
   RUN("forces", launch_forces(d_coords, grid, nloc, nall, sel, w.nlist, w.nnei, w.pair_off, w.g,
-                              wgt, sign, d_out, w.vir_part, s));
+                              wgt, m->seed_unit, sign, d_out, w.vir_part, s));
   if (d_virial || d_energy)
     RUN("reduce", launch_reduce(w.e, w.vir_part, nloc, d_energy, d_virial, d_atom_energy, s));
   HIP_TRY(hipGetLastError());

@@ -257,21 +257,21 @@ void launch_desc_oproj_bwd(const float *geom, const float *G, const float *T, co
 // ---------------------------------------------------------------------------
 // energies, pair gradients, forces, virial (misc.hip)
 // ---------------------------------------------------------------------------
-// e_i = z3 . w_out + b_out + ebias[type_i]; a3 = w_out * (1 - t3^2).
+// e_i = z3 . w_out + b_out + ebias[type_i]; a3 = seed * (1 - t3^2).
 void launch_energy(const float *z3, const float *t3, int ld, int nfit, const float *w_out,
-                   float b_out, const float *ebias, const int32_t *types, int nloc, float *e,
-                   float *a3, hipStream_t s);
+                   const float *seed, float b_out, const float *ebias, const int32_t *types,
+                   int nloc, float *e, float *a3, hipStream_t s);
 // g_ij = de_i/dd_ij from the per-pair upstream gradients.
 void launch_env_bwd(const float *geom, const float *gs, const float *dRt, const float *gw,
                     const float *gr, const int *Mptr, int Mmax, float sel_inv_unused,
                     float *g, hipStream_t s);
 // Forces by a deterministic gather over the full neighbour lists, per-centre
 // virial partials and FP64 outputs.  With per-centre weights wgt (nullable =
-// all ones) the result is sign * (-sum_i wgt_i de_i/dx_k); sign = +1 gives
-// forces, sign = -1 the gradient of sum_i wgt_i e_i.
+// all ones) and g in units of unit the result is sign * (-sum_i wgt_i de_i/dx_k);
+// sign = +1 gives forces, sign = -1 the gradient of sum_i wgt_i e_i.
 void launch_forces(const double *coords, CellGrid grid, int nloc, int nall, int sel,
                    const int *nlist, const int *nnei, const int *pair_off, const float *g,
-                   const double *wgt, double sign, double *forces, double *vir_part,
+                   const double *wgt, double unit, double sign, double *forces, double *vir_part,
                    hipStream_t s);
 // E = sum e_i, Xi = sum of partials (fixed-order FP64 reductions); atom_energy.
 // energy == nullptr skips the energy part, virial == nullptr the virial part.

@@ -107,6 +107,9 @@ struct dp_model {
   std::vector<dpa1::Linear> fitl;     // layer 0 uses per-type bias fb0
   float *fb0 = nullptr;         // [ntypes][ldf[0]]
   float *w_out = nullptr;       // [ldf.back()]
+  // seeds of the adjoint, w_out in units of seed_unit (a power of two)
+  float *seed = nullptr;
+  double seed_unit = 1.0;
   float b_out = 0.f;
   float *ebias = nullptr;       // [ntypes]
   std::vector<void *> weight_allocs;

@@ -30,7 +30,8 @@ __device__ __forceinline__ void pair_vec(const double *__restrict__ x, int i, in
 // one wavefront per centre row: e_i and the fitting-net adjoint seed
 __global__ __launch_bounds__(256) void k_energy(const float *__restrict__ z3,
                                                 const float *__restrict__ t3, int ld, int nfit,
-                                                const float *__restrict__ w_out, float b_out,
+                                                const float *__restrict__ w_out,
+                                                const float *__restrict__ seed, float b_out,
                                                 const float *__restrict__ ebias,
                                                 const int32_t *__restrict__ types, int nloc,
                                                 float *__restrict__ e, float *__restrict__ a3) {
@@ -41,10 +42,9 @@ __global__ __launch_bounds__(256) void k_energy(const float *__restrict__ z3,
   for (int c = lane; c < ld; c += kWave) {
     float a = 0.f;
     if (c < nfit) {
-      const float w = w_out[c];
-      s += z3[(size_t)i * ld + c] * w;
+      s += z3[(size_t)i * ld + c] * w_out[c];
       const float t = t3[(size_t)i * ld + c];
-      a = w * (1.0f - t * t);
+      a = seed[c] * (1.0f - t * t);
     }
     a3[(size_t)i * ld + c] = a;
   }
@@ -110,8 +110,8 @@ __global__ __launch_bounds__(256) void k_forces(const double *__restrict__ x, Ce
                                                 const int *__restrict__ nnei,
                                                 const int *__restrict__ pair_off,
                                                 const float *__restrict__ g,
-                                                const double *__restrict__ wgt, double sign,
-                                                double *__restrict__ forces,
+                                                const double *__restrict__ wgt, double unit,
+                                                double sign, double *__restrict__ forces,
                                                 double *__restrict__ vir_part) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int k = blockIdx.x * 4 + wave;
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(256) void k_forces(const double *__restrict__ x, Ce
   for (int c = 0; c < 9; ++c) v[c] = 0.0;
   const bool local = k < nloc;
   const int base = local ? pair_off[k] : 0;
-  const double wk = (local && wgt) ? wgt[k] : 1.0;
+  const double wk = (local && wgt) ? unit * wgt[k] : unit;
   for (int s = lane; s < nk; s += kWave) {
     const int j = row[s];
     if (local) {
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void k_forces(const double *__restrict__ x, Ce
       const int t = find_slot(nlist + (size_t)j * sel, nnei[j], k);
       if (t >= 0) {
         const float4 gj = *(const float4 *)(g + 4 * (size_t)(pair_off[j] + t));
-        const double wj = wgt ? wgt[j] : 1.0;
+        const double wj = wgt ? unit * wgt[j] : unit;
         f0 -= wj * gj.x;
         f1 -= wj * gj.y;
         f2 -= wj * gj.z;
@@ -219,11 +219,11 @@ __global__ __launch_bounds__(512) void k_reduce(const float *__restrict__ e,
 }  // namespace
 
 void launch_energy(const float *z3, const float *t3, int ld, int nfit, const float *w_out,
-                   float b_out, const float *ebias, const int32_t *types, int nloc, float *e,
-                   float *a3, hipStream_t s) {
+                   const float *seed, float b_out, const float *ebias, const int32_t *types,
+                   int nloc, float *e, float *a3, hipStream_t s) {
   if (nloc <= 0) return;
   hipLaunchKernelGGL(k_energy, dim3((nloc + 3) / 4), dim3(256), 0, s, z3, t3, ld, nfit, w_out,
-                     b_out, ebias, types, nloc, e, a3);
+                     seed, b_out, ebias, types, nloc, e, a3);
 }
 
 void launch_env_bwd(const float *geom, const float *gs, const float *dRt, const float *gw,
@@ -235,11 +235,11 @@ void launch_env_bwd(const float *geom, const float *gs, const float *dRt, const 
 
 void launch_forces(const double *coords, CellGrid grid, int nloc, int nall, int sel,
                    const int *nlist, const int *nnei, const int *pair_off, const float *g,
-                   const double *wgt, double sign, double *forces, double *vir_part,
+                   const double *wgt, double unit, double sign, double *forces, double *vir_part,
                    hipStream_t s) {
   if (nall <= 0) return;
   hipLaunchKernelGGL(k_forces, dim3((nall + 3) / 4), dim3(256), 0, s, coords, grid, nloc, nall,
-                     sel, nlist, nnei, pair_off, g, wgt, sign, forces, vir_part);
+                     sel, nlist, nnei, pair_off, g, wgt, unit, sign, forces, vir_part);
 }
 
 void launch_reduce(const float *e, const double *vir_part, int nloc, double *energy,

@@ -14,11 +14,18 @@
 // two MFMAs (32 cycles) where FP32 takes four (128 cycles).
 //
 // The products of f16 terms are exact and the matrix core rounds once or so
-// per MFMA instead of once per depth: over 128 normally distributed depths
-// the result is off by 1.6e-7 of its root mean square, FP32 MFMAs by 2.0e-7
-// (positive operands: 8.6e-7 and 1.3e-6; the same at row scales of 1e-12 and
-// 1e9).  Scales are powers of two and so exact; f16 subnormals are not flushed
-// by these instructions.
+// per MFMA instead of once per depth.  Scales are powers of two and so exact;
+// f16 subnormals are not flushed by these instructions.  Forces on small systems
+// are off by 5e-7 to 2.7e-6 of their root mean square, where the whole model in
+// FP32 on the CPU is off by 1.1e-6 to 6.4e-6; without the lo terms it would be
+// 2.5e-4 and more (tests/test_gpu_split_scales.py bounds it at 2e-5).
+//
+// The bound on small values is one against the row's largest, so rows must not
+// hold values of very different scales that matter alike.  Each row of W^T and
+// of the pair tensors has a scale of its own, and the channels of W_Q and W_K,
+// and of W_V and W_O, are balanced when weights are loaded.  An infinite value
+// makes its row's products NaN; in FP32 they would be infinite or NaN, and NaN
+// after the next sum over features of both signs.
 //
 // Only products of the input-gradient adjoint take these operands.  The
 // forward up to the attention logits keeps FP32 MFMAs in their order: its

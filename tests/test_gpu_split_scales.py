@@ -106,3 +106,34 @@ def test_channels_of_other_scales(what, name, tmp_path):
     t = synth.draw_weights(shape, 2)
     scaled_channel(t, what)
     check(shape, t, name, tmp_path)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("e", [-120, -100, -62, -31, 31, 62, 120])
+def test_energy_unit(e, precision, tmp_path):
+    """Forces and virial are linear in w_out: in another energy unit (an eV is about 2^-62 joules)
+    they are the same times a power of two, to the bit."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_07276_amd import binding
+    print(f"case: energy unit 2^{e}, {precision}", flush=True)
+    x, types = system("o41")
+    shape = synth.ModelShape()
+    p = str(tmp_path / "w.bin")
+    got = []
+    for k in (0, e):
+        t = synth.draw_weights(shape, 2)
+        t["w_out"] = t["w_out"] * 2.0 ** k
+        t["b_out"] = t["b_out"] * 2.0 ** k
+        t["energy_bias"] = t["energy_bias"] * 2.0 ** k
+        synth.write_weights(p, shape, t)
+        m = binding.Model(p, RC, SEL)
+        try:
+            if precision == "bf16":
+                m.set_precision(binding.PREC_BF16)
+            _, F, V, _ = m.compute(x, types, None, len(x), 0)
+            got.append((F * 2.0 ** -k, V * 2.0 ** -k))
+        finally:
+            m.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
