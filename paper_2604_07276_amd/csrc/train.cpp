@@ -113,25 +113,29 @@ std::vector<char> make_image(const dp_trainer *t) {
   return img;
 }
 
+// Element n of an array, or null before there is one.
+float *at(float *p, size_t n) { return p ? p + n : nullptr; }
+
 // The weight-gradient products and sums of one frame of N atoms (before the first
-// frame, when the model has no workspace yet, for their sizes only).
+// frame, when neither the model nor the trainer has a workspace yet, for their
+// sizes only).
 TrWgrads weight_gradients(const dp_trainer *t, int N) {
   const dp_model *m = t->m;
   const auto &w = m->w;
   const int T = m->ntypes, H0 = m->fit[0], H1 = m->fit[1];
   const int ldD = m->ldD, ldf0 = m->ldf[0], ldf1 = m->ldf[1];
   const size_t Pst = ((size_t)N * m->sel + 15) / 16 * 16;
-  const int *Pdev = w.pair_off + N;
+  const int *Pdev = w.pair_off ? w.pair_off + N : nullptr;
   const int Pmax = (int)Pst;
   TrWgrads b;
-  b.product(w.dmat, t->Xd, ldD, t->Zb1, t->Zb1 + (size_t)N * ldf0, ldf0, m->M * m->axis, H0,
+  b.product(w.dmat, t->Xd, ldD, t->Zb1, at(t->Zb1, (size_t)N * ldf0), ldf0, m->M * m->axis, H0,
             nullptr, N, false, t->acc + t->o_W0d);
-  b.product(w.z.empty() ? nullptr : w.z[0], t->Yd1, ldf0, t->Zb2, t->Zb2 + (size_t)N * ldf1,
+  b.product(w.z.empty() ? nullptr : w.z[0], t->Yd1, ldf0, t->Zb2, at(t->Zb2, (size_t)N * ldf1),
             ldf1, H0, H1, nullptr, N, false, t->acc + t->o_W1f);
-  b.product(t->X3, t->X3 + Pst * kTrN2, kTrN2, t->Z3, t->Z3 + Pst * kTrN3, kTrN3, kTrN2, kTrN3,
-            Pdev, Pmax, true, t->acc + t->o_W3);
-  b.product(t->X2, t->X2 + Pst * kTrN1, kTrN1, t->Z2, t->Z2 + Pst * kTrN2, kTrN2, kTrN1, kTrN2,
-            Pdev, Pmax, true, t->acc + t->o_W2);
+  b.product(t->X3, at(t->X3, Pst * kTrN2), kTrN2, t->Z3, at(t->Z3, Pst * kTrN3), kTrN3, kTrN2,
+            kTrN3, Pdev, Pmax, true, t->acc + t->o_W3);
+  b.product(t->X2, at(t->X2, Pst * kTrN1), kTrN1, t->Z2, at(t->Z2, Pst * kTrN2), kTrN2, kTrN1,
+            kTrN2, Pdev, Pmax, true, t->acc + t->o_W2);
   b.colsum(t->Z3, kTrN3, kTrN3, Pdev, Pmax, true, nullptr, 1, t->acc + t->o_b3);
   b.colsum(t->Z2, kTrN2, kTrN2, Pdev, Pmax, true, nullptr, 1, t->acc + t->o_b2);
   b.colsum(t->Z1, kTrN1, kTrN1, Pdev, Pmax, true, t->grp, T * T, t->acc + t->o_tab);
@@ -148,7 +152,7 @@ int ensure_buffers(dp_trainer *t, int n, int nframes) {
   dp_model *m = t->m;
   const size_t P = ((size_t)cn * m->sel + 15) / 16 * 16;
   // pair operands: primal rows [0, P), tangent rows [P, 2 P)
-  const size_t ldr = 2 * P + 16;
+  const size_t ldr = 2 * P;
   const int ldD = m->ldD, ldf0 = m->ldf[0], ldf1 = m->ldf[1];
   const int nsq = tr_seed_blocks(cn);
   // per-centre GEMM operands keep one 16-row tile of slack
@@ -172,8 +176,8 @@ int ensure_buffers(dp_trainer *t, int n, int nframes) {
                oX3 = take(sizeof(float) * ldr * kTrN2), oZ3 = take(sizeof(float) * ldr * kTrN3),
                oX2 = take(sizeof(float) * ldr * kTrN1), oZ2 = take(sizeof(float) * ldr * kTrN2),
                oZ1 = take(sizeof(float) * ldr * kTrN1), oWS1 = take(sizeof(float) * ldr * kTrN1),
-               oGrp = take(sizeof(int) * (P + 16));
-  if (ldr * kTrN3 >= ((size_t)1 << 32))
+               oGrp = take(sizeof(int) * P);
+  if ((ldr + 16) * kTrN3 >= ((size_t)1 << 32))
     return fail(DP_ERR_ARG, "natoms * sel = %zu pair rows exceed the trainer's limit", P);
   const size_t oPart = take(sizeof(float) * weight_gradients(t, cn).room());
   if (t->arena) {

@@ -477,7 +477,7 @@ __global__ __launch_bounds__(64 * kTrWaves, 3) void k_tr_pair_rev(
       TileL12 x;
       tile_l12(a, w2, a.table + (size_t)(tj * a.ntypes + ti) * kTrN1, pt.s, lane, g, x);
       if (valid) {
-float *x2 = X2 + q * kTrN1, *x3 = X3 + q * kTrN2;
+        float *x2 = X2 + q * kTrN1, *x3 = X3 + q * kTrN2;
         *(floatx4 *)(x2 + row1) = x.h1;
         *(floatx4 *)(x2 + Pcap * kTrN1 + row1) = x.h1d;
 #pragma unroll
@@ -513,7 +513,7 @@ float *x2 = X2 + q * kTrN1, *x3 = X3 + q * kTrN2;
         *(floatx4 *)(ta + r * kTrRow + 16 * t + 4 * g) = zb;
         *(floatx4 *)(tb_ + r * kTrRow + 16 * t + 4 * g) = zbd;
         if (valid) {
-float *z3 = Z3 + q * kTrN3 + 16 * t;
+          float *z3 = Z3 + q * kTrN3 + 16 * t;
           *(floatx4 *)(z3 + row3) = zb;
           *(floatx4 *)(z3 + Pcap * kTrN3 + row3) = zbd;
         }
@@ -568,7 +568,7 @@ float *z3 = Z3 + q * kTrN3 + 16 * t;
         *(floatx4 *)pb = floatx4{zbd[0], hbd[t][0], zbd[1], hbd[t][1]};
         *(floatx4 *)(pb + 4) = floatx4{zbd[2], hbd[t][2], zbd[3], hbd[t][3]};
         if (valid) {
-float *z2 = Z2 + q * kTrN2 + 16 * t;
+          float *z2 = Z2 + q * kTrN2 + 16 * t;
           *(floatx4 *)(z2 + row2) = zb;
           *(floatx4 *)(z2 + Pcap * kTrN2 + row2) = zbd;
         }
