@@ -15,11 +15,12 @@
 // energy continuous when a neighbour crosses the cutoff (sw -> 0 turns its
 // logit into -S, the value the padding term stands for).
 //
-// Layout: one workgroup per centre, one wavefront per 16-neighbour tile
-// (n <= 128 -> at most 8 tiles).  All products run on
-// v_mfma_f32_16x16x4_f32.  Logit tiles are computed transposed, S^T = K Q^T,
-// so that lane l holds keys 4*(l/16)+{0..3} of query l%16: that register
-// layout is exactly the B operand of the next product (A V, dS K, ...),
+// Layout: one wavefront per 16-neighbour tile of a centre (n <= 128 -> at most 8
+// tiles), one centre or several to a workgroup.  Products run on the FP32 matrix
+// cores in the FP32 forward, on two-term f16 operands (split.h) in its adjoint,
+// and on BF16 operands in BF16 mode.  Logit tiles are computed transposed,
+// S^T = K Q^T, so that lane l holds keys 4*(l/16)+{0..3} of query l%16: that
+// register layout is exactly the B operand of the next product (A V, dS K, ...),
 // so probabilities never leave registers in the forward pass.
 #include <cfloat>
 
@@ -77,13 +78,6 @@ __device__ __forceinline__ float sum_groups(float v) {  // over lanes sharing la
 __device__ __forceinline__ float max_groups(float v) {
   v = fmaxf(v, __shfl_xor(v, 16));
   v = fmaxf(v, __shfl_xor(v, 32));
-  return v;
-}
-__device__ __forceinline__ float sum_rows(float v) {  // over the 16 lanes of a group
-  v += __shfl_xor(v, 1);
-  v += __shfl_xor(v, 2);
-  v += __shfl_xor(v, 4);
-  v += __shfl_xor(v, 8);
   return v;
 }
 
@@ -304,8 +298,7 @@ __device__ __forceinline__ void accum_lds2(const float *XT, int tile, int r, int
 }
 
 // The same contraction with the rows in row-major LDS (X[row][kLDR]): the A
-// operand is read with scalar LDS loads, four rows per lane group.
-// BF16: row tiles 'tile' and 'tile' + 1 in one 16x16x32 step.
+// operand is read with scalar LDS loads, four rows per lane group.  Row tiles 'tile' and 'tile' + 1 in one 16x16x32 step.
 __device__ __forceinline__ void accum_rows2(const float *X, int tile, int r, int g,
                                             const floatx4 &bt0, const floatx4 &bt1,
                                             floatx4 (&acc)[8]) {
@@ -676,7 +669,9 @@ __global__ __launch_bounds__(C * NPAD / 16 * 64, OP ? (C == 2 && NPAD == 96 ? 3 
 //   dS = dL w_q w_k / sqrt(d) ; dQ = dS K ; dK = dS^T Q
 //   X = dL (lam + S) + dH c  -> dw_q += sum_k X w_k, dw_k += sum_q X w_q
 //   Y = dH w_q w_k           -> drhat_q += sum_k Y rhat_k, drhat_k += sum_q Y rhat_q
-// Two kernels per class, both reading lam and (m, 1/Z) stored by the forward.
+// FP32 takes one kernel for every class (k_attn_bwd_s), BF16 one for the classes
+// of up to 96 neighbours (k_attn_bwd_f) and two for the 128 class; all read lam
+// and (m, 1/Z) stored by the forward.  The two:
 // k_attn_bwd_q (wave = query tile): dA^T from V staged row-major, then dS,
 // dQ (K^T staged) and the query-side sums; it writes dA in the layout of lam
 // (row = query, n columns), (m, 1/Z, D_q) and the query-side sums per pair.
@@ -686,15 +681,14 @@ __global__ __launch_bounds__(C * NPAD / 16 * 64, OP ? (C == 2 && NPAD == 96 ? 3 
 // (Q^T staged) and the key-side sums; it adds both sides into dE/dsw and
 // dE/drhat.
 
-template <int NPAD>
-__global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd_q(
+__global__ __launch_bounds__(512, 2) void k_attn_bwd_q(
     const float *__restrict__ qkv, const float *__restrict__ o, const float *__restrict__ dO,
     const float *__restrict__ geom, const int *__restrict__ pair_off,
     const int *__restrict__ nnei, const int *__restrict__ clist, const int *__restrict__ ccount,
     int sel, float shift, const float *__restrict__ lam, const float2 *__restrict__ fstat,
     float *__restrict__ dqkv, float4 *__restrict__ astat, float4 *__restrict__ qside,
     float *__restrict__ dA) {
-  constexpr int NT = NPAD / 16;
+  constexpr int NPAD = 128, NT = NPAD / 16;
   extern __shared__ float4 smem[];
   float4 *kg = smem;                     // [NPAD] rhat, sw
   float *buf = (float *)(kg + NPAD);     // V rows, then K^T
@@ -806,8 +800,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
   }
 }
 
-template <int NPAD>
-__global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd_k(
+__global__ __launch_bounds__(512, 2) void k_attn_bwd_k(
     const float *__restrict__ qkv, const float *__restrict__ dO,
     const float *__restrict__ geom, const int *__restrict__ pair_off,
     const int *__restrict__ nnei, const int *__restrict__ clist, const int *__restrict__ ccount,
@@ -815,7 +808,7 @@ __global__ __launch_bounds__(NPAD / 16 * 64, NPAD <= 96 ? 3 : 2) void k_attn_bwd
     float *__restrict__ dqkv, const float4 *__restrict__ astat,
     const float4 *__restrict__ qsbuf, float *__restrict__ gw, float *__restrict__ gr,
     int accumulate) {
-  constexpr int NT = NPAD / 16;
+  constexpr int NPAD = 128, NT = NPAD / 16;
   extern __shared__ float4 smem[];
   float4 *kg = smem;                     // [NPAD] rhat, sw
   float4 *stats = kg + NPAD;             // [NPAD] m, 1/Z, D_q of each query
@@ -1055,15 +1048,17 @@ __device__ __forceinline__ void accum_tr(const __bf16 *xt, int tile, const bf16x
 
 // The value of lane i ^ S of the 16 lanes of a group, on the vector ALU: a
 // rotation by 8, a permutation of quads, and for 4 a shift up for the even quads
-// and one down for the odd ones.
-template <int S>
-__device__ __forceinline__ float xor16(float x) {
-  if constexpr (S == 4) {
+// and one down for the odd ones.  MIRROR: of lane i ^ (2 S - 1) below 8, one
+// operation each; any lane across bit S does for a sum, in another order.
+template <int S, bool MIRROR>
+__device__ __forceinline__ float partner16(float x) {
+  if constexpr (S == 4 && !MIRROR) {
     const int v = __builtin_bit_cast(int, x);
     const int lo = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0x5, false);
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(lo, v, 0x114, 0xf, 0xa, false));
   } else {
-    return dpp<S == 8 ? kDppXor8 : S == 2 ? 0x4E : kDppXor1>(x);
+    constexpr int kXor2 = MIRROR ? kDppXor3 : 0x4E;
+    return dpp<S == 8 ? kDppXor8 : S == 4 ? kDppXor7 : S == 2 ? kXor2 : kDppXor1>(x);
   }
 }
 
@@ -1073,22 +1068,24 @@ __device__ __forceinline__ float xor16(float x) {
 // and the lane keeps one sum: a select between two array elements would be
 // turned into an indexed access and push the array out of registers.  On the
 // vector ALU, not through LDS: they were 180 of a wavefront's 480 LDS
-// operations (0.98 -> 0.94 ms a layer).
-template <int S>
+// operations in the BF16 adjoint (0.98 -> 0.94 ms a layer), which keeps the
+// order it had there; the FP32 one takes the cheaper mirrors.
+template <int S, bool MIRROR>
 __device__ __forceinline__ void halve16(float (&v)[16], int r) {
   const bool up = (r & S) != 0;
 #pragma unroll
   for (int j = 0; j < S; ++j) {
-    const float lo_t = v[j] + xor16<S>(v[j]);
-    const float hi_t = v[j + S] + xor16<S>(v[j + S]);
-    v[j] = up ? hi_t : lo_t;
+    const float lo = v[j] + partner16<S, MIRROR>(v[j]);
+    const float hi = v[j + S] + partner16<S, MIRROR>(v[j + S]);
+    v[j] = up ? hi : lo;
   }
 }
-__device__ __forceinline__ float reduce16_transposed(float (&v)[16], int r) {
-  halve16<8>(v, r);
-  halve16<4>(v, r);
-  halve16<2>(v, r);
-  halve16<1>(v, r);
+template <bool MIRROR>
+__device__ __forceinline__ float reduce16(float (&v)[16], int r) {
+  halve16<8, MIRROR>(v, r);
+  halve16<4, MIRROR>(v, r);
+  halve16<2, MIRROR>(v, r);
+  halve16<1, MIRROR>(v, r);
   return v[0];
 }
 
@@ -1267,7 +1264,7 @@ __global__ __launch_bounds__(768, 3) void k_attn_bwd_f(
         *(bf16x4 *)(Ds + q * LDF + kt * 16 + 4 * g) = dsb;
         // lane r now holds the wavefront's total of term r / 4 for key
         // 4g + r % 4 of this tile
-        const float kt_sum = reduce16_transposed(ks, r);
+        const float kt_sum = reduce16<false>(ks, r);
         ((float *)ksum)[(wave * NPAD + kt * 16 + 4 * g + (r & 3)) * 4 + (r >> 2)] = kt_sum;
         // dQ = dS K, tiles taken in pairs
         if (kt % 2 == 0) dsp = dsb;
@@ -1371,8 +1368,8 @@ __global__ __launch_bounds__(768, 3) void k_attn_bwd_f(
 
 // ---------------------------------------------------- adjoint, split operands
 //
-// The FP32 adjoint of one centre, one workgroup per centre, on two-term f16
-// operands (split.h).  Wavefront = tile of 16 keys: with its own V rows as the
+// The FP32 adjoint of a centre on two-term f16 operands (split.h), two centres of
+// the 96 class to a workgroup and one of the others.  Wavefront = tile of 16 keys: with its own V rows as the
 // MFMA's column operand and dO in LDS, dA comes out as lane (key r, queries
 // 4g + v), which is the column operand of dV = A^T dO and dK = dS^T Q as it
 // stands; only dS goes through LDS, for dQ = dS K (wavefront = tile of 16
@@ -1501,28 +1498,6 @@ __device__ __forceinline__ void store_rows(float *out, bool ok, const floatx4 (&
 #pragma unroll
     for (int f = 0; f < NF; ++f) *(floatx4 *)(out + 16 * f) = acc[f] * down;
   }
-}
-
-// Sum of 16 per-lane values over the 16 lanes of a lane group: after four
-// halving steps lane r holds the total of value r.
-__device__ __forceinline__ float reduce16_dpp(float (&v)[16], int r) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float lo = v[j] + dpp<kDppXor8>(v[j]), hi = v[j + 8] + dpp<kDppXor8>(v[j + 8]);
-    v[j] = (r & 8) ? hi : lo;
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float lo = v[j] + dpp<kDppXor7>(v[j]), hi = v[j + 4] + dpp<kDppXor7>(v[j + 4]);
-    v[j] = (r & 4) ? hi : lo;
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const float lo = v[j] + dpp<kDppXor3>(v[j]), hi = v[j + 2] + dpp<kDppXor3>(v[j + 2]);
-    v[j] = (r & 2) ? hi : lo;
-  }
-  const float lo = v[0] + dpp<kDppXor1>(v[0]), hi = v[1] + dpp<kDppXor1>(v[1]);
-  return (r & 1) ? hi : lo;
 }
 
 template <int NPAD>
@@ -1705,7 +1680,7 @@ __global__ __launch_bounds__(bwds_threads<NPAD>(), NPAD <= 96 ? 3 : 2) void k_at
           qs[12 + v] = Y * gk.z;
         }
         // lane r now holds the tile's total of term r / 4 for query 4g + r % 4
-        const float t = reduce16_dpp(qs, r);
+        const float t = reduce16<true>(qs, r);
         ((float *)qsum)[(wave * NPAD + qt * 16 + 4 * g + (r & 3)) * 4 + (r >> 2)] = t;
         lcur = lnxt;
         __builtin_amdgcn_sched_barrier(0);
@@ -2367,8 +2342,8 @@ hipError_t prepare_class(int dev, int cus, int cls) {
   } else if constexpr (NPAD <= 96) {
     if (e == hipSuccess) e = prepare(k_attn_bwd_f<NPAD>, 768, bwdf_lds<NPAD>(), 8);
   } else {
-    if (e == hipSuccess) e = prepare(k_attn_bwd_q<NPAD>, th, bwdq_lds<NPAD>(), 4);
-    if (e == hipSuccess) e = prepare(k_attn_bwd_k<NPAD>, th, bwdk_lds<NPAD>(), 5);
+    if (e == hipSuccess) e = prepare(k_attn_bwd_q, th, bwdq_lds<NPAD>(), 4);
+    if (e == hipSuccess) e = prepare(k_attn_bwd_k, th, bwdk_lds<NPAD>(), 5);
   }
   return e;
 }
@@ -2482,7 +2457,7 @@ void launch_attn_bwd_q(const AttnArgs &a, const float *qkv, const float *o, cons
                        const float *lam, const float *fstat, float *dqkv, float *astat,
                        float *qside, float *dA, hipStream_t s) {
   if (a.nloc <= 0) return;
-  hipLaunchKernelGGL(k_attn_bwd_q<128>, dim3(grid_for(4, 3)), dim3(512), bwdq_lds<128>(),
+  hipLaunchKernelGGL(k_attn_bwd_q, dim3(grid_for(4, 3)), dim3(512), bwdq_lds<128>(),
                      s, qkv, o, dO, a.geom, a.pair_off, a.nnei, a.clist + 3 * (size_t)a.nloc,
                      a.ccount + 3, a.sel, a.shift, lam, (const float2 *)fstat, dqkv,
                      (float4 *)astat, (float4 *)qside, dA);
@@ -2492,7 +2467,7 @@ void launch_attn_bwd_k(const AttnArgs &a, const float *qkv, const float *dO, con
                        const float *dA, float *dqkv, const float *astat, const float *qside,
                        float *gw, float *gr, int accumulate, hipStream_t s) {
   if (a.nloc <= 0) return;
-  hipLaunchKernelGGL(k_attn_bwd_k<128>, dim3(grid_for(5, 3)), dim3(512), bwdk_lds<128>(),
+  hipLaunchKernelGGL(k_attn_bwd_k, dim3(grid_for(5, 3)), dim3(512), bwdk_lds<128>(),
                      s, qkv, dO, a.geom, a.pair_off, a.nnei, a.clist + 3 * (size_t)a.nloc,
                      a.ccount + 3, a.shift, lam, dA, dqkv, (const float4 *)astat,
                      (const float4 *)qside, gw, gr, accumulate);
