@@ -23,6 +23,7 @@
 // register layout is exactly the B operand of the next product (A V, dS K, ...),
 // so probabilities never leave registers in the forward pass.
 #include <cfloat>
+#include <mutex>
 
 #include "attn_classes.h"
 #include "dpa1_internal.h"
@@ -2319,22 +2320,24 @@ hipError_t occupancy_grid(K kernel, int threads, size_t lds, int cus, int *out) 
 }
 
 template <int NPAD, bool BF>
-hipError_t prepare_class(int dev, int cus, int cls) {
+hipError_t prepare_class(int dev, int cus, int cls, int cols) {
   const int th = NPAD / 16 * 64;
-  const auto lds_limit = [](const void *kernel, size_t lds) {
-    return lds > 65536 ? hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)lds)
-                       : hipSuccess;
-  };
   const auto prepare = [&](auto kernel, int threads, size_t lds, int kind) {
-    const hipError_t r = lds_limit((const void *)kernel, lds);
-    return r == hipSuccess ? occupancy_grid(kernel, threads, lds, cus, &g_grid[dev][kind][cls]) : r;
+    int &grid = g_grid[dev][kind][cls];
+    if (grid > 0) return hipSuccess;
+    const hipError_t r =
+        lds > 65536 ? hipFuncSetAttribute((const void *)kernel,
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
+                    : hipSuccess;
+    return r == hipSuccess ? occupancy_grid(kernel, threads, lds, cus, &grid) : r;
   };
   constexpr int C = fwd_centres<NPAD>();
-  hipError_t e = prepare(k_attn_fwd<NPAD, BF, false, 1>, th, fwd_lds<NPAD>(1, 0), BF ? 3 : 0);
-  if (e == hipSuccess)
+  hipError_t e;
+  if (cols == 0)
+    e = prepare(k_attn_fwd<NPAD, BF, false, 1>, th, fwd_lds<NPAD>(1, 0), BF ? 3 : 0);
+  else if (cols <= kFwdMaxCols)
     e = prepare(k_attn_fwd<NPAD, BF, true, C>, C * th, fwd_lds<NPAD>(C, kFwdMaxCols), BF ? 9 : 7);
-  if (e == hipSuccess)
+  else
     e = prepare(k_attn_fwd<NPAD, BF, true, 1>, th, fwd_lds<NPAD>(1, kOpCols), BF ? 6 : 2);
   if constexpr (!BF) {
     if (e == hipSuccess)
@@ -2348,38 +2351,39 @@ hipError_t prepare_class(int dev, int cus, int cls) {
   return e;
 }
 
+template <bool BF>
+hipError_t prepare_classes(int dev, int cus, int classes, int cols) {
+  hipError_t e = prepare_class<32, BF>(dev, cus, 0, cols);
+  if (e == hipSuccess && classes > 1) e = prepare_class<64, BF>(dev, cus, 1, cols);
+  if (e == hipSuccess && classes > 2) e = prepare_class<96, BF>(dev, cus, 2, cols);
+  if (e == hipSuccess && classes > 3) e = prepare_class<128, BF>(dev, cus, 3, cols);
+  int &grid = g_desc_grid[dev][BF ? 1 : 0];
+  const int lds = (int)(sizeof(float) * kDoLds);
+  if (e == hipSuccess && grid <= 0) {
+    e = hipFuncSetAttribute((const void *)k_desc_oproj_bwd<BF>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e == hipSuccess) e = occupancy_grid(k_desc_oproj_bwd<BF>, 256, lds, cus, &grid);
+  }
+  return e;
+}
+
 }  // namespace
 
 int attn_class_count(int sel) { return sel <= 32 ? 1 : sel <= 64 ? 2 : sel <= 96 ? 3 : 4; }
 int attn_class_npad(int cls) { return 32 * (cls + 1); }
 
-hipError_t attn_prepare() {
+hipError_t attn_prepare(int sel, int cols, int bf16) {
+  static std::mutex lock;  // models are created in any thread
+  const std::lock_guard<std::mutex> guard(lock);
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  if (e == hipSuccess) e = prepare_class<32, false>(dev, cus, 0);
-  if (e == hipSuccess) e = prepare_class<64, false>(dev, cus, 1);
-  if (e == hipSuccess) e = prepare_class<96, false>(dev, cus, 2);
-  if (e == hipSuccess) e = prepare_class<128, false>(dev, cus, 3);
-  if (e == hipSuccess) e = prepare_class<32, true>(dev, cus, 0);
-  if (e == hipSuccess) e = prepare_class<64, true>(dev, cus, 1);
-  if (e == hipSuccess) e = prepare_class<96, true>(dev, cus, 2);
-  if (e == hipSuccess) e = prepare_class<128, true>(dev, cus, 3);
-  const int lds = (int)(sizeof(float) * kDoLds);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void *)k_desc_oproj_bwd<false>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void *)k_desc_oproj_bwd<true>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e == hipSuccess)
-    e = occupancy_grid(k_desc_oproj_bwd<false>, 256, lds, cus, &g_desc_grid[dev][0]);
-  if (e == hipSuccess)
-    e = occupancy_grid(k_desc_oproj_bwd<true>, 256, lds, cus, &g_desc_grid[dev][1]);
-  return e;
+  const int classes = attn_class_count(sel);
+  return bf16 ? prepare_classes<true>(dev, cus, classes, cols)
+              : prepare_classes<false>(dev, cus, classes, cols);
 }
 
 void launch_attn_classes(const int *nnei, int nloc, int active, int *ccount, int *clist,

@@ -702,6 +702,11 @@ bool attn_fwd_fuses_projection(const dp_model *m) {
   return m->ldM == kAttnOpCols && m->dattn == 128;
 }
 
+hipError_t prepare_attention(const dp_model *m, int bf16) {
+  if (m->n_attn == 0) return hipSuccess;
+  return attn_prepare(m->sel, attn_fwd_fuses_projection(m) ? m->M : 0, bf16);
+}
+
 #define RUN(name, call)                                           \
   do {                                                            \
     hipEvent_t a_ = nullptr, b_ = nullptr;                        \
@@ -1098,7 +1103,7 @@ int dp_create(const char *weights_path, double rcut, int sel, dp_model **out) {
       m->ccount_host[4] = -1;  // no counts yet: every class active
     }
     if (e == hipSuccess) e = hipStreamCreate(&m->own);
-    if (e == hipSuccess) e = attn_prepare();
+    if (e == hipSuccess) e = prepare_attention(m, 0);
     if (e != hipSuccess) rc = fail(DP_ERR_DEVICE, "device setup failed: %s", hipGetErrorString(e));
   }
   if (rc != DP_OK) {
@@ -1296,7 +1301,11 @@ int dp_set_precision(dp_model *m, int precision) {
   if (precision != DP_PREC_FP32 && precision != DP_PREC_BF16)
     return fail(DP_ERR_ARG, "unknown precision %d", precision);
   if (m->last) (void)hipStreamSynchronize(m->last);
-  m->bf16 = precision == DP_PREC_BF16;
+  const int bf16 = precision == DP_PREC_BF16;
+  int rc = set_device(m);
+  if (rc) return rc;
+  HIP_TRY(prepare_attention(m, bf16));
+  m->bf16 = bf16;
   m->fwd.valid = false;  // a pending adjoint must come from a forward in the new mode
   return DP_OK;
 }

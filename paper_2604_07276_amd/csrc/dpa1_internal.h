@@ -175,8 +175,11 @@ int attn_class_count(int sel);
 int attn_class_npad(int cls);
 // Row stride of the stored scaled logits (floats per pair).
 constexpr int kAttnLamLd = 128;
-// Per device, once: LDS limits of the large classes and persistent grid sizes.
-hipError_t attn_prepare();
+// LDS limits and persistent grid sizes of the kernels that a model can launch, once
+// per device (69 us a kernel: all 33 took 2.3 ms of the first model's creation):
+// the classes of sel, the forward with the projection to cols features (0:
+// without it), one precision.
+hipError_t attn_prepare(int sel, int cols, int bf16);
 // Class lists from the neighbour counts: ccount [4] (zeroed beforehand),
 // clist [4][nloc].
 // ccount [8]: centres listed per class [0..3], centres per neighbour-count
