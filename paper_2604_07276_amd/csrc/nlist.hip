@@ -547,7 +547,13 @@ void launch_nlist(const double *coords, int nloc, int nall, CellGrid grid, doubl
                   DevFlags *flags, hipStream_t s) {
   if (nall <= 0) return;
   const int ncell = grid.nc[0] * grid.nc[1] * grid.nc[2];
-  const int parts = std::max(1, std::min(4, 768 / ncell));  // workgroups of a cell
+  // Workgroups of a cell: as many as run at once on 256 CUs, three to each by LDS,
+  // and four at most (a cell of 22 atoms leaves each then fewer than its eight
+  // wavefronts take at once).  More than run at once stage tiles for nothing.  At
+  // 0.1 atoms per cubic A with 1, 2, 3, 4 workgroups: 64 cells 23.4, 17.0, 15.3,
+  // 12.3 us; 216 cells 26.0, 20.0, 18.6, 20.2; 343 cells 30.7, 24.7, 26.1, 26.8;
+  // 512 cells 31.1, 32.9, 33.6, 34.7.
+  const int parts = std::max(1, std::min(4, 768 / ncell));
   hipLaunchKernelGGL(k_nlist, dim3(ncell, parts), dim3(kWave * kCellWaves), 0, s, coords, nloc, grid,
                      rcut * rcut, sel, cell_start, cell_atoms, nlist, nnei, flags);
 }
