@@ -86,15 +86,14 @@ int upload(dp_model *m, const std::vector<float> &h, float **out) {
   return DP_OK;
 }
 
-// Scales of the rows of w (ld entries each) as two-term f16 operands.
-std::vector<float> split_scales(const std::vector<float> &w, int ld) {
-  std::vector<float> up(w.size() / ld);
-  for (size_t r = 0; r < up.size(); ++r) {
+// Appends the scales of the rows of w (ld entries each) as two-term f16 operands.
+void append_split_scales(std::vector<float> &w, int ld) {
+  const size_t rows = w.size() / ld;
+  for (size_t r = 0; r < rows; ++r) {
     float m = 0.f;
     for (int k = 0; k < ld; ++k) m = std::max(m, std::fabs(w[r * ld + k]));
-    up[r] = split::scale_of(m).up;
+    w.push_back(split::scale_of(m).up);
   }
-  return up;
 }
 
 // The two factors of an attention channel, W_Q and W_K (columns) or W_V (column)
@@ -311,13 +310,15 @@ int dpa1::load_weights_image(dp_model *m, const std::vector<char> &buf, bool ref
       gav[o] = (float)ga[o];
       bev[o] = (float)be[o];
     }
-    const std::vector<float> upq = split_scales(wb, 3 * D), upo = split_scales(wbo, ldM);
-    if ((rc = upload(m, upq, &at.up_qkv)) || (rc = upload(m, upo, &at.up_o)) ||
-        (rc = upload(m, wt, &at.Wt_qkv)) || (rc = upload(m, wb, &at.Wb_qkv)) ||
+    append_split_scales(wb, 3 * D);
+    append_split_scales(wbo, ldM);
+    if ((rc = upload(m, wt, &at.Wt_qkv)) || (rc = upload(m, wb, &at.Wb_qkv)) ||
         (rc = upload(m, bqkv, &at.b_qkv)) || (rc = upload(m, wto, &at.Wt_o)) ||
         (rc = upload(m, wbo, &at.Wb_o)) || (rc = upload(m, bov, &at.b_o)) ||
         (rc = upload(m, gav, &at.gamma)) || (rc = upload(m, bev, &at.beta)))
       return rc;
+    at.up_qkv = at.Wb_qkv + (size_t)ldM * 3 * D;
+    at.up_o = at.Wb_o + (size_t)D * ldM;
     if (refresh)
       m->attn[a] = at;
     else

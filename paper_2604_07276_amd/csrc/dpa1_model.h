@@ -101,7 +101,7 @@ struct dp_model {
   std::vector<dpa1::Linear> embl;     // layers 1..n_emb-1 (index l)
   struct Attn {
     float *Wt_qkv, *Wb_qkv, *b_qkv, *Wt_o, *Wb_o, *b_o, *gamma, *beta;
-    float *up_qkv, *up_o;  // split.h scales of the rows of Wb_qkv and Wb_o
+    float *up_qkv, *up_o;  // split.h scales of the rows of Wb_qkv and Wb_o, behind them
   };
   std::vector<Attn> attn;
   std::vector<dpa1::Linear> fitl;     // layer 0 uses per-type bias fb0
