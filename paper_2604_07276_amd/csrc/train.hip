@@ -101,15 +101,16 @@ __device__ __forceinline__ PairTangent pair_tangent(const float4 g0, const float
 //
 // The per-pair embedding passes run on the FP32 matrix cores, a wavefront
 // taking tiles of 16 pairs of its centre.  v_mfma_f32_16x16x4_f32 is, bit for
-// bit, a chain of fused multiply-adds over its four depths in order (checked on
-// the hardware over 1.5 M results), so a product over ascending depth started
-// from the bias gives the bits of the scalar loop z = fma(w[k], h[k], z), at
-// twice the vector unit's rate and without a scalar weight load per use.  With
-// weights as the row operand a lane receives, for pair r = lane % 16, outputs
-// 16 t + 4 g + {0..3} (g = lane / 16) of tile t; as the column operand of the
-// next product it has to hold depth 4 c + g in step c, which a turn through
-// wave-private LDS arranges (rows of 68 or 36 floats: no bank conflicts).
-// Weights sit in LDS in the order of the steps: 64 lanes' values side by side.
+// bit, a chain of fused multiply-adds over its four depths in order (the
+// gradients kept the bits that scalar loops had given them), so a product over
+// ascending depth started from the bias gives the bits of the scalar loop
+// z = fma(w[k], h[k], z), at twice the vector unit's rate and without a scalar
+// weight load per use.  With weights as the row operand a lane receives, for pair
+// r = lane % 16, outputs 16 t + 4 g + {0..3} (g = lane / 16) of tile t; as the
+// column operand of the next product it has to hold depth 4 c + g in step c,
+// which a turn through wave-private LDS arranges (rows of 68 or 36 floats: no
+// bank conflicts).  Weights sit in LDS in the order of the steps: 64 lanes'
+// values side by side.
 //
 // One lane per pair with scalar weights left a third of the lanes idle (84
 // neighbours in two chunks of 64) and, at 256 registers and more, one wavefront
