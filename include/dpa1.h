@@ -154,9 +154,7 @@ int dp_backward_device(dp_model *m, const double *d_atom_weight, double *d_grad_
  *                 softmax, layer norms and activations stay FP32, energy,
  *                 force and virial reductions FP64.
  * Applies to the steps enqueued after the call; waits for the handle's last
- * step.  The first call with BF16 on a model with attention and sel > 96 adds
- * buffers to the pair workspace if there is one.  Returns DP_ERR_ARG for any
- * other value, DP_ERR_OOM or DP_ERR_DEVICE when those buffers or the mode's
+ * step.  Returns DP_ERR_ARG for any other value, DP_ERR_DEVICE when the mode's
  * kernels cannot be prepared (the precision then stays as it was). */
 enum dp_precision { DP_PREC_FP32 = 0, DP_PREC_BF16 = 1 };
 int dp_set_precision(dp_model *m, int precision);

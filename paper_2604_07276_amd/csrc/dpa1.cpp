@@ -425,13 +425,6 @@ bool emb_is_fused(const dp_model *m) {
   return m->emb.size() == 3 && emb_fused_supported(m->lde[0], m->lde[1], m->lde[2]);
 }
 
-// The attention forward applies the output projection and layer norm itself
-// when the embedding width pads to kAttnOpCols columns and the attention
-// width is 128 (the shapes its kernel is built for).
-bool attn_fwd_fuses_projection(const dp_model *m) {
-  return m->ldM == kAttnOpCols && m->dattn == 128;
-}
-
 size_t carve_topo(dp_model *m, char *base, int nloc, int nall, int ncell) {
   Carver c{base};
   auto &w = m->w;
@@ -472,9 +465,6 @@ size_t carve_topo(dp_model *m, char *base, int nloc, int nall, int ncell) {
   return c.off + 256;
 }
 
-// The BF16 adjoint of the 128 class is in two kernels, which read o and hand dL/dA
-// and per-pair sums on; nothing else needs those buffers once the forward applies
-// the output projection itself (392 of 2,880 floats a pair row of two layers).
 size_t carve_pairs(dp_model *m, char *base, size_t P, bool shared) {
   Carver c{base};
   auto &w = m->w;
@@ -507,7 +497,7 @@ size_t carve_pairs(dp_model *m, char *base, size_t P, bool shared) {
       w.fstat[a] = w.fstat[0];
     } else {
       w.qkv[a] = c.take<float>(P * 3 * m->dattn);
-      if (m->two_kernels || !attn_fwd_fuses_projection(m)) w.o[a] = c.take<float>(P * m->dattn);
+      w.o[a] = c.take<float>(P * m->dattn);
       w.lam[a] = c.take<float>(P * kAttnLamLd);
       w.fstat[a] = c.take<float>(P * 2);
     }
@@ -527,12 +517,9 @@ size_t carve_pairs(dp_model *m, char *base, size_t P, bool shared) {
   w.gr = c.take<float>(P * 4);
   w.gs = c.take<float>(P);
   w.g = c.take<float>(P * 4);
-  w.astat = w.qside = w.dA = nullptr;
-  if (m->two_kernels) {
-    w.astat = c.take<float>(P * 4);
-    w.qside = c.take<float>(P * 4);
-    w.dA = c.take<float>(P * kAttnLamLd);
-  }
+  w.astat = c.take<float>(P * 4);
+  w.qside = c.take<float>(P * 4);
+  w.dA = m->n_attn > 0 ? c.take<float>(P * kAttnLamLd) : nullptr;
   w.du.assign(ne, nullptr);
   w.dh.assign(ne, nullptr);
   if (!fused)
@@ -579,11 +566,14 @@ int ensure_workspace(dp_model *m, int nloc, int nall, int ncell) {
   return DP_OK;
 }
 
-// Lays the pair arena out for cap rows (synchronous; the caller has synchronised
-// the stream).  Every layer's attention activations are stored unless that
-// exceeds the memory budget (then shared buffers and recomputation in the
-// adjoint).
-int lay_pairs(dp_model *m, long cap) {
+// Lays out the pair arena for at least `pairs` rows (synchronous; the caller
+// has synchronised the stream).  Every layer's attention activations are
+// stored unless that exceeds the memory budget (then shared buffers and
+// recomputation in the adjoint).
+int ensure_pairs(dp_model *m, long pairs) {
+  const long cap_max = (long)m->cap_nloc * m->sel;
+  long cap = pairs + pairs / 8;
+  cap = std::min(std::max(cap, pairs), cap_max);
   const size_t P = (size_t)cap + 64;
   const dp_model::WS saved = m->w;
   const size_t full = carve_pairs(m, nullptr, P, false);
@@ -595,28 +585,21 @@ int lay_pairs(dp_model *m, long cap) {
     return fail(DP_ERR_OOM, "workspace of %zu bytes exceeds the memory budget of %.0f bytes%s",
                 bytes + m->arena_bytes, m->mem_budget,
                 m->n_attn > 1 ? " even with recomputation" : "");
-  m->cap_pairs = -1;  // no layout until this one is complete
-  m->fwd.valid = false;
   if (m->parena) {
     HIP_TRY(hipFree(m->parena));
     m->parena = nullptr;
     m->parena_bytes = 0;
   }
   HIP_TRY(hipMalloc(&m->parena, bytes));
-  m->parena_bytes = bytes;
   HIP_TRY(hipMemset(m->parena, 0, bytes));
+  m->parena_bytes = bytes;
   carve_pairs(m, (char *)m->parena, P, shared);
   m->recompute = shared;
   m->cap_pairs = cap;
   m->cap_pairs_nloc = m->cap_nloc;
   m->want_pairs = 0;
+  m->fwd.valid = false;
   return DP_OK;
-}
-
-// At least `pairs` rows.
-int ensure_pairs(dp_model *m, long pairs) {
-  const long cap_max = (long)m->cap_nloc * m->sel;
-  return lay_pairs(m, std::min(std::max(pairs + pairs / 8, pairs), cap_max));
 }
 
 // ---------------------------------------------------------------- validation
@@ -712,6 +695,13 @@ const char *const kAttnFwdLnName[4] = {"attn_fwd_ln_n32", "attn_fwd_ln_n64", "at
                                        "attn_fwd_ln_n128"};
 const char *const kAttnBwdName[4] = {"attn_bwd_n32", "attn_bwd_n64", "attn_bwd_n96",
                                      "attn_bwd_n128"};
+
+// The attention forward applies the output projection and layer norm itself
+// when the embedding width pads to kAttnOpCols columns and the attention
+// width is 128 (the shapes its kernel is built for).
+bool attn_fwd_fuses_projection(const dp_model *m) {
+  return m->ldM == kAttnOpCols && m->dattn == 128;
+}
 
 hipError_t prepare_attention(const dp_model *m, int bf16) {
   if (m->n_attn == 0) return hipSuccess;
@@ -1316,15 +1306,6 @@ int dp_set_precision(dp_model *m, int precision) {
   int rc = set_device(m);
   if (rc) return rc;
   HIP_TRY(prepare_attention(m, bf16));
-  if (bf16 && m->n_attn > 0 && attn_class_count(m->sel) == 4 && !m->two_kernels) {
-    // laid out here, since the next step may be under capture (not if that one
-    // has to lay it out anyway)
-    m->two_kernels = true;
-    if (m->want_pairs <= m->cap_pairs && (rc = lay_pairs(m, m->cap_pairs))) {
-      m->two_kernels = false;
-      return rc;
-    }
-  }
   m->bf16 = bf16;
   m->fwd.valid = false;  // a pending adjoint must come from a forward in the new mode
   return DP_OK;

@@ -123,7 +123,6 @@ struct dp_model {
   int cap_pairs_nloc = -1; // topology capacity the pair arena was laid out with
   long want_pairs = 0;     // pair count of a step that outgrew the arena
   double mem_budget = 0;   // workspace budget in bytes (0: unlimited)
-  bool two_kernels = false;  // the pair buffers serve the BF16 adjoint of the 128 class too
   bool recompute = false;  // attention activations shared across layers, recomputed
   int shared_layer = -1;   // layer whose activations the shared buffers hold
   struct WS {
