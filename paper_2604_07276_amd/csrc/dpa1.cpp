@@ -585,20 +585,21 @@ int ensure_pairs(dp_model *m, long pairs) {
     return fail(DP_ERR_OOM, "workspace of %zu bytes exceeds the memory budget of %.0f bytes%s",
                 bytes + m->arena_bytes, m->mem_budget,
                 m->n_attn > 1 ? " even with recomputation" : "");
+  m->cap_pairs = -1;  // no layout until this one is complete
+  m->fwd.valid = false;
   if (m->parena) {
     HIP_TRY(hipFree(m->parena));
     m->parena = nullptr;
     m->parena_bytes = 0;
   }
   HIP_TRY(hipMalloc(&m->parena, bytes));
-  HIP_TRY(hipMemset(m->parena, 0, bytes));
   m->parena_bytes = bytes;
+  HIP_TRY(hipMemset(m->parena, 0, bytes));
   carve_pairs(m, (char *)m->parena, P, shared);
   m->recompute = shared;
   m->cap_pairs = cap;
   m->cap_pairs_nloc = m->cap_nloc;
   m->want_pairs = 0;
-  m->fwd.valid = false;
   return DP_OK;
 }
 
@@ -733,6 +734,8 @@ int enqueue_forward(dp_model *m, const double *d_coords, const int32_t *d_types,
   const int *Pptr = w.pair_off + nloc;
   const int ne = (int)m->emb.size(), na = m->n_attn, nf = (int)m->fit.size();
 
+  // an earlier forward's adjoint is over, also when this one does not get through
+  m->fwd.valid = false;
   if (nall <= kBinAtoms && grid.ncell <= kBinCells) {
     RUN("cells", launch_bin_small(d_coords, d_types, nall, m->ntypes, grid, m->flags, w.ccount,
                                   w.types_safe, w.cell_start, w.cell_atoms, s));

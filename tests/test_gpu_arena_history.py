@@ -55,3 +55,48 @@ def test_bits_do_not_depend_on_earlier_steps(atoms, model, precision, tmp_path):
         m.close()
     assert first[0] == again[0]
     assert all(np.array_equal(a, b) for a, b in zip(first[1:], again[1:]))
+
+
+def test_adjoint_of_a_refused_forward(tmp_path):
+    """A forward that is refused for its memory leaves no earlier forward to differentiate (its
+    pair offsets are the new system's by then), and the handle goes on with what fits."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_07276_amd import binding
+    print("case: adjoint after a forward over the memory budget, 150 atoms", flush=True)
+    p = str(tmp_path / "w.bin")
+    synth.make_weights(p, seed=3)
+    c = synth.open_cluster(150, 9.0, 5, seed=9)
+    dev = torch.device("cuda:0")
+    x0 = torch.tensor(c.coords, device=dev)
+    x1 = 0.7 * x0  # more than twice the neighbour pairs
+    t = torch.tensor(c.types, device=dev)
+    e = torch.zeros(1, dtype=torch.float64, device=dev)
+    g = torch.zeros((150, 3), dtype=torch.float64, device=dev)
+    m = binding.Model(p, RC, SEL)
+    try:
+        m.forward_device(x0, t, None, 150, 0, e)
+        m.backward_device(g)
+        m.sync()
+        want = g.clone()
+        m.set_memory_budget(m.memory_info()[0])
+        m.forward_device(x0, t, None, 150, 0, e)
+        m.sync()
+        m.forward_device(x1, t, None, 150, 0, e)
+        with pytest.raises(binding.DPError) as ei:
+            m.sync()
+        assert ei.value.code == -8
+        with pytest.raises(binding.DPError) as ei:
+            m.forward_device(x1, t, None, 150, 0, e)
+        assert ei.value.code == -7
+        with pytest.raises(binding.DPError) as ei:
+            m.backward_device(g)
+        assert ei.value.code == -1
+        m.set_memory_budget(0)
+        m.forward_device(x0, t, None, 150, 0, e)
+        m.backward_device(g)
+        m.sync()
+        assert torch.equal(g, want)
+    finally:
+        m.close()
