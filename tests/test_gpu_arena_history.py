@@ -100,3 +100,52 @@ def test_adjoint_of_a_refused_forward(tmp_path):
         assert torch.equal(g, want)
     finally:
         m.close()
+
+
+@pytest.mark.parametrize("atoms", [192, 2000, 9000])
+def test_captured_steps_of_both_precisions(atoms, tmp_path):
+    """Steps captured in FP32 and, after the precision was set and without a step in between, in
+    BF16 on one handle: both graphs replay in turn, on other coordinates, with an eager step's
+    bits."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_07276_amd import binding
+    print(f"case: captured steps, {atoms} atoms", flush=True)
+    p = str(tmp_path / "w.bin")
+    synth.make_weights(p, seed=3)
+    s = synth.lattice_system(atoms, (atoms / 0.1) ** (1 / 3), (0.64, 0.10, 0.03, 0.22, 0.01), seed=0)
+    dev = torch.device("cuda:0")
+    x0 = torch.tensor(s.coords, device=dev)
+    x, t = x0.clone(), torch.tensor(s.types, device=dev)
+
+    def outputs():
+        return [torch.zeros(k, dtype=torch.float64, device=dev) for k in (1, (atoms, 3), 9)]
+
+    m, eager = binding.Model(p, RC, SEL), binding.Model(p, RC, SEL)
+    try:
+        got, graphs = {}, {}
+        for prec in (binding.PREC_FP32, binding.PREC_BF16):
+            m.set_precision(prec)
+            got[prec] = outputs()
+            if prec == binding.PREC_FP32:
+                m.compute_device(x, t, s.box, atoms, 0, *got[prec])
+                m.sync()
+            torch.cuda.synchronize()
+            graphs[prec] = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graphs[prec]):
+                m.compute_device(x, t, s.box, atoms, 0, *got[prec])
+        for k in range(3):
+            noise = np.random.default_rng(k).normal(0.0, 0.01, (atoms, 3))
+            x.copy_(x0 + torch.tensor(noise, device=dev))
+            for prec, graph in graphs.items():
+                graph.replay()
+                torch.cuda.synchronize()
+                eager.set_precision(prec)
+                want = outputs()
+                eager.compute_device(x, t, s.box, atoms, 0, *want)
+                eager.sync()
+                assert all(torch.equal(a, b) for a, b in zip(got[prec], want))
+    finally:
+        m.close()
+        eager.close()

@@ -17,22 +17,12 @@ import numpy as np
 import pytest
 
 import bf16_oracle
+from clusters import compact_cluster
 from oracle import dpa1_oracle as orc
 from paper_2604_07276_amd import synth
 
 RC, SEL = 6.0, 120
 NEIGHBOURS = [16, 31, 32, 33, 63, 64, 65, 95, 96, 97, 120]
-
-
-def compact_cluster(atoms, seed):
-    """The grid points nearest to a grid's centre, 0.95 A apart with a little jitter: every pair
-    of up to 121 atoms is within the cutoff."""
-    rng = np.random.default_rng(seed)
-    g = np.stack(np.meshgrid(*[np.arange(-4, 5) * 0.95] * 3, indexing="ij"), -1).reshape(-1, 3)
-    x = g[np.argsort((g * g).sum(1), kind="stable")[:atoms]]
-    x = x + rng.uniform(-0.03, 0.03, x.shape)
-    # (differences are exact at every offset)
-    return np.round(x * 2.0 ** 20) / 2.0 ** 20, rng.integers(0, 5, atoms).astype(np.int32)
 
 
 @pytest.mark.gpu
@@ -53,6 +43,7 @@ def test_copies_equal_one(neighbours, precision, tmp_path):
     p = str(tmp_path / "w.bin")
     synth.make_weights(p, seed=2)
     x, types = compact_cluster(n, neighbours)
+    x = np.round(x * 2.0 ** 20) / 2.0 ** 20  # differences are exact at every offset
     side = int(np.ceil(copies ** (1 / 3)))
     at = 32.0 * np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), -1).reshape(-1, 3)
     many = (at[:copies, None, :] + x).reshape(-1, 3)

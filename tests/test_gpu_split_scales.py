@@ -14,6 +14,7 @@ leave those 11 bits, 2.1e-4 and more in the forces).
 import numpy as np
 import pytest
 
+from clusters import compact_cluster
 from oracle import dpa1_oracle as orc
 from paper_2604_07276_amd import synth
 
@@ -21,15 +22,6 @@ pytestmark = pytest.mark.gpu
 
 RC, SEL = 6.0, 120
 F_REL = 2e-5
-
-
-def compact_cluster(atoms, seed):
-    """The grid points nearest to a grid's centre, 0.95 A apart with a little jitter: every pair
-    of up to 121 atoms is within the cutoff."""
-    rng = np.random.default_rng(seed)
-    g = np.stack(np.meshgrid(*[np.arange(-4, 5) * 0.95] * 3, indexing="ij"), -1).reshape(-1, 3)
-    x = g[np.argsort((g * g).sum(1), kind="stable")[:atoms]]
-    return x + rng.uniform(-0.03, 0.03, x.shape), rng.integers(0, 5, atoms).astype(np.int32)
 
 
 def system(name):
